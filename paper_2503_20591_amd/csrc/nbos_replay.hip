@@ -365,6 +365,18 @@ template <uint32_t F> void set_reg_closed_kernel(nbos_replay *h, int nj) {
   set_kernel(h, reg_closed_kernel_for<F>(nj), "regk::nbos_replay_reg_closed_kernel<%d, %uu>", nj > 8 ? 8 : nj, F);
 }
 
+// the Batch baseline's kernel for clusters of up to 64, 128, 256, 512, 768 or 1,024 hosts (the keys of all its
+// hosts are unrolled over registers: a kernel for more hosts than there are looks at the others for nothing);
+// returns the chunks of 64 hosts it is compiled for
+template <int NCH> int set_batch_kernel_of(nbos_replay *h) {
+  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NCH>, "batchk::nbos_replay_batch_kernel<%d>", NCH, 0u);
+  return NCH;
+}
+int set_batch_kernel(nbos_replay *h, int chunks) {
+  return chunks <= 1 ? set_batch_kernel_of<1>(h) : chunks <= 2 ? set_batch_kernel_of<2>(h) : chunks <= 4 ? set_batch_kernel_of<4>(h)
+         : chunks <= 8 ? set_batch_kernel_of<8>(h) : chunks <= 12 ? set_batch_kernel_of<12>(h) : set_batch_kernel_of<16>(h);
+}
+
 // which flavour of the register kernel: see the comment inside
 int32_t choose_reg_kernel(nbos_replay *h, int maxlds) {
   const nbos_config *cfg = &h->cfg;
@@ -428,9 +440,10 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
   const size_t n_cap = (size_t)sh->n_cap;
   const bool force_generic = (cfg->flags & NBOS_F_GENERIC_KERNEL) != 0;
   if (batch_mode) {
-    h->lds_bytes = 64 + 64 + 128 + (size_t)HP * (32 + 4) + 2 * NGPU * batchk::NCH * 4 + n_cap * 12 + (n_cap + 2) * 2;
+    // a row of 32 bytes per host, a record of 8 bytes and a place in the queue per session
+    const int chunks = set_batch_kernel(h, HP / WAVE);
+    h->lds_bytes = (size_t)chunks * WAVE * 32 + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
-    set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel, "batchk::nbos_replay_batch_kernel%.0u", -1, 0u);
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
     // hosts in registers; 8 bytes per session, 64 staged sessions
     h->lds_bytes = 64 + 64 + 128 + (warm_pool ? (size_t)WAVE * 16 : 0) + n_cap * 8 + WAVE * 4;

@@ -1,0 +1,32 @@
+"""The kernels at the edges of what each instance is compiled for, against the CPU oracle, bit for bit
+(all outputs are integers: no tolerance)."""
+import numpy as np
+import pytest
+
+from paper_2503_20591_amd import tracegen as tg
+from test_gpu_parity import as_batch, assert_same, gpu_run, rp  # noqa: F401  (rp: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def crowded(seed, hosts, G, sessions_per_host, cells_per_session, gap_s=5.0, dur_s=300.0, with_end=False):
+    """A trace that fills ``hosts`` hosts of ``G`` GPUs: queues, blocked heads, several completions between events."""
+    return tg.make_trace(seed, hosts * sessions_per_host, hosts * sessions_per_host * cells_per_session, ramp_ms=60_000,
+                         gpus=lambda r, n: np.minimum(tg.gpus_uniform(r, n), G).astype(np.uint8),
+                         gap=lambda r, s: tg.exp_ms(r, gap_s, s), dur=lambda r, s: tg.lognormal_ms(r, dur_s, 1.0, s),
+                         with_end=with_end)
+
+
+@pytest.mark.parametrize("grow", [False, True], ids=["fixed", "grow"])
+@pytest.mark.parametrize("hosts,G", [(1, 8), (2, 1), (63, 8), (64, 3), (65, 8), (128, 2), (129, 1), (256, 4), (257, 3), (512, 2),
+                                     (513, 1), (768, 2), (769, 3), (1024, 1), (1024, 2)])
+def test_batch_kernel_at_its_chunk_edges(rp, oracle, hosts, G, grow):  # noqa: F811
+    # one kernel for up to 64, 128, 256, 512, 768, 1,024 hosts; rows of fewer than 8 GPUs are padded
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, gpus_per_host=G),
+                [crowded(7, hosts, G, 3, 3), crowded(8, hosts, G, 2, 2)], [0, 1, 0], [1000, 1000, 1000], f"edge{hosts}")
+    as_batch(b, delay=15_000, scale_out=grow)
+    if grow:
+        b.config.update(hosts_initial=max(1, hosts - 40), hosts_max=hosts, boot_delay_ms=20_000)
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert st["cells_queued"].max() > 0
