@@ -169,23 +169,49 @@ __device__ __forceinline__ uint32_t instance_flags(const KParams &p) {
 constexpr int32_t CLX_LOADED = (int32_t)0x80000000;
 constexpr int32_t CL_WIN_MAX = 1 << 24;
 
-// Cold counters kept in LDS (lane 0 adds with ds_add, no return value). CS_BLAZY and the CL_B* sums are
-// only fed by the event-parallel rounds of the any-size kernel.
+// Control flow of the replay kernels is wave-uniform, and no branch in their loops is divergent: a region that
+// only some lanes execute costs about 40 clocks of its own (exec saved, a branch, exec restored) and, worse,
+// makes the compiler rebuild the uniform branches around it with flags in scalar registers. So per-lane
+// conditions are joined by & and | (&& and || on lanes are branches), a store that
+// one lane would do is done by all lanes, same value and same address, loads clamp their index, and an LDS
+// atomic that is one lane's business is done by all lanes too, the others adding 0 to words of their own
+// somewhere in the first 512 bytes.
+//
+// Cold counters kept in LDS (ds_add, no return value). CS_BLAZY and the CL_B* sums are only fed by the
+// event-parallel rounds of the any-size kernel. The head of a replay's LDS: c64[8], c32[16], hist[32].
 enum { CS_PLACED, CS_REJECTED, CS_QUEUED, CS_ABORTED, CS_MIGR, CS_SO, CS_SI, CS_PEAK, CS_MAXDELAY,
        CS_NON, CS_SUMS, CS_OPENG, CS_BLAZY, CS_NREP, CS_MIGRWARM, CS_N32 };
 enum { CL_SUMDELAY, CL_GWAIT, CL_PROV, CL_RESV, CL_SUB, CL_BDUR, CL_BGEXEC, CL_REPL, CL_N64 };
 
+constexpr size_t LDS_HEAD = 8 * 8 + 16 * 4 + 32 * 4;
+constexpr size_t LDS_LEAST = 512;              // what the adds below may touch (with zeros)
+
 template <class L>
 __device__ __forceinline__ void c32_add(L &m, int lane, int idx, uint32_t v) {
-  if (lane == 0) atomicAdd(&m.c32[idx], v);
+  atomicAdd(&m.c32[(idx + lane) & (WAVE - 1)], lane == 0 ? v : 0u);
 }
 template <class L>
 __device__ __forceinline__ void c32_max(L &m, int lane, int idx, uint32_t v) {
-  if (lane == 0) atomicMax(&m.c32[idx], v);
+  atomicMax(&m.c32[(idx + lane) & (WAVE - 1)], lane == 0 ? v : 0u);
 }
 template <class L>
 __device__ __forceinline__ void c64_add(L &m, int lane, int idx, int64_t v) {
-  if (lane == 0) atomicAdd(&m.c64[idx], (unsigned long long)v);
+  atomicAdd(&m.c64[(idx + lane) & (WAVE - 1)], lane == 0 ? (unsigned long long)v : 0ull);
+}
+template <class L>
+__device__ __forceinline__ void hist_add(L &m, int lane, int32_t delay) {        // delay > 0
+  const int b = 32 - __builtin_clz((uint32_t)delay);
+  atomicAdd(&m.hist[((b > 31 ? 31 : b) + lane) & (WAVE - 1)], lane == 0 ? 1u : 0u);
+}
+
+// Lanes with `hit` put v side by side into `staged`, from lane `at` on, in lane order; lanes below `at` keep what
+// they have. One push through the LDS crossbar: the lanes without a hit fill the remaining places.
+__device__ __forceinline__ int32_t stage_hits(int32_t staged, int lane, int at, bool hit, uint64_t hits, int32_t v) {
+  const int n = __builtin_popcountll(hits);
+  const int rank = lane_rank(hits);
+  const int dst = (at + (hit ? rank : n + lane - rank)) & (WAVE - 1);
+  const int32_t got = __builtin_amdgcn_ds_permute(dst << 2, v);
+  return lane < at ? staged : got;
 }
 
 // Can the dynamic limit of Section 3.4.1 ever admit a host that the replay's own cap turns away? Not while
@@ -234,7 +260,7 @@ __device__ __forceinline__ void decide(C &c, R &r, int32_t now, uint32_t outcome
   const uint64_t code = decision_code(now, outcome, s, slot, host);
   r.digest = r.digest * DIGEST_PRIME + code;
   if (__builtin_expect(c.dlog != nullptr, 0)) {
-    if (c.lane == 0 && (int64_t)r.n_dec < c.p.dlog_stride) c.dlog[r.n_dec] = code;
+    if ((int64_t)r.n_dec < c.p.dlog_stride) c.dlog[r.n_dec] = code;
   }
   r.n_dec++;
 }
@@ -262,19 +288,18 @@ __device__ __forceinline__ void timer_push(C &c, R &r, int32_t t, uint32_t kind,
     ovf_push(c, r, t, k, d);
     return;
   }
-  bool before = c.lane < r.q_n && (c.qt < t || (c.qt == t && c.qk < k));
+  const bool before = (c.lane < r.q_n) & ((c.qt < t) | ((c.qt == t) & (c.qk < k)));
   int pos = __builtin_popcountll(wballot(before));
   int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x138, 0xF, 0xF, false);          // wave_shr:1
   int32_t sd = __builtin_amdgcn_update_dpp(c.qd, c.qd, 0x138, 0xF, 0xF, false);
   uint32_t sk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x138, 0xF, 0xF, false);
-  if (c.lane > pos) { c.qt = st; c.qd = sd; c.qk = sk; }
-  if (c.lane == pos) { c.qt = t; c.qd = d; c.qk = k; }
+  const bool up = c.lane > pos, here = c.lane == pos;
+  c.qt = here ? t : up ? st : c.qt;   c.qd = here ? d : up ? sd : c.qd;   c.qk = here ? k : up ? sk : c.qk;
   if constexpr (C::closed) {
     const int32_t sx = __builtin_amdgcn_update_dpp(c.qx, c.qx, 0x138, 0xF, 0xF, false);
     const int32_t sn = __builtin_amdgcn_update_dpp(c.qnx, c.qnx, 0x138, 0xF, 0xF, false);
     const int32_t sh = __builtin_amdgcn_update_dpp(c.qnth, c.qnth, 0x138, 0xF, 0xF, false);
-    if (c.lane > pos) { c.qx = sx; c.qnx = sn; c.qnth = sh; }
-    if (c.lane == pos) { c.qx = x; c.qnx = nx; c.qnth = nth; }
+    c.qx = here ? x : up ? sx : c.qx;   c.qnx = here ? nx : up ? sn : c.qnx;   c.qnth = here ? nth : up ? sh : c.qnth;
   }
   r.q_n++;
   if (pos == 0) r.q_head_t = t;

@@ -46,7 +46,6 @@ constexpr uint32_t RK_FLAGS = 0xFFFu;        // the bits below the hosts
 __device__ __forceinline__ uint32_t slot_host(uint32_t hw, uint32_t slot) { return (hw >> (12u + 6u * slot)) & 63u; }
 
 struct Lds {
-  int32_t *stage;    // [64] sessions whose timers move into the registers
   int32_t *warm;     // [64][4] when each pre-warmed container of a host is available (only with the pool)
   int2 *sess;
   uint32_t *hist;
@@ -103,12 +102,12 @@ struct Ctx {
 // write a session record; lanes of the current tile that prefetched it go stale
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void sess_write(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint32_t hw, int32_t tm, uint32_t fl) {
-  if (c.lane == 0) c.m.sess[s] = make_int2((int)((hw & ~RK_FLAGS) | (fl & RK_FLAGS)), tm);
+  c.m.sess[s] = make_int2((int)((hw & ~RK_FLAGS) | (fl & RK_FLAGS)), tm);
   r.dirty |= wballot(c.vsid == s);
 }
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void sess_write_flag(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint32_t fl) {
-  if (c.lane == 0) c.m.sess[s].x = (int)fl;
+  c.m.sess[s].x = (int)fl;
   r.dirty |= wballot(c.vsid == s);
 }
 
@@ -123,16 +122,25 @@ __device__ __forceinline__ void ovf_push(Ctx<NJ, F> &c, Regs &r, int32_t t, uint
   if constexpr (Ctx<NJ, F>::closed) {
     // the session's one timer waits in its record: a retry is implied by it as ever, the time of a
     // next event replaces the busy-until time (a closed loop never asks for it)
-    if (c.lane == 0) {
-      atomicOr((unsigned int *)&c.m.sess[s].x, RK_OVF);
-      if ((k >> 16) != QK_RETRY) c.m.sess[s].y = t;
-    }
+    wave_sync();
+    const int2 rec = c.m.sess[s];
+    c.m.sess[s] = make_int2(rec.x | (int)RK_OVF, (k >> 16) != QK_RETRY ? t : rec.y);
   } else {
-    if (c.lane == 0) { atomicOr((unsigned int *)&c.m.sess[s].x, RK_OVF); c.ovf_dur[s] = d; }
+    wave_sync();
+    c.m.sess[s].x |= (int)RK_OVF;
+    c.ovf_dur[s] = d;
   }
   r.dirty |= wballot(c.vsid == s);
   if (r.o_n == 0 || t < r.o_min_t || (t == r.o_min_t && k < r.o_min_k)) { r.o_min_t = t; r.o_min_k = k; }
   r.o_n++;
+}
+
+// the time of the timer that waits in a session's record (a retry's is implied by it)
+template <int NJ, uint32_t F>
+__device__ __forceinline__ int32_t waiting_time(const Ctx<NJ, F> &c, const int2 rec) {
+  const uint32_t fl = (uint32_t)rec.x;
+  const int32_t at = rec.y + (int32_t)((fl >> 8) & 15u) * c.p.retry_iv;
+  return (fl & 7u) == SS_QUEUED ? at : rec.y;
 }
 
 // Registers empty: all timers that are due within a window after the earliest one move
@@ -146,6 +154,7 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
   constexpr uint32_t kOther = Ctx<NJ, F>::closed ? QK_NEXT : QK_END;
   wave_sync();
   int cnt;
+  int32_t staged = 0;                            // the sessions whose timers come in, one per lane
   int32_t left;                                  // earliest time left behind
   int32_t win = r.cl_win;
   for (;;) {
@@ -155,17 +164,13 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
     int32_t mn = NEVER;
     for (int s0 = 0; s0 < c.n_sess; s0 += WAVE) {
       const int s = s0 + c.lane;
-      int32_t d = NEVER;
-      if (s < c.n_sess) {
-        const int2 rec = c.m.sess[s];
-        const uint32_t fl = (uint32_t)rec.x;
-        if (fl & RK_OVF) d = (fl & 7u) == SS_QUEUED ? rec.y + (int32_t)((fl >> 8) & 15u) * c.p.retry_iv : rec.y;
-      }
+      const int2 rec = c.m.sess[min(s, c.n_sess - 1)];
+      const int32_t due = waiting_time(c, rec);
+      const int32_t d = (s < c.n_sess) & (((uint32_t)rec.x & RK_OVF) != 0) ? due : NEVER;
       const bool hit = d <= T;
       const uint64_t b = wballot(hit);
       if (b != 0) {
-        const int pos = cnt + lane_rank(b);
-        if (hit && pos < WAVE) c.m.stage[pos] = s;
+        staged = cnt < WAVE ? stage_hits(staged, c.lane, cnt, hit, b, s) : staged;
         cnt += __builtin_popcountll(b);
       }
       mn = hit ? mn : (d < mn ? d : mn);
@@ -181,17 +186,16 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
       // more than 64 timers at the instant o_min_t: the earliest by kind and session alone
       wave_sync();
       uint32_t best = 0xFFFFFFFFu;
-      for (int s = c.lane; s < c.n_sess; s += WAVE) {
-        const int2 rec = c.m.sess[s];
+      for (int s0 = 0; s0 < c.n_sess; s0 += WAVE) {
+        const int s = s0 + c.lane;
+        const int2 rec = c.m.sess[min(s, c.n_sess - 1)];
         const uint32_t fl = (uint32_t)rec.x;
-        if (fl & RK_OVF) {
-          const bool retry = (fl & 7u) == SS_QUEUED;
-          const int32_t d = retry ? rec.y + (int32_t)((fl >> 8) & 15u) * c.p.retry_iv : rec.y;
-          if (d == T) best = umin(best, ((retry ? QK_RETRY : kOther) << 16) | (uint32_t)s);
-        }
+        const uint32_t k = (((fl & 7u) == SS_QUEUED ? QK_RETRY : kOther) << 16) | (uint32_t)s;
+        const int32_t due = waiting_time(c, rec);
+        best = umin(best, (s < c.n_sess) & ((fl & RK_OVF) != 0) & (due == T) ? k : 0xFFFFFFFFu);
       }
       best = wave_min(best);
-      if (c.lane == 0) c.m.stage[0] = (int32_t)(best & 0xFFFFu);
+      staged = (int32_t)(best & 0xFFFFu);
       cnt = 1;
       left = T;
       break;
@@ -203,32 +207,29 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
   else if (cnt > 7 * WAVE / 8) r.cl_win = win - win / 4;
   else r.cl_win = win;
   wave_sync();
-  // lane i < cnt takes the timer of session stage[i]
+  // lane i < cnt takes the timer of the session staged there
   const bool take = c.lane < cnt;
-  uint32_t key = 0xFFFFFFFFu;
-  int32_t t = NEVER, e = 0;
-  if (take) {
-    const int s = c.m.stage[c.lane];
-    const int2 rec = c.m.sess[s];
-    const uint32_t fl = (uint32_t)rec.x;
-    const bool retry = (fl & 7u) == SS_QUEUED;
-    t = retry ? rec.y + (int32_t)((fl >> 8) & 15u) * c.p.retry_iv : rec.y;
-    key = ((retry ? QK_RETRY : kOther) << 16) | (uint32_t)s;
-    c.m.sess[s].x = (int)(fl & ~RK_OVF);
-  }
+  const int last_staged = lane_get(staged, cnt - 1);
+  const int s = take ? staged : last_staged;                   // (the lanes beyond do what the last one does)
+  const int2 rec = c.m.sess[s];
+  const uint32_t fl = (uint32_t)rec.x;
+  const int32_t due = waiting_time(c, rec);
+  const int32_t t = take ? due : NEVER;
+  const uint32_t own_key = (((fl & 7u) == SS_QUEUED ? QK_RETRY : kOther) << 16) | (uint32_t)s;
+  const uint32_t key = take ? own_key : 0xFFFFFFFFu;
+  int32_t e = 0;
+  c.m.sess[s].x = (int)(fl & ~RK_OVF);
   // the cursors / durations were written by lane 0 when the timers were scheduled: the fence makes this
   // wave's own stores visible to its other lanes
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   int32_t x = 0, nx = -1, nth = 0;
   if constexpr (Ctx<NJ, F>::closed) {
-    if (take) {
-      e = c.cl_cur[key & 0xFFFFu];
-      const int2 ch = c.cl_chain[e];
-      x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
-      nx = ch.x; nth = ch.y;
-    }
+    e = c.cl_cur[s];
+    const int2 ch = c.cl_chain[e];
+    x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
+    nx = ch.x; nth = ch.y;
   } else {
-    if (take && (key >> 16) == QK_RETRY) e = c.ovf_dur[key & 0xFFFFu];    // qd carries the queued cell's duration
+    e = c.ovf_dur[s];                            // qd carries the queued cell's duration (of a deferred end: not looked at)
     // the records taken have lost their mark: lanes of the tile that prefetched one read it again. Such a
     // session was queued or ending when the tile was loaded (or its lanes are stale already)
     r.dirty |= r.slow_lanes;
@@ -237,7 +238,7 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
   for (int j = 0; j < cnt; j++) {
     const int32_t tj = lane_get(t, j);
     const uint32_t kj = (uint32_t)lane_get((int)key, j);
-    rank += (tj < t || (tj == t && kj < key)) ? 1 : 0;
+    rank += (tj < t) | ((tj == t) & (kj < key)) ? 1 : 0;
   }
   const int dst = take ? rank : c.lane;          // a permutation: the timers taken in order, the rest where they are
   c.qt = __builtin_amdgcn_ds_permute(dst << 2, t);
@@ -273,25 +274,25 @@ __device__ __forceinline__ int committed(const Ctx<NJ, F> &c, int32_t now) {
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void bind_gpus(Ctx<NJ, F> &c, int h, int g, int32_t now, int32_t finish) {
   const int j = h >> 3, hl = h & 7;
-  const bool mine = (c.lane >> 3) == hl && (c.lane & 7) < c.p.G;
+  const bool mine = ((c.lane >> 3) == hl) & ((c.lane & 7) < c.p.G);
 #pragma unroll
   for (int jj = 0; jj < NJ; jj++) {
     if (jj == j) {
-      bool fr = mine && c.fin[jj] <= now;
-      int rank = lane_rank(wballot(fr));
-      if (fr && rank < g) c.fin[jj] = finish;
+      const bool fr = mine & (c.fin[jj] <= now);
+      const int rank = lane_rank(wballot(fr));
+      c.fin[jj] = fr & (rank < g) ? finish : c.fin[jj];
     }
   }
 }
 
 template <int NJ, uint32_t F>
 __device__ __forceinline__ int boot_host(Ctx<NJ, F> &c, Regs &r, int32_t now, uint32_t hs_new) {
-  uint64_t off = wballot(c.lane < c.p.Hmax && c.hr == NEVER);
+  const uint64_t off = wballot((c.lane < c.p.Hmax) & (c.hr == NEVER));
   int h = (int)__builtin_ctzll(off);                 // the caller has checked that one exists
   int32_t ra = now + c.p.boot;
   if (c.lane == h) { c.hr = ra; c.hs = hs_new; }
   if (c.flags() & NBOS_F_WARM_POOL) {         // its pre-warmed containers are there once it is up
-    if (c.lane < 4) c.m.warm[4 * h + c.lane] = ra + c.p.prewarm;
+    c.m.warm[4 * h + (c.lane & 3)] = ra + c.p.prewarm;
   }
   c.fu = c.fu < ra ? c.fu : ra;               // a new host may have idle GPUs from then on
   c32_add(c.m, c.lane, CS_NON, 1u);
@@ -340,7 +341,7 @@ __device__ __forceinline__ void cl_schedule(Ctx<NJ, F> &c, Regs &r, uint32_t s, 
   if (e < 0) return;
   const int64_t t = (int64_t)base + r.cl_nth;
   if (t >= 0x7FFFFFFFLL) { r.status = NBOS_E_RANGE; return; }
-  if (c.lane == 0) c.cl_cur[s] = e;
+  c.cl_cur[s] = e;
   timer_push(c, r, (int32_t)t, QK_NEXT, s, e);
 }
 
@@ -352,7 +353,7 @@ __device__ __forceinline__ void session_start(Ctx<NJ, F> &c, Regs &r, uint32_t s
   const int C = committed(c, now);
   const int S = (int)(c.hs & 0xFFFFu);
   const int32_t room = cap_room(c, g);
-  uint32_t key = (c.hr <= now && S <= room) ? (((uint32_t)C << 22) | ((uint32_t)S << 10) | (uint32_t)c.lane)
+  uint32_t key = (c.hr <= now) & (S <= room) ? (((uint32_t)C << 22) | ((uint32_t)S << 10) | (uint32_t)c.lane)
                                             : 0xFFFFFFFFu;
   int pick0 = -1, pick1 = -1, pick2 = -1, k = 0;
   uint32_t m0 = wave_min(key);
@@ -413,7 +414,7 @@ __device__ __forceinline__ void end_session(Ctx<NJ, F> &c, Regs &r, uint32_t s, 
   const int g = (int)((fl >> 3) & 7u) + 1;
   const uint32_t sub = (uint32_t)g | (1u << 16);
   const int h0 = (int)slot_host(hw, 0), h1 = (int)slot_host(hw, 1), h2 = (int)slot_host(hw, 2);
-  if (c.lane == h0 || c.lane == h1 || c.lane == h2) c.hs -= sub;
+  c.hs -= (c.lane == h0) | (c.lane == h1) | (c.lane == h2) ? sub : 0u;
   sess_write_flag(c, r, s, (fl & ~(7u | SF_ENDING)) | SS_ENDED);
   c32_add(c.m, c.lane, CS_SUMS, (uint32_t)(-3 * g));
   c64_add(c.m, c.lane, CL_SUB, (int64_t)(3 * g) * now);
@@ -443,18 +444,13 @@ __device__ __forceinline__ void start_cell(Ctx<NJ, F> &c, Regs &r, uint32_t s, u
   const uint32_t nw = (hw & ~RK_FLAGS) | (((fl & ~(7u | (15u << 8))) | SS_PLACED) & RK_FLAGS);
   if (__builtin_expect(delay == 0, 1)) {
     r.h0++;                                     // histogram bin 0 lives in a register
-    if (c.lane == 0) c.m.sess[s] = make_int2((int)nw, finish);
   } else {
-    int b = 32 - __builtin_clz((uint32_t)delay);
-    b = b > 31 ? 31 : b;
-    if (c.lane == 0) {
-      c.m.sess[s] = make_int2((int)nw, finish);
-      atomicAdd(&c.m.hist[b], 1u);
-      atomicAdd(&c.m.c64[CL_SUMDELAY], (unsigned long long)delay);
-      atomicMax(&c.m.c32[CS_MAXDELAY], (uint32_t)delay);
-      atomicAdd(&c.m.c64[CL_GWAIT], (unsigned long long)((int64_t)g * (start - now)));
-    }
+    hist_add(c.m, c.lane, delay);
+    c64_add(c.m, c.lane, CL_SUMDELAY, delay);
+    c32_max(c.m, c.lane, CS_MAXDELAY, (uint32_t)delay);
+    c64_add(c.m, c.lane, CL_GWAIT, (int64_t)g * (start - now));
   }
+  c.m.sess[s] = make_int2((int)nw, finish);
   r.dirty |= wballot(c.vsid == s);
   r.lazy_max = r.lazy_max > finish ? r.lazy_max : finish;
   decide(c, r, now, outcome, s, (uint32_t)slot, (uint32_t)host);
@@ -495,7 +491,7 @@ __device__ __forceinline__ void start_at_once(Ctx<NJ, F> &c, Regs &r, uint32_t s
   if ((hw >> 30) == (uint32_t)slot + 1u) r.reused++;
   // the record's word: hosts as they are, this slot the last executor; state "placed", retry count 0 already
   const uint32_t nw = (hw & 0x3FFFFFFFu) | ((uint32_t)(slot + 1) << 30);
-  if (c.lane == 0) c.m.sess[s] = make_int2((int)nw, finish);
+  c.m.sess[s] = make_int2((int)nw, finish);
   r.dirty |= wballot(c.vsid == s);
   r.lazy_max = r.lazy_max > finish ? r.lazy_max : finish;
   decide(c, r, now, NBOS_D_START, s, (uint32_t)slot, (uint32_t)host);
@@ -514,7 +510,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
   uint32_t kb = 0xFFFFFFFFu;
   if (!hopeless) {
     C = committed(c, now);
-    const bool can = c.hr <= now && C + g <= c.p.G;       // a ready host with g idle GPUs
+    const bool can = (c.hr <= now) & (C + g <= c.p.G);       // a ready host with g idle GPUs
     idle_ok = wballot(can);
     // (a) election, Section 3.2.2: among the session's hosts that can bind, fewest committed GPUs, then
     // lowest host index: the smallest of the three hosts' keys
@@ -533,7 +529,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
   // lowers it again, see boot_host).
   if (!hopeless && idle_ok == 0) {
     const int32_t bound = earliest_idle(c, g);
-    if (c.lane >= g - 1 && c.fu < bound) c.fu = bound;
+    c.fu = (c.lane >= g - 1) & (c.fu < bound) ? bound : c.fu;
   }
   // (b), (c): a target exists? Only then is the replica to move worked out: the one on the fullest
   // ready host (ties: lowest host); replicas on booting hosts only if all three are.
@@ -568,11 +564,12 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
         // Section 3.2.3: the target's pre-warmed container that has been available longest, if any
         // is available now, shortens the start; its replacement is there one pre-warm time later
         wave_sync();
-        const uint32_t av = c.lane < c.p.warm_n ? (uint32_t)c.m.warm[4 * dst + c.lane] : 0xFFFFFFFFu;
+        const uint32_t av_own = (uint32_t)c.m.warm[4 * dst + (c.lane & 3)];
+        const uint32_t av = c.lane < c.p.warm_n ? av_own : 0xFFFFFFFFu;
         const uint32_t first = wave_min(av);
         if ((int32_t)first <= now) {
           const int w = (int)__builtin_ctzll(wballot(av == first));
-          if (c.lane == w) c.m.warm[4 * dst + w] = now + c.p.prewarm;
+          c.m.warm[4 * dst + w] = now + c.p.prewarm;
           c32_add(c.m, c.lane, CS_MIGRWARM, 1u);
           warm = true;
         }
@@ -618,9 +615,9 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
     const uint32_t nfl = (fl & ~(7u | (15u << 8))) | SS_QUEUED | ((uint32_t)retries << 8);
     if (first) {                                 // first time in the queue: the submit time goes in
       c32_add(c.m, c.lane, CS_QUEUED, 1u);
-      if (c.lane == 0) c.m.sess[s] = make_int2((int)nfl, t_submit);
+      c.m.sess[s] = make_int2((int)nfl, t_submit);
     } else {
-      if (c.lane == 0) c.m.sess[s].x = (int)nfl;
+      c.m.sess[s].x = (int)nfl;
     }
     r.dirty |= wballot(c.vsid == s);
     if constexpr (Ctx<NJ, F>::closed) {
@@ -674,12 +671,12 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
     const int g = (int)((fl >> 3) & 7u) + 1;
     if (now >= lane_get(c.fu, g - 1)) {
       const int C = committed(c, now);
-      const bool can = c.hr <= now && C + g <= c.p.G;
+      const bool can = (c.hr <= now) & (C + g <= c.p.G);
       if (elect(c, hw, can ? (uint32_t)c.lane : 0xFFFFFFFFu) != 0xFFFFFFFFu) break;   // the election succeeds
       const uint64_t idle_ok = wballot(can);
       if (idle_ok == 0) {
         const int32_t bound = earliest_idle(c, g);
-        if (c.lane >= g - 1 && c.fu < bound) c.fu = bound;
+        c.fu = (c.lane >= g - 1) & (c.fu < bound) ? bound : c.fu;
       } else if (c.flags() & NBOS_F_MIGRATE) {
         const int S = (int)(c.hs & 0xFFFFu);
         if (idle_ok & wballot(S <= cap_room(c, g))) break;                        // a migration target
@@ -694,7 +691,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
       // it fails for the last time: the cell is given up, the session is idle again, the timer goes
       c32_add(c.m, c.lane, CS_ABORTED, 1u);
       decide(c, r, now, NBOS_D_ABORT, s, 0, 0);
-      if (c.lane == 0) c.m.sess[s] = make_int2((int)((fl & ~(7u | (15u << 8))) | SS_PLACED), 0);
+      c.m.sess[s] = make_int2((int)((fl & ~(7u | (15u << 8))) | SS_PLACED), 0);
       r.dirty |= wballot(c.vsid == s);
       c.qt = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);                      // wave_shl:1
       c.qd = __builtin_amdgcn_update_dpp(c.qd, c.qd, 0x130, 0xF, 0xF, false);
@@ -711,7 +708,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
       while (retries < c.p.max_retries && t_submit + retries * c.p.retry_iv < bound) retries++;
     }
     const uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
-    if (c.lane == 0) c.m.sess[s].x = (int)nfl;
+    c.m.sess[s].x = (int)nfl;
     r.dirty |= wballot(c.vsid == s);
     // ... and move the entry from lane 0 to its new place: entries before it shift down one lane
     const int32_t t_new = t_submit + retries * c.p.retry_iv;
@@ -730,10 +727,10 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
         continue;
       }
     }
-    const bool before = c.lane >= 1 && c.lane < r.q_n && (c.qt < t_new || (c.qt == t_new && c.qk < key));
+    const bool before = (c.lane >= 1) & (c.lane < r.q_n) & ((c.qt < t_new) | ((c.qt == t_new) & (c.qk < key)));
     const int pos = __builtin_popcountll(wballot(before));
-    if (c.lane < pos) { c.qt = st; c.qd = sd; c.qk = sk; }
-    if (c.lane == pos) { c.qt = t_new; c.qd = d_own; c.qk = key; }
+    const bool down = c.lane < pos, here = c.lane == pos;
+    c.qt = here ? t_new : down ? st : c.qt;   c.qd = here ? d_own : down ? sd : c.qd;   c.qk = here ? key : down ? sk : c.qk;
     r.q_head_t = lane_get(c.qt, 0);
   }
   return last;
@@ -743,7 +740,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
 // release the highest-numbered ready host without replicas
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void release_host(Ctx<NJ, F> &c, Regs &r, int32_t now) {
-  const uint64_t e = wballot(c.hr <= now && (c.hs >> 16) == 0);
+  const uint64_t e = wballot((c.hr <= now) & ((c.hs >> 16) == 0));
   const int victim = 63 - (int)__builtin_clzll(e);
   if (c.lane == victim) c.hr = NEVER;
   c32_add(c.m, c.lane, CS_NON, (uint32_t)-1);
@@ -755,7 +752,7 @@ __device__ __forceinline__ void release_host(Ctx<NJ, F> &c, Regs &r, int32_t now
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void tick(Ctx<NJ, F> &c, Regs &r, int32_t now) {
   int A = __builtin_popcountll(wballot(c.hr <= now));
-  int Z = __builtin_popcountll(wballot(c.hr <= now && (c.hs >> 16) == 0));
+  int Z = __builtin_popcountll(wballot((c.hr <= now) & ((c.hs >> 16) == 0)));
   int released = 0;
   if (c.flags() & NBOS_F_AUTOSCALE) {
     // expected capacity f * sum C in whole hosts plus the scaling buffer; hosts being provisioned
@@ -813,7 +810,6 @@ __device__ __forceinline__ Lds lds_carve_closed(const KParams &p, unsigned char 
   m.c32 = (uint32_t *)q;       q += 16 * 4;
   m.hist = (uint32_t *)q;      q += 32 * 4;
   m.sess = (int2 *)q;          q += (size_t)p.n_cap * 8;     // at a fixed offset: its accesses fold it in
-  m.stage = (int32_t *)q;      q += WAVE * 4;
   m.warm = (int32_t *)q;                                     // only there with the pool
   return m;
 }
@@ -883,7 +879,6 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   m.c32 = (uint32_t *)q;       q += 16 * 4;
   m.hist = (uint32_t *)q;      q += 32 * 4;
   m.sess = (int2 *)q;          q += (size_t)p.n_cap * 8;     // at a fixed offset: its accesses fold it in
-  m.stage = (int32_t *)q;      q += WAVE * 4;
   m.warm = (int32_t *)q;                                     // only there with the pool
 
   // S0: hosts 0..H0-1 ready at time 0, the rest off; sessions unplaced
@@ -925,7 +920,10 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   // S1: stream the events, one per lane per tile, next tile in flight
   int64_t base = ev_lo;                     // first event of the tile held in (nt, nd, ns)
   int32_t vt = 0, vd = 0, vs = 0, nt = 0, nd = 0, ns = 0;
-  if (base + lane < ev_hi) { nt = p.ev_time[base + lane]; nd = p.ev_dur[base + lane]; ns = p.ev_sk[base + lane]; }
+  if (base < ev_hi) {
+    const int64_t at = min(base + lane, ev_hi - 1);
+    nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
+  }
 
   // Outer loop: one iteration per tile of 64 events plus a last one (`final`) that drains the
   // timers. Inner loop: one iteration per item (queued timer, auto-scaler period, or arrival); it
@@ -933,36 +931,38 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   bool final = false;
   while (r.status == NBOS_OK) {
     int2 rec = make_int2(0, 0);             // prefetched session record of this lane's event
-    uint32_t fast = 0;                      // this lane's event is a cell of an idle placed session
-    bool base_valid_cell = false;           // this lane's event is a cell
-    uint64_t todo = 0;
+    uint64_t todo = 0, cellmask = 0;        // events to look at; which are cells
+    uint64_t fastmask = 0;                  // ... and which are cells of an idle placed session
     if (base < ev_hi) {
       // the prefetched tile becomes current; start loading the one after it
       vt = nt; vd = nd; vs = ns;
       const int64_t cur = base;
       base += WAVE;
-      if (base + lane < ev_hi) { nt = p.ev_time[base + lane]; nd = p.ev_dur[base + lane]; ns = p.ev_sk[base + lane]; }
+      if (base < ev_hi) {
+        const int64_t at = min(base + lane, ev_hi - 1);
+        nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
+      }
       const bool valid = cur + lane < ev_hi;
       const bool is_last = cur + lane == ev_hi - 1;
       const uint32_t sid = (uint32_t)vs & 0xFFFFFFu;
       const bool is_cell = ((uint32_t)vs >> 24) == NBOS_EV_CELL;
       c.vsid = valid ? sid : 0xFFFFFFFFu;
       wave_sync();
-      if (valid) rec = m.sess[sid];
+      rec = m.sess[sid];                    // (lanes beyond the last event hold that one's)
       // Cells of sessions in a final state (rejected / ended) and cells that arrive while the
       // session's running cell lasts beyond them change nothing: count them, skip them. Neither
       // condition can be undone before the event's time. The last event of the trace is never
       // skipped, so timers due before it still run first.
       const uint32_t st = (uint32_t)rec.x & 7u;
-      const bool dead = st == SS_REJECTED || st == SS_ENDED;
-      const bool running = st == SS_PLACED && rec.y > vt;
-      const bool skip = valid && !is_last && (dead || (is_cell && running));
-      r.c_total += (uint32_t)__builtin_popcountll(wballot(valid && is_cell));
-      r.c_unplaced += (uint32_t)__builtin_popcountll(wballot(skip && is_cell && dead));
-      r.c_busy += (uint32_t)__builtin_popcountll(wballot(skip && is_cell && !dead));
-      fast = (valid && is_cell && st == SS_PLACED && !running && !((uint32_t)rec.x & SF_ENDING)) ? 1u : 0u;
-      base_valid_cell = valid && is_cell;
-      todo = wballot(valid && !skip);
+      const bool dead = (st == SS_REJECTED) | (st == SS_ENDED);
+      const bool running = (st == SS_PLACED) & (rec.y > vt);
+      const bool skip = valid & !is_last & (dead | (is_cell & running));
+      cellmask = wballot(valid & is_cell);
+      r.c_total += (uint32_t)__builtin_popcountll(cellmask);
+      r.c_unplaced += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & dead));
+      r.c_busy += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & !dead));
+      fastmask = wballot(valid & is_cell & (st == SS_PLACED) & !running & (((uint32_t)rec.x & SF_ENDING) == 0));
+      todo = wballot(valid & !skip);
       r.dirty = 0;
       if (ev_hi - cur <= WAVE) {
         int32_t tl = lane_get(vt, (int)(ev_hi - cur - 1));
@@ -971,9 +971,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
     } else {
       final = true;
     }
-    const uint64_t fastmask = wballot(fast != 0);
     PROF(PC_TILE, 1);
-    const uint64_t cellmask = wballot(base_valid_cell);
     r.slow_lanes = ~fastmask;
     for (;;) {
       if (__builtin_expect(r.status != NBOS_OK, 0)) break;
@@ -1003,7 +1001,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
         // election (Section 3.2.2) on the vector side: every host's key (committed GPUs, index), or all
         // ones where it cannot bind; the keys of the session's three hosts are read and compared
         const int C = committed(c, t);
-        const uint32_t key = (c.hr <= t && C + g <= c.p.G) ? (((uint32_t)C << 6) | (uint32_t)c.lane) : 0xFFFFFFFFu;
+        const uint32_t key = (c.hr <= t) & (C + g <= c.p.G) ? (((uint32_t)C << 6) | (uint32_t)c.lane) : 0xFFFFFFFFu;
         const uint32_t kb = elect(c, hw, key);
         if (kb == 0xFFFFFFFFu) break;                         // every replica yields
         const int hl = (int)(kb & 63u);
@@ -1143,12 +1141,12 @@ __device__ __forceinline__ int32_t cl_failing_retries(Ctx<NJ, F> &c, Regs &r, in
     const int g = (int)((fl >> 3) & 7u) + 1;
     if (now >= lane_get(c.fu, g - 1)) {
       const int C = committed(c, now);
-      const bool can = c.hr <= now && C + g <= c.p.G;
+      const bool can = (c.hr <= now) & (C + g <= c.p.G);
       if (elect(c, hw, can ? (uint32_t)c.lane : 0xFFFFFFFFu) != 0xFFFFFFFFu) break;   // the election succeeds
       const uint64_t idle_ok = wballot(can);
       if (idle_ok == 0) {
         const int32_t bound = earliest_idle(c, g);
-        if (c.lane >= g - 1 && c.fu < bound) c.fu = bound;
+        c.fu = (c.lane >= g - 1) & (c.fu < bound) ? bound : c.fu;
       } else if (c.flags() & NBOS_F_MIGRATE) {
         const int S = (int)(c.hs & 0xFFFFu);
         if (idle_ok & wballot(S <= cap_room(c, g))) break;                        // a migration target
@@ -1167,7 +1165,7 @@ __device__ __forceinline__ int32_t cl_failing_retries(Ctx<NJ, F> &c, Regs &r, in
     if ((int64_t)t_submit + (int64_t)retries * c.p.retry_iv >= 0x7FFFFFFFLL) break;   // out of range: general path
     last = now;
     const uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
-    if (c.lane == 0) c.m.sess[s].x = (int)nfl;
+    c.m.sess[s].x = (int)nfl;
     const int32_t t_new = t_submit + retries * c.p.retry_iv;
     const int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);          // wave_shl:1
     const int32_t sd = __builtin_amdgcn_update_dpp(c.qd, c.qd, 0x130, 0xF, 0xF, false);
@@ -1184,11 +1182,12 @@ __device__ __forceinline__ int32_t cl_failing_retries(Ctx<NJ, F> &c, Regs &r, in
       r.q_head_t = r.q_n > 0 ? lane_get(c.qt, 0) : NEVER;
     } else {
       // it moves from lane 0 to its new place: the entries before that shift down one lane
-      const bool before = c.lane >= 1 && c.lane < r.q_n && (c.qt < t_new || (c.qt == t_new && c.qk < key));
+      const bool before = (c.lane >= 1) & (c.lane < r.q_n) & ((c.qt < t_new) | ((c.qt == t_new) & (c.qk < key)));
       const int pos = __builtin_popcountll(wballot(before));
       const int32_t d_own = lane_get(c.qd, 0), x_own = lane_get(c.qx, 0), n_own = lane_get(c.qnx, 0), h_own = lane_get(c.qnth, 0);
-      if (c.lane < pos) { c.qt = st; c.qd = sd; c.qk = sk; c.qx = sx; c.qnx = sn; c.qnth = sh; }
-      if (c.lane == pos) { c.qt = t_new; c.qd = d_own; c.qk = key; c.qx = x_own; c.qnx = n_own; c.qnth = h_own; }
+      const bool down = c.lane < pos, here = c.lane == pos;
+      c.qt = here ? t_new : down ? st : c.qt;   c.qd = here ? d_own : down ? sd : c.qd;    c.qk = here ? key : down ? sk : c.qk;
+      c.qx = here ? x_own : down ? sx : c.qx;   c.qnx = here ? n_own : down ? sn : c.qnx;  c.qnth = here ? h_own : down ? sh : c.qnth;
       r.q_head_t = lane_get(c.qt, 0);
     }
   }
@@ -1241,12 +1240,11 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
     int32_t vt = 0, vnx = -1, vnth = -1;
     uint32_t vs = 0;
     if (base < ev_hi) {
-      if (base + lane < ev_hi) {
-        vt = p.ev_time[base + lane]; vs = (uint32_t)p.ev_sk[base + lane];
-        const int2 ch = p.cl_chain[base + lane];
-        vnx = ch.x; vnth = ch.y;
-      }
-      todo = wballot((vs >> 24) == NBOS_EV_START && vnth >= 0);
+      const int64_t at = min(base + lane, ev_hi - 1);
+      vt = p.ev_time[at]; vs = (uint32_t)p.ev_sk[at];
+      const int2 ch = p.cl_chain[at];
+      vnx = ch.x; vnth = ch.y;
+      todo = wballot((base + lane < ev_hi) & ((vs >> 24) == NBOS_EV_START) & (vnth >= 0));
     } else {
       final = true;
     }
@@ -1263,11 +1261,12 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
           if (last >= 0) { r.t_end = r.t_end > last ? r.t_end : last; continue; }
         }
         if (!(lane_get(c.qx, 0) & CLX_LOADED) && ((uint32_t)lane_get((int)c.qk, 0) >> 16) != QK_END) {
-          if (c.lane < r.q_n && !(c.qx & CLX_LOADED) && (c.qk >> 16) != QK_END) {
-            const int2 ch = c.cl_chain[c.qd];
-            c.qx = c.cl_dur[c.qd] | (int32_t)(((uint32_t)c.cl_sk[c.qd] >> 24) << 28) | CLX_LOADED;
-            c.qnx = ch.x; c.qnth = ch.y;
-          }
+          const bool load = (c.lane < r.q_n) & ((c.qx & CLX_LOADED) == 0) & ((c.qk >> 16) != QK_END);
+          const int32_t e = load ? c.qd : 0;                   // (the lanes with nothing to load read event 0)
+          const int2 ch = c.cl_chain[e];
+          const int32_t x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
+          c.qx = load ? x : c.qx;
+          c.qnx = load ? ch.x : c.qnx; c.qnth = load ? ch.y : c.qnth;
         }
         const int32_t now = r.q_head_t;
         const uint32_t key = (uint32_t)lane_get((int)c.qk, 0);

@@ -377,6 +377,11 @@ int set_batch_kernel(nbos_replay *h, int chunks) {
          : chunks <= 8 ? set_batch_kernel_of<8>(h) : chunks <= 12 ? set_batch_kernel_of<12>(h) : set_batch_kernel_of<16>(h);
 }
 
+// LDS of a replay with its hosts in registers: counters, 8 bytes per session, the pre-warmed pool
+size_t reg_lds_bytes(size_t n_cap, bool warm_pool) {
+  return std::max(LDS_HEAD + n_cap * 8 + (warm_pool ? (size_t)WAVE * 16 : 0), LDS_LEAST);
+}
+
 // which flavour of the register kernel: see the comment inside
 int32_t choose_reg_kernel(nbos_replay *h, int maxlds) {
   const nbos_config *cfg = &h->cfg;
@@ -445,8 +450,8 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     h->lds_bytes = (size_t)chunks * WAVE * 32 + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
-    // hosts in registers; 8 bytes per session, 64 staged sessions
-    h->lds_bytes = 64 + 64 + 128 + (warm_pool ? (size_t)WAVE * 16 : 0) + n_cap * 8 + WAVE * 4;
+    // hosts in registers; 8 bytes per session
+    h->lds_bytes = reg_lds_bytes(n_cap, warm_pool);
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     const int nj = (cfg->hosts_max + 7) / 8;
     const uint32_t policy = cfg->flags & kPolicyFlags;
@@ -454,7 +459,7 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     else set_reg_closed_kernel<kRuntimeClosed>(h, nj);
   } else if (closed_loop) {
     // 12 bytes of record and 4 of timer per session; 64 staged sessions
-    h->lds_bytes = 64 + 64 + 128 + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
+    h->lds_bytes = LDS_HEAD + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
                    (n_cap + 3) / 4 * 16 + WAVE * 4;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     // instances for the common flag sets, as for the other kernels
@@ -465,13 +470,13 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     else if (policy == (NBOS_F_MIGRATE | NBOS_F_SCALE_OUT)) set_closed_kernel<kMigrOut>(h);
     else set_closed_kernel<kRuntimeClosed>(h);
   } else if (sh->in_regs) {
-    h->lds_bytes = 64 + 64 + 128 + (warm_pool ? (size_t)WAVE * 16 : 0) + n_cap * 8 + WAVE * 4;      // + 64 staged sessions
+    h->lds_bytes = reg_lds_bytes(n_cap, warm_pool);
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     const int32_t rc = choose_reg_kernel(h, maxlds);
     if (rc != NBOS_OK) return rc;
   } else {
     // 12 bytes of record and 4 of timer per session; 64 staged sessions
-    h->lds_bytes = 64 + 64 + 128 + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
+    h->lds_bytes = LDS_HEAD + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
                    (n_cap + 3) / 4 * 16 + WAVE * 4;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     // same idea as for the register kernel; its batches are small (the LDS footprint allows few
@@ -774,7 +779,7 @@ int32_t nbos_replay_run_static(const nbos_config *cfg_in, const nbos_inputs *in,
   nbos_replay tmp{};                      // never leaves this call; its vectors stay empty
   tmp.cfg = cfg; tmp.in = *in; tmp.stream = (hipStream_t)stream; tmp.device = dev; tmp.threads = WAVE;
   const bool warm_pool = (cfg.flags & NBOS_F_WARM_POOL) != 0;
-  tmp.lds_bytes = 64 + 64 + 128 + (warm_pool ? (size_t)WAVE * 16 : 0) + n_cap * 8 + WAVE * 4;
+  tmp.lds_bytes = reg_lds_bytes(n_cap, warm_pool);
   int maxlds = 0;
   if (hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return NBOS_E_HIP;
   if (tmp.lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
