@@ -62,7 +62,7 @@ struct KParams {
   const int32_t *trace_of_replay, *cap_milli;
   nbos_stats *stats;
   uint64_t *dlog;          // null unless the decision log is on
-  int32_t *ovf_dur;        // open loop: [n_replays][n_cap] durations of queued cells whose timer is
+  int32_t *ovf_dur;        // open loop: [n_replays][n_cap] (any-size kernel: n_cap + 1) durations of queued cells whose timer is
                            // outside the sorted registers
   int64_t dlog_stride;     // codes per replay
   int32_t n_replays, H0, Hmax, HP, G;
@@ -137,6 +137,12 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// c ? a : b without a branch, whatever a and b take to work out (the compiler likes to move that into an arm)
+__device__ __forceinline__ int32_t pick(bool c, int32_t a, int32_t b) {
+  const int32_t m = c ? -1 : 0;
+  return (a & m) | (b & ~m);
 }
 
 // wave-wide ballot straight from the predicate (no int round trip)

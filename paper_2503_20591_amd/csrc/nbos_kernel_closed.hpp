@@ -117,11 +117,11 @@ __global__ void __launch_bounds__(WAVE) nbos_closed_chain_kernel(const int64_t *
 // records go there, all at once; the others are inserted into the registers one by one.
 template <uint32_t F>
 __device__ __forceinline__ void cl_after_round(Ctx<F> &c, Regs &r, int n) {
-  const bool succ = c.lane < n && c.qnx >= 0;
-  const int32_t ts = succ ? c.qt + (c.qx & 0x0FFFFFFF) + c.qnth : 0;       // in range: checked before the round
+  const bool succ = (c.lane < n) & (c.qnx >= 0);
+  const int32_t ts = pick(succ, c.qt + (c.qx & 0x0FFFFFFF) + c.qnth, 0);   // in range: checked before the round
   const int32_t es = c.qnx;
   const uint32_t ss = c.qk & 0xFFFFu;
-  if (succ) c.cl_cur[ss] = es;
+  c.cl_cur[succ ? (int)ss : c.p.n_cap] = es;        // (one word more than sessions)
   // drop the n earliest
   const int src = ((c.lane + n) & (WAVE - 1)) << 2;
   c.qt = __builtin_amdgcn_ds_bpermute(src, c.qt);
@@ -133,11 +133,13 @@ __device__ __forceinline__ void cl_after_round(Ctx<F> &c, Regs &r, int n) {
   r.q_n -= n;
   r.q_head_t = r.q_n > 0 ? lane_get(c.qt, 0) : NEVER;
   const uint32_t ks = (QK_NEXT << 16) | ss;
-  const bool far = succ && r.o_n > 0 && !(ts < r.o_min_t || (ts == r.o_min_t && ks < r.o_min_k));
+  const bool far = succ & (r.o_n > 0) & !((ts < r.o_min_t) | ((ts == r.o_min_t) & (ks < r.o_min_k)));
   wave_sync();
-  if (far) {
-    c.m.sess[ss].z = (int)(((uint32_t)c.m.sess[ss].z & ~(3u << CL_KIND_SHIFT)) | (QK_NEXT << CL_KIND_SHIFT));
-    c.m.due[ss] = ts;
+  if (wballot(far) != 0) {
+    SessRec *rec = &c.m.sess[far ? ss : 0u];
+    const uint32_t z = (uint32_t)rec->z;
+    *sink(c, far, &rec->z) = (int)((z & ~(3u << CL_KIND_SHIFT)) | (QK_NEXT << CL_KIND_SHIFT));
+    *sink(c, far, &c.m.due[far ? ss : 0u]) = ts;
   }
   wave_sync();
   r.o_n += __builtin_popcountll(wballot(far));
@@ -169,7 +171,7 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_closed_kernel(KP
 
   const int32_t caplim = p.cap_milli[rep] * p.G * 3;
   Ctx<F> c{p, m, lane, caplim / 1000, p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr,
-           NEVER, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, n_sess, p.cl_cursor + (int64_t)rep * p.n_cap,
+           NEVER, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, n_sess, p.cl_cursor + (int64_t)rep * (p.n_cap + 1),
            p.ev_dur + ev_lo, p.ev_sk + ev_lo, p.cl_chain + ev_lo, 0, -1, 0};
   Regs r;
   memset(&r, 0, sizeof r);
@@ -179,7 +181,7 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_closed_kernel(KP
   r.min_s = -1;
   r.cl_win = 1024;
   c.nw = (int)(blockDim.x / WAVE);
-  c.wid = (int)(threadIdx.x / WAVE);
+  c.wid = uni((int)(threadIdx.x / WAVE));
   c.dyn = dynamic_limit_matters(p, c.flags(), c.slim);
   c.n_on = p.H0;
   if (c.wid != 0) {
@@ -197,12 +199,11 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_closed_kernel(KP
     int32_t vt = 0, vnx = -1, vnth = -1;
     uint32_t vs = 0;
     if (base < ev_hi) {
-      if (base + lane < ev_hi) {
-        vt = p.ev_time[base + lane]; vs = (uint32_t)p.ev_sk[base + lane];
-        const int2 ch = p.cl_chain[base + lane];
-        vnx = ch.x; vnth = ch.y;
-      }
-      todo = wballot((vs >> 24) == NBOS_EV_START && vnth >= 0);
+      const int64_t at = min(base + lane, ev_hi - 1);
+      vt = p.ev_time[at]; vs = (uint32_t)p.ev_sk[at];
+      const int2 ch = p.cl_chain[at];
+      vnx = ch.x; vnth = ch.y;
+      todo = wballot((base + lane < ev_hi) & ((vs >> 24) == NBOS_EV_START) & (vnth >= 0));
     } else {
       final = true;
     }
@@ -216,11 +217,12 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_closed_kernel(KP
         if (!(lane_get(c.qx, 0) & CLX_LOADED) && ((uint32_t)lane_get((int)c.qk, 0) >> 16) != QK_END) {
           // the earliest timer was scheduled straight into the registers: its event's duration, kind and
           // chain record are loaded now, and with them those of all other such timers (one round trip)
-          if (c.lane < r.q_n && !(c.qx & CLX_LOADED) && (c.qk >> 16) != QK_END) {
-            const int2 ch = c.cl_chain[c.qd];
-            c.qx = c.cl_dur[c.qd] | (int32_t)(((uint32_t)c.cl_sk[c.qd] >> 24) << 28) | CLX_LOADED;
-            c.qnx = ch.x; c.qnth = ch.y;
-          }
+          const bool load = (c.lane < r.q_n) & ((c.qx & CLX_LOADED) == 0) & ((c.qk >> 16) != QK_END);
+          const int32_t e = load ? c.qd : 0;                   // (the lanes with nothing to load read event 0)
+          const int2 ch = c.cl_chain[e];
+          const int32_t x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
+          c.qx = pick(load, x, c.qx);
+          c.qnx = pick(load, ch.x, c.qnx); c.qnth = pick(load, ch.y, c.qnth);
         }
         // a round needs the next cells of two sessions at the head at least
         if (batching && cooldown == 0 && r.q_n >= 2 && ((uint32_t)lane_get((int)c.qk, 0) >> 16) == QK_NEXT &&
@@ -230,16 +232,15 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_closed_kernel(KP
           // (its event's data are loaded), and if no successor that the run schedules could come
           // before it: it is earlier than the earliest "finish + think time" over all of them.
           const uint32_t sid = c.qk & 0xFFFFu;
-          const bool cell = c.lane < r.q_n && (c.qk >> 16) == QK_NEXT && (c.qx & CLX_LOADED) != 0 &&
-                            (((uint32_t)c.qx >> 28) & 3u) == NBOS_EV_CELL && c.qt <= t;
-          SessRec rec = {0, 0, 0};
-          if (cell) rec = m.sess[sid];
+          const bool cell = (c.lane < r.q_n) & ((c.qk >> 16) == QK_NEXT) & ((c.qx & CLX_LOADED) != 0) &
+                            ((((uint32_t)c.qx >> 28) & 3u) == NBOS_EV_CELL) & (c.qt <= t);
+          const SessRec rec = m.sess[cell ? sid : 0u];
           const int32_t vd = c.qx & 0x0FFFFFFF;
-          const int64_t after = (int64_t)c.qt + vd + (c.qnx >= 0 ? c.qnth : 0);
-          const bool ok = cell && ((uint32_t)rec.z & 7u) == SS_PLACED && rec.y <= c.qt && !((uint32_t)rec.z & SF_ENDING) &&
-                          after < 0x7FFFFFFFLL;
-          const int32_t bound = (int32_t)wave_min(ok && c.qnx >= 0 ? (uint32_t)after : 0x7FFFFFFFu);
-          const uint64_t out = ~wballot(ok && c.qt < bound);
+          const int64_t after = (int64_t)c.qt + vd + pick(c.qnx >= 0, c.qnth, 0);
+          const bool ok = cell & (((uint32_t)rec.z & 7u) == SS_PLACED) & (rec.y <= c.qt) & (((uint32_t)rec.z & SF_ENDING) == 0) &
+                          (after < 0x7FFFFFFFLL);
+          const int32_t bound = (int32_t)wave_min(ok & (c.qnx >= 0) ? (uint32_t)after : 0x7FFFFFFFu);
+          const uint64_t out = ~wballot(ok & (c.qt < bound));
           const int k = out != 0 ? (int)__builtin_ctzll(out) : WAVE;
           if (k >= 2) {
             const uint64_t run = k >= WAVE ? ~0ull : ((1ull << k) - 1ull);

@@ -58,8 +58,8 @@ struct Lds {
   uint32_t *hsn;
   SessRec *sess;
   int32_t *due;                // [n_cap] time of a session's timer while it waits outside the registers, else NEVER
-  int32_t *stage;              // [64] sessions whose timers move into the registers
-  int32_t *mail;               // [MAIL_WORDS] what the helper waves are to do, and what they found (see helpers_go)
+  int32_t *mail;               // [MAIL_WORDS] what the helper waves are to do, and what they found (see helpers_go);
+                               // words 4 to 7: where lanes that have nothing to store store it (see sink)
 };
 
 struct Regs {
@@ -122,27 +122,27 @@ constexpr int32_t QD_DUR_MASK = (1 << QD_G_SHIFT) - 1;
 
 template <uint32_t F>
 __device__ __forceinline__ void sess_write(Ctx<F> &c, Regs &r, uint32_t s, uint32_t hw, int32_t tm, uint32_t fl) {
-  if (c.lane == 0) { c.m.sess[s].x = (int)hw; c.m.sess[s].y = tm; c.m.sess[s].z = (int)fl; }
+  c.m.sess[s].x = (int)hw; c.m.sess[s].y = tm; c.m.sess[s].z = (int)fl;
   r.dirty |= wballot(c.vsid == s);
 }
 template <uint32_t F>
 __device__ __forceinline__ void sess_write_flag(Ctx<F> &c, Regs &r, uint32_t s, uint32_t fl) {
-  if (c.lane == 0) c.m.sess[s].z = (int)fl;
+  c.m.sess[s].z = (int)fl;
   r.dirty |= wballot(c.vsid == s);
 }
+// Where a lane stores a word: at p, or nowhere that matters. (A store that only some lanes do is done by all.)
+template <uint32_t F>
+__device__ __forceinline__ int32_t *sink(const Ctx<F> &c, bool store, int32_t *p) { return store ? p : c.m.mail + 4; }
 
 // ---- timers outside the sorted registers wait in the session records ---------------------------------
 template <uint32_t F>
 __device__ __forceinline__ void ovf_push(Ctx<F> &c, Regs &r, int32_t t, uint32_t k, int32_t d) {
   const uint32_t s = k & 0xFFFFu;
-  if (c.lane == 0) {
-    const uint32_t z = (uint32_t)c.m.sess[s].z;
-    c.m.sess[s].z = (int)((z & ~(3u << CL_KIND_SHIFT)) | ((k >> 16) << CL_KIND_SHIFT));
-    c.m.due[s] = t;
-    if constexpr (!Ctx<F>::closed) {
-      if ((k >> 16) == QK_RETRY) c.ovf_dur[s] = d & QD_DUR_MASK;
-    }
-  }
+  wave_sync();
+  const uint32_t z = (uint32_t)c.m.sess[s].z;
+  c.m.sess[s].z = (int)((z & ~(3u << CL_KIND_SHIFT)) | ((k >> 16) << CL_KIND_SHIFT));
+  c.m.due[s] = t;
+  if constexpr (!Ctx<F>::closed) c.ovf_dur[s] = d & QD_DUR_MASK;      // (of a deferred end: not looked at)
   if constexpr (!Ctx<F>::closed) r.dirty |= wballot(c.vsid == s);      // the flags word of the record has changed
   if (r.o_n == 0 || t < r.o_min_t || (t == r.o_min_t && k < r.o_min_k)) { r.o_min_t = t; r.o_min_k = k; }
   r.o_n++;
@@ -160,6 +160,7 @@ template <uint32_t F>
 __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   wave_sync();
   int cnt;
+  int32_t staged = 0;                            // the sessions whose timers come in, one per lane
   int32_t left;                                  // earliest time left behind
   int32_t win = r.cl_win;
   for (;;) {
@@ -169,19 +170,21 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
     int32_t mn = NEVER;                          // earliest time beyond the window, per lane
     // four sessions per lane and step (due[] is padded with NEVER to a multiple of four)
     const int4 *due4 = (const int4 *)c.m.due;
-    for (int s0 = 4 * c.lane; s0 - 4 * c.lane < c.n_sess; s0 += 4 * WAVE) {
-      const int4 d = s0 < c.n_sess ? due4[s0 >> 2] : make_int4(NEVER, NEVER, NEVER, NEVER);
-      const int32_t lo = min(min(d.x, d.y), min(d.z, d.w));
+    const int quads = (c.n_sess + 3) >> 2;
+    for (int q0 = 0; q0 < quads; q0 += WAVE) {
+      const int q = q0 + c.lane, s0 = 4 * q;
+      const int4 d = due4[min(q, quads - 1)];
+      const bool in = q < quads;
+      const int32_t lo = in ? min(min(d.x, d.y), min(d.z, d.w)) : NEVER;
       if (wballot(lo <= T) != 0) {               // rare: some of these timers are inside the window
 #pragma unroll
         for (int j = 0; j < 4; j++) {
           const int32_t dj = j == 0 ? d.x : j == 1 ? d.y : j == 2 ? d.z : d.w;
-          const bool hit = dj <= T;
+          const bool hit = in & (dj <= T);
           const uint64_t b = wballot(hit);
-          const int pos = cnt + lane_rank(b);
-          if (hit && pos < WAVE) c.m.stage[pos] = s0 + j;
+          staged = cnt < WAVE ? stage_hits(staged, c.lane, cnt, hit, b, s0 + j) : staged;
           cnt += __builtin_popcountll(b);
-          mn = hit ? mn : (dj < mn ? dj : mn);
+          mn = hit | !in ? mn : min(dj, mn);
         }
       } else {
         mn = lo < mn ? lo : mn;
@@ -198,11 +201,13 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
       // more than 64 timers at the instant o_min_t: the earliest by kind and session alone
       wave_sync();
       uint32_t best = 0xFFFFFFFFu;
-      for (int s = c.lane; s < c.n_sess; s += WAVE) {
-        if (c.m.due[s] == T) best = umin(best, ((((uint32_t)c.m.sess[s].z >> CL_KIND_SHIFT) & 3u) << 16) | (uint32_t)s);
+      for (int s0 = 0; s0 < c.n_sess; s0 += WAVE) {
+        const int s = min(s0 + c.lane, c.n_sess - 1);          // (the last session more than once: no matter)
+        const uint32_t k = ((((uint32_t)c.m.sess[s].z >> CL_KIND_SHIFT) & 3u) << 16) | (uint32_t)s;
+        best = umin(best, c.m.due[s] == T ? k : 0xFFFFFFFFu);
       }
       best = wave_min(best);
-      if (c.lane == 0) c.m.stage[0] = (int32_t)(best & 0xFFFFu);
+      staged = (int32_t)(best & 0xFFFFu);
       cnt = 1;
       left = T;
       break;
@@ -214,35 +219,37 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   else if (cnt > 7 * WAVE / 8) r.cl_win = win - win / 4;
   else r.cl_win = win;
   wave_sync();
-  // lane i < cnt takes the timer of session stage[i]
+  // lane i < cnt takes the timer of the session staged there
   const bool take = c.lane < cnt;
-  uint32_t key = 0xFFFFFFFFu;
-  int32_t t = NEVER, e = 0;
-  if (take) {
-    const int s = c.m.stage[c.lane];
-    t = c.m.due[s];
-    c.m.due[s] = NEVER;
-    key = ((((uint32_t)c.m.sess[s].z >> CL_KIND_SHIFT) & 3u) << 16) | (uint32_t)s;
-  }
+  const int last_staged = lane_get(staged, cnt - 1);
+  const int s = take ? staged : last_staged;     // (the lanes beyond do what the last one does)
+  const int32_t due = c.m.due[s];
+  const uint32_t own_key = ((((uint32_t)c.m.sess[s].z >> CL_KIND_SHIFT) & 3u) << 16) | (uint32_t)s;
+  const int32_t t = take ? due : NEVER;
+  const uint32_t key = take ? own_key : 0xFFFFFFFFu;
+  int32_t e = 0;
+  wave_sync();
+  c.m.due[s] = NEVER;
   // the cursors / durations were written by lane 0 when the timers were scheduled: the fence makes this
   // wave's own stores visible to its other lanes
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   int32_t x = 0, nx = -1, nth = 0;
   if constexpr (Ctx<F>::closed) {
-    if (take) e = c.cl_cur[key & 0xFFFFu];
-    if (take && (key >> 16) != QK_END) {
-      const int2 ch = c.cl_chain[e];
-      x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
-      nx = ch.x; nth = ch.y;
-    }
+    e = c.cl_cur[s];
+    const bool ev = (own_key >> 16) != QK_END;
+    const int32_t at = ev ? e : 0;
+    const int2 ch = c.cl_chain[at];
+    const int32_t own_x = c.cl_dur[at] | (int32_t)(((uint32_t)c.cl_sk[at] >> 24) << 28) | CLX_LOADED;
+    x = ev ? own_x : 0;
+    nx = ev ? ch.x : -1; nth = ev ? ch.y : 0;
   } else {
-    if (take && (key >> 16) == QK_RETRY) e = c.ovf_dur[key & 0xFFFFu];       // qd carries the queued cell's duration
+    e = c.ovf_dur[s];                            // qd carries the queued cell's duration (of a deferred end: not looked at)
   }
   int rank = 0;
   for (int j = 0; j < cnt; j++) {
     const int32_t tj = lane_get(t, j);
     const uint32_t kj = (uint32_t)lane_get((int)key, j);
-    rank += (tj < t || (tj == t && kj < key)) ? 1 : 0;
+    rank += (tj < t) | ((tj == t) & (kj < key)) ? 1 : 0;
   }
   // lanes beyond cnt hold the largest key: their rank is cnt, any order among them will do
   const int dst = take ? rank : c.lane;
@@ -268,16 +275,19 @@ __device__ __forceinline__ int committed(const Ctx<F> &c, int h, int32_t now) {
   return (a.x > now) + (a.y > now) + (a.z > now) + (a.w > now) + (b.x > now) + (b.y > now) + (b.z > now) + (b.w > now);
 }
 
-// bind g free GPUs of host h until `finish` (lanes 0..G-1 each look at one GPU)
+// free GPUs (bits of the low byte) below GPU k
+__device__ __forceinline__ int gpu_rank(uint32_t free_mask, int k) { return __builtin_popcount(free_mask & ((1u << k) - 1u)); }
+
+// bind g free GPUs of host h until `finish` (lane = GPU; every eighth lane does the same)
 template <uint32_t F>
 __device__ __forceinline__ void bind_gpus(Ctx<F> &c, int h, int g, int32_t now, int32_t finish) {
   wave_sync();
   int32_t *row = (int32_t *)&c.m.fin[2 * h];
-  const bool mine = c.lane < c.p.G;
-  const int32_t f = mine ? row[c.lane] : NEVER;
-  const bool fr = mine && f <= now;
-  const int rank = lane_rank(wballot(fr));
-  if (fr && rank < g) row[c.lane] = finish;
+  const int k = c.lane & 7;
+  const int32_t f = row[k];
+  const bool fr = (k < c.p.G) & (f <= now);
+  const int rank = gpu_rank((uint32_t)wballot(fr), k);
+  row[k] = fr & (rank < g) ? finish : f;
 }
 
 // ---- helper waves ------------------------------------------------------------------------------------
@@ -296,7 +306,7 @@ constexpr int MAX_WAVES = 4, MAIL_WORDS = 8 + 4 * MAX_WAVES;
 template <uint32_t F>
 __device__ __forceinline__ void helpers_go(const Ctx<F> &c, int cmd, int32_t now, int g, int32_t room) {
   if (c.nw == 1) return;
-  if (c.lane == 0) *(int4 *)c.m.mail = make_int4(cmd, now, g, room);
+  *(int4 *)c.m.mail = make_int4(cmd, now, g, room);
   __syncthreads();
 }
 template <uint32_t F>
@@ -315,7 +325,7 @@ __device__ __forceinline__ int find_off_host(const Ctx<F> &c) {
   wave_sync();
   for (int base = 0; base < c.p.HP; base += WAVE) {
     const int h = base + c.lane;
-    const uint64_t off = wballot(h < c.p.Hmax && c.m.ready_at[h] == NEVER);
+    const uint64_t off = wballot((h < c.p.Hmax) & (c.m.ready_at[h] == NEVER));
     if (off) return base + (int)__builtin_ctzll(off);
   }
   return 0;
@@ -325,9 +335,9 @@ template <uint32_t F>
 __device__ __forceinline__ int boot_host(Ctx<F> &c, Regs &r, int32_t now, uint32_t hs_new) {
   const int h = find_off_host(c);
   const int32_t ra = now + c.p.boot;
-  if (c.lane == 0) { c.m.ready_at[h] = ra; c.m.hsn[h] = hs_new; }
+  c.m.ready_at[h] = ra; c.m.hsn[h] = hs_new;
   if (c.flags() & NBOS_F_WARM_POOL) {         // its pre-warmed containers are there once it is up
-    if (c.lane < 4) c.m.warm[4 * h + c.lane] = ra + c.p.prewarm;
+    c.m.warm[4 * h + (c.lane & 3)] = ra + c.p.prewarm;
   }
   c.fu = c.fu < ra ? c.fu : ra;               // a new host may have idle GPUs from then on
   c.fc = c.fc < ra ? c.fc : ra;
@@ -348,18 +358,19 @@ template <uint32_t F>
 __device__ __forceinline__ uint32_t best_host_part(const Ctx<F> &c, int32_t now, int g, int32_t room, bool &any_idle) {
   uint32_t best = 0xFFFFFFFFu;
   bool idle_seen = false;
-  for (int h = c.wid * WAVE + c.lane; h < c.p.HP; h += WAVE * c.nw) {
+  for (int h0 = c.wid * WAVE; h0 < c.p.HP; h0 += WAVE * c.nw) {
+    const int h = h0 + c.lane;
     const int32_t ra = c.m.ready_at[h];
     const int S = (int)(c.m.hsn[h] & 0xFFFFu);
-    const bool capped = ra <= now && S <= room;
+    const bool capped = (ra <= now) & (S <= room);
     // the GPU rows are only read for a chunk of hosts in which somebody passes the cap (or while it
     // is still open whether any host has g idle GPUs)
     if (wballot(capped) == 0 && idle_seen) continue;
     const int C = committed(c, h, now);
-    const bool roomy = ra <= now && C + g <= c.p.G;
-    idle_seen = idle_seen || wballot(roomy) != 0;
+    const bool roomy = (ra <= now) & (C + g <= c.p.G);
+    idle_seen = idle_seen | (wballot(roomy) != 0);
     const uint32_t key = ((uint32_t)C << 22) | ((uint32_t)S << 10) | (uint32_t)h;
-    if (capped && roomy) best = umin(best, key);
+    best = umin(best, capped & roomy ? key : 0xFFFFFFFFu);
   }
   any_idle = idle_seen;
   return wave_min(best);
@@ -373,7 +384,7 @@ __device__ __forceinline__ uint32_t best_host(const Ctx<F> &c, int32_t now, int 
   helpers_done(c);
   for (int w = 1; w < c.nw; w++) {
     key = umin(key, helper_result(c, w, 0));
-    any_idle = any_idle || helper_result(c, w, 1) != 0;
+    any_idle = any_idle | (helper_result(c, w, 1) != 0);
   }
   return key;
 }
@@ -383,15 +394,15 @@ template <uint32_t F>
 __device__ __forceinline__ int32_t min_subscription(const Ctx<F> &c) {
   wave_sync();
   uint32_t best = 0xFFFFu;
-  for (int h = c.lane; h < c.p.HP; h += WAVE) {
-    const uint32_t S = c.m.hsn[h] & 0xFFFFu;
-    if (c.m.ready_at[h] != NEVER) best = umin(best, S);
+  for (int h0 = 0; h0 < c.p.HP; h0 += WAVE) {
+    const uint32_t S = c.m.hsn[h0 + c.lane] & 0xFFFFu;
+    best = umin(best, c.m.ready_at[h0 + c.lane] != NEVER ? S : 0xFFFFu);
   }
   return (int32_t)wave_min(best);
 }
 
 __device__ __forceinline__ void order2(int32_t &a, int32_t &b) {
-  const int32_t lo = a < b ? a : b, hi = a < b ? b : a;
+  const int32_t lo = min(a, b), hi = max(a, b);
   a = lo; b = hi;
 }
 
@@ -406,7 +417,9 @@ __device__ __forceinline__ int32_t kth_free_time(const int4 a, const int4 b, int
   order2(v0, v4); order2(v1, v5); order2(v2, v6); order2(v3, v7);
   order2(v2, v4); order2(v3, v5);
   order2(v1, v2); order2(v3, v4); order2(v5, v6);
-  return g == 1 ? v0 : g == 2 ? v1 : g == 3 ? v2 : g == 4 ? v3 : g == 5 ? v4 : g == 6 ? v5 : g == 7 ? v6 : v7;
+  v6 = g & 1 ? v6 : v7;   v4 = g & 1 ? v4 : v5;   v2 = g & 1 ? v2 : v3;   v0 = g & 1 ? v0 : v1;      // a choice by the bits of g - 1
+  v4 = (g - 1) & 2 ? v6 : v4;   v0 = (g - 1) & 2 ? v2 : v0;
+  return (g - 1) & 4 ? v4 : v0;
 }
 
 // Earliest time at which some host that is on could have g idle GPUs if nothing new were committed:
@@ -420,7 +433,8 @@ template <uint32_t F>
 __device__ __forceinline__ int32_t earliest_idle_part(const Ctx<F> &c, int g, int32_t room, int32_t &capped) {
   const int G = c.p.G;
   int32_t best = NEVER, best_cap = NEVER;
-  for (int h = c.wid * WAVE + c.lane; h < c.p.HP; h += WAVE * c.nw) {
+  for (int h0 = c.wid * WAVE; h0 < c.p.HP; h0 += WAVE * c.nw) {
+    const int h = h0 + c.lane;
     int32_t y = kth_free_time(c.m.fin[2 * h], c.m.fin[2 * h + 1], G, g);
     const int32_t ra = c.m.ready_at[h];
     y = y > ra ? y : ra;
@@ -452,13 +466,13 @@ __device__ __forceinline__ int32_t earliest_idle(const Ctx<F> &c, int g, int32_t
 template <uint32_t F>
 __device__ __forceinline__ void cap_bound_host_freed(Ctx<F> &c, int h, int32_t s_new, int32_t now) {
   if ((c.flags() & NBOS_F_DYNAMIC_SR) && c.dyn) return;   // the limit moves with the cluster's sums: no bound is kept
-  if (wballot(c.lane < NGPU && c.fc > now) == 0) return;  // every bound lies in the past already: as good as none
+  if (wballot((c.lane < NGPU) & (c.fc > now)) == 0) return;  // every bound lies in the past already: as good as none
   wave_sync();
   const int g = (c.lane & 7) + 1;
   int32_t y = kth_free_time(c.m.fin[2 * h], c.m.fin[2 * h + 1], c.p.G, g);
   const int32_t ra = c.m.ready_at[h];
   y = y > ra ? y : ra;
-  if (c.lane < NGPU && s_new + g <= c.slim && y < c.fc) c.fc = y;
+  c.fc = (c.lane < NGPU) & (s_new + g <= c.slim) & (y < c.fc) ? y : c.fc;
 }
 
 // ---- closed loop: the session's next event is due one think time after `base` --------------------
@@ -470,8 +484,14 @@ __device__ __forceinline__ void cl_schedule(Ctx<F> &c, Regs &r, uint32_t s, int3
   if (e < 0) return;
   const int64_t t = (int64_t)base + r.cl_nth;
   if (t >= 0x7FFFFFFFLL) { r.status = NBOS_E_RANGE; return; }
-  if (c.lane == 0) c.cl_cur[s] = e;
+  c.cl_cur[s] = e;
   timer_push(c, r, (int32_t)t, QK_NEXT, s, e);
+}
+
+// host h: S | replicas << 16 changes by `by` (one ds_add, nothing to wait for; the other lanes add 0 to neighbours)
+template <uint32_t F>
+__device__ __forceinline__ void subscribe(const Ctx<F> &c, int h, uint32_t by) {
+  atomicAdd(&c.m.hsn[h ^ c.lane], c.lane == 0 ? by : 0u);
 }
 
 // Placement candidates among this wave's chunks of hosts (Sections 3.2.1, 3.4.1): ready and under the cap;
@@ -485,11 +505,11 @@ __device__ __forceinline__ void place_part(const Ctx<F> &c, int32_t now, int32_t
 #pragma unroll
   for (int j = 0; j < MAXCH; j++) {
     keys[j] = 0xFFFFFFFFu;
-    const int h = (j * c.nw + c.wid) * WAVE + c.lane;
-    if (h - c.lane < c.p.HP) {
+    const int h0 = (j * c.nw + c.wid) * WAVE, h = h0 + c.lane;
+    if (h0 < c.p.HP) {
       const int S = (int)(c.m.hsn[h] & 0xFFFFu);
-      if (c.m.ready_at[h] <= now && S <= room)
-        keys[j] = ((uint32_t)committed(c, h, now) << 22) | ((uint32_t)S << 10) | (uint32_t)h;
+      const uint32_t key = ((uint32_t)committed(c, h, now) << 22) | ((uint32_t)S << 10) | (uint32_t)h;
+      keys[j] = (c.m.ready_at[h] <= now) & (S <= room) ? key : 0xFFFFFFFFu;
     }
   }
   uint32_t out[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
@@ -520,10 +540,10 @@ __device__ __forceinline__ void session_start(Ctx<F> &c, Regs &r, uint32_t s, ui
   else place_part<NBOS_MAX_HOSTS / WAVE>(c, now, room, m0, m1, m2);
   if (c.nw > 1) {
     // the three best of every wave meet in the mail words: the three best of those are the hosts
-    if (c.lane == 0) { c.m.mail[8] = (int)m0; c.m.mail[9] = (int)m1; c.m.mail[10] = (int)m2; }
+    c.m.mail[8] = (int)m0; c.m.mail[9] = (int)m1; c.m.mail[10] = (int)m2;
     helpers_done(c);
-    uint32_t key = 0xFFFFFFFFu;
-    if (c.lane < 4 * c.nw && (c.lane & 3) != 3) key = (uint32_t)c.m.mail[8 + c.lane];
+    const uint32_t found = (uint32_t)c.m.mail[8 + (c.lane & (4 * MAX_WAVES - 1))];
+    uint32_t key = (c.lane < 4 * c.nw) & ((c.lane & 3) != 3) ? found : 0xFFFFFFFFu;
     m0 = wave_min(key);
     key = key == m0 ? 0xFFFFFFFFu : key;
     m1 = wave_min(key);
@@ -551,7 +571,7 @@ __device__ __forceinline__ void session_start(Ctx<F> &c, Regs &r, uint32_t s, ui
     int h = i == 0 ? pick0 : (i == 1 ? pick1 : pick2);
     if (i < k) {
       r.min_s = -1;
-      if (c.lane == 0) atomicAdd(&c.m.hsn[h], add);          // (one ds_add, nothing to wait for)
+      subscribe(c, h, add);
       decide(c, r, now, NBOS_D_PLACE, s, (uint32_t)i, (uint32_t)h);
     } else {
       h = boot_host(c, r, now, add);
@@ -576,10 +596,8 @@ template <uint32_t F>
 __device__ __forceinline__ void end_session(Ctx<F> &c, Regs &r, uint32_t s, uint32_t hw, uint32_t fl, int32_t now) {
   const int g = (int)((fl >> 3) & 7u) + 1;
   const uint32_t sub = (uint32_t)g | (1u << 16);
-  if (c.lane < 3) {
-    const int h = (int)((hw >> (10 * c.lane)) & 1023u);
-    atomicSub(&c.m.hsn[h], sub);                // three distinct hosts, one lane each
-  }
+  const int hl = (int)((hw >> ((10 * c.lane) & 31)) & 1023u);   // three distinct hosts, one lane each
+  atomicSub(&c.m.hsn[c.lane < 3 ? hl : c.lane], c.lane < 3 ? sub : 0u);
   r.min_s = -1;
   if (!((c.flags() & NBOS_F_DYNAMIC_SR) && c.dyn)) {
     wave_sync();
@@ -617,21 +635,13 @@ __device__ __forceinline__ void start_cell(Ctx<F> &c, Regs &r, uint32_t s, uint3
   const uint32_t nfl = (fl & ~(7u | SF_QONCE | (15u << 8))) | SS_PLACED;
   if (delay == 0) {
     r.h0++;                                     // histogram bin 0 lives in a register
-    if (c.lane == 0) {
-      c.m.sess[s].x = (int)hw; c.m.sess[s].y = finish;
-      if (nfl != fl) c.m.sess[s].z = (int)nfl;
-    }
   } else {
-    int b = 32 - __builtin_clz((uint32_t)delay);
-    b = b > 31 ? 31 : b;
-    if (c.lane == 0) {
-      c.m.sess[s].x = (int)hw; c.m.sess[s].y = finish; c.m.sess[s].z = (int)nfl;
-      atomicAdd(&c.m.hist[b], 1u);
-      atomicAdd(&c.m.c64[CL_SUMDELAY], (unsigned long long)delay);
-      atomicMax(&c.m.c32[CS_MAXDELAY], (uint32_t)delay);
-      atomicAdd(&c.m.c64[CL_GWAIT], (unsigned long long)((int64_t)g * (start - now)));
-    }
+    hist_add(c.m, c.lane, delay);
+    c64_add(c.m, c.lane, CL_SUMDELAY, delay);
+    c32_max(c.m, c.lane, CS_MAXDELAY, (uint32_t)delay);
+    c64_add(c.m, c.lane, CL_GWAIT, (int64_t)g * (start - now));
   }
+  c.m.sess[s].x = (int)hw; c.m.sess[s].y = finish; c.m.sess[s].z = (int)nfl;
   r.dirty |= wballot(c.vsid == s);
   r.lazy_max = r.lazy_max > finish ? r.lazy_max : finish;
   decide(c, r, now, outcome, s, (uint32_t)slot, (uint32_t)host);
@@ -662,7 +672,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
   int32_t *row = (int32_t *)&c.m.fin[2 * hr];
   const int32_t f = row[k];
   const int32_t ra = c.m.ready_at[hr];
-  const uint64_t busy = wballot(act && f > now);
+  const uint64_t busy = wballot(act & (f > now));
   const uint64_t rdy = wballot(ra <= now);
   const int C0 = __builtin_popcount((uint32_t)busy & 0xFFu), C1 = __builtin_popcount((uint32_t)(busy >> 8) & 0xFFu),
             C2 = __builtin_popcount((uint32_t)(busy >> 16) & 0xFFu);
@@ -680,9 +690,10 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
     }
     if (kb != 0xFFFFFFFFu) {
       const int lead = (int)(kb & 3u), hl = (int)((kb >> 2) & 1023u);
-      const bool fr = act && (c.lane >> 3) == lead && k < G && f <= now;
-      const int rank = lane_rank(wballot(fr));
-      if (fr && rank < g) row[k] = now + dur;
+      // (every lane writes the GPU it has read: the lead's free ones get the new time; lanes 24 up do what 16 to 23 do)
+      const bool fr = (k < G) & (f <= now);
+      const int rank = gpu_rank((uint32_t)(wballot(fr) >> (8 * lead)), k);
+      row[k] = (rr == lead) & fr & (rank < g) ? now + dur : f;
       if (now == t_submit) r.c_imm++;
       start_cell(c, r, s, hw, fl, lead, hl, now, now, t_submit, dur, NBOS_D_START);
       return (Ctx<F>::closed || (fl & SF_ENDING)) ? -1 : NEVER;      // (those push a timer of their own)
@@ -704,7 +715,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
           // every later attempt with a request of g or more.
           int32_t unused;
           const int32_t bound = earliest_idle(c, g, room, unused);
-          if (c.lane >= g - 1 && c.fu < bound) c.fu = bound;
+          c.fu = (c.lane >= g - 1) & (c.fu < bound) ? bound : c.fu;
         }
       }
     } else if (now >= lane_get(c.fc, g - 1)) {
@@ -717,10 +728,8 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
         // under the cap, once, for every later attempt with a request of g or more.
         int32_t under_cap;
         const int32_t bound = earliest_idle(c, g, room, under_cap);
-        if (c.lane >= g - 1) {
-          if (c.fu < bound) c.fu = bound;
-          if (c.fc < under_cap) c.fc = under_cap;
-        }
+        c.fu = (c.lane >= g - 1) & (c.fu < bound) ? bound : c.fu;
+        c.fc = (c.lane >= g - 1) & (c.fc < under_cap) ? under_cap : c.fc;
       }
     }
   }
@@ -746,17 +755,19 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
         // Section 3.2.3: the target's pre-warmed container that has been available longest, if any
         // is available now, shortens the start; its replacement is there one pre-warm time later
         wave_sync();
-        const uint32_t av = c.lane < c.p.warm_n ? (uint32_t)c.m.warm[4 * dst + c.lane] : 0xFFFFFFFFu;
+        const uint32_t av_own = (uint32_t)c.m.warm[4 * dst + (c.lane & 3)];
+        const uint32_t av = c.lane < c.p.warm_n ? av_own : 0xFFFFFFFFu;
         const uint32_t first = wave_min(av);
         if ((int32_t)first <= now) {
           const int w = (int)__builtin_ctzll(wballot(av == first));
-          if (c.lane == w) c.m.warm[4 * dst + w] = now + c.p.prewarm;
+          c.m.warm[4 * dst + w] = now + c.p.prewarm;
           start = now + c.p.warm_migr;
           outcome = NBOS_D_MIGRATE_WARM;
           c32_add(c.m, c.lane, CS_MIGRWARM, 1u);
         }
       }
-      if (c.lane == 0) { atomicSub(&c.m.hsn[hv], moved); atomicAdd(&c.m.hsn[dst], moved); }
+      subscribe(c, hv, 0u - moved);
+      subscribe(c, dst, moved);
       r.min_s = -1;
       wave_sync();
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
@@ -768,7 +779,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
     } else {
       // (c) a new host for the cell, Section 3.4.2: reserved and bound before it is up
       const int32_t start = now + c.p.boot + c.p.migr;
-      if (c.lane == 0) atomicSub(&c.m.hsn[hv], moved);
+      subscribe(c, hv, 0u - moved);
       r.min_s = -1;
       wave_sync();
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
@@ -787,10 +798,9 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
     const uint32_t nfl = (fl & ~(7u | (15u << 8))) | SS_QUEUED | SF_QONCE | ((uint32_t)retries << 8);
     if (!(fl & SF_QONCE)) {                      // first time in the queue: the submit time goes in
       c32_add(c.m, c.lane, CS_QUEUED, 1u);
-      if (c.lane == 0) { c.m.sess[s].y = t_submit; c.m.sess[s].z = (int)nfl; }
-    } else {
-      if (c.lane == 0) c.m.sess[s].z = (int)nfl;
+      c.m.sess[s].y = t_submit;
     }
+    c.m.sess[s].z = (int)nfl;
     r.dirty |= wballot(c.vsid == s);
     if constexpr (Ctx<F>::closed) {
       if ((int64_t)t_submit + (int64_t)retries * c.p.retry_iv >= 0x7FFFFFFFLL) { r.status = NBOS_E_RANGE; return -1; }
@@ -828,10 +838,10 @@ __device__ __forceinline__ void release_host(Ctx<F> &c, Regs &r, int32_t now) {
   wave_sync();
   for (int base = c.p.HP - WAVE; base >= 0 && victim < 0; base -= WAVE) {
     const int h = base + c.lane;
-    const uint64_t e = wballot(c.m.ready_at[h] <= now && (c.m.hsn[h] >> 16) == 0);
+    const uint64_t e = wballot((c.m.ready_at[h] <= now) & ((c.m.hsn[h] >> 16) == 0));
     if (e) victim = base + 63 - (int)__builtin_clzll(e);
   }
-  if (c.lane == 0) c.m.ready_at[victim] = NEVER;
+  c.m.ready_at[victim] = NEVER;
   r.min_s = -1;
   c32_add(c.m, c.lane, CS_NON, (uint32_t)-1);
   c.n_on--;
@@ -846,10 +856,11 @@ __device__ __forceinline__ void tick_part(const Ctx<F> &c, int32_t now, int &A, 
   const bool autoscale = (c.flags() & NBOS_F_AUTOSCALE) != 0;
   A = 0; Z = 0;
   uint32_t busy = 0;                       // this lane's share of sum C
-  for (int h = c.wid * WAVE + c.lane; h < c.p.HP; h += WAVE * c.nw) {
+  for (int h0 = c.wid * WAVE; h0 < c.p.HP; h0 += WAVE * c.nw) {
+    const int h = h0 + c.lane;
     const bool ready = c.m.ready_at[h] <= now;
     A += __builtin_popcountll(wballot(ready));
-    Z += __builtin_popcountll(wballot(ready && (c.m.hsn[h] >> 16) == 0));
+    Z += __builtin_popcountll(wballot(ready & ((c.m.hsn[h] >> 16) == 0)));
     if (autoscale) busy += (uint32_t)committed(c, h, now);
   }
   sum_c = autoscale ? (uint32_t)wave_sum(busy) : 0u;
@@ -881,7 +892,7 @@ __device__ __forceinline__ void helper_loop(const Ctx<F> &c) {
       tick_part(c, now, A, Z, r2);
       r0 = (uint32_t)A; r1 = (uint32_t)Z;
     }
-    if (c.lane == 0) { c.m.mail[8 + 4 * c.wid] = (int)r0; c.m.mail[9 + 4 * c.wid] = (int)r1; c.m.mail[10 + 4 * c.wid] = (int)r2; }
+    c.m.mail[8 + 4 * c.wid] = (int)r0; c.m.mail[9 + 4 * c.wid] = (int)r1; c.m.mail[10 + 4 * c.wid] = (int)r2;
     __syncthreads();
   }
 }
@@ -958,21 +969,19 @@ template <uint32_t F>
 __device__ __forceinline__ void retry_lookahead(Ctx<F> &c, const Regs &r) {
   wave_sync();
   const int G = c.p.G;
-  const bool cand = c.lane < r.q_n && (c.qk >> 16) == QK_RETRY && !((uint32_t)c.qd & QD_LOOKED);
-  if (cand) {
-    const SessRec rec = c.m.sess[c.qk & 0xFFFFu];
-    const uint32_t hw = (uint32_t)rec.x, fl = (uint32_t)rec.z;
-    const int g = (int)((fl >> 3) & 7u) + 1;
-    const int32_t vt = c.qt;
-    const uint32_t h0 = hw & 1023u, h1 = (hw >> 10) & 1023u, h2 = (hw >> 20) & 1023u;
-    const int C0 = committed(c, (int)h0, vt), C1 = committed(c, (int)h1, vt), C2 = committed(c, (int)h2, vt);
-    const bool can = (c.m.ready_at[h0] <= vt && C0 + g <= G) || (c.m.ready_at[h1] <= vt && C1 + g <= G) ||
-                     (c.m.ready_at[h2] <= vt && C2 + g <= G);
-    const bool more = (int)((fl >> 8) & 15u) < c.p.max_retries;        // not the retry that gives the cell up
-    uint32_t d = (uint32_t)c.qd | QD_LOOKED;
-    if (!can && more) d |= QD_EFAIL | ((uint32_t)(g - 1) << QD_G_SHIFT);
-    c.qd = (int32_t)d;
-  }
+  const bool cand = (c.lane < r.q_n) & ((c.qk >> 16) == QK_RETRY) & (((uint32_t)c.qd & QD_LOOKED) == 0);
+  const SessRec rec = c.m.sess[cand ? c.qk & 0xFFFFu : 0u];
+  const uint32_t hw = (uint32_t)rec.x, fl = (uint32_t)rec.z;
+  const int g = (int)((fl >> 3) & 7u) + 1;
+  const int32_t vt = c.qt;
+  const uint32_t h0 = hw & 1023u, h1 = (hw >> 10) & 1023u, h2 = (hw >> 20) & 1023u;
+  const int C0 = committed(c, (int)h0, vt), C1 = committed(c, (int)h1, vt), C2 = committed(c, (int)h2, vt);
+  const bool can = ((c.m.ready_at[h0] <= vt) & (C0 + g <= G)) | ((c.m.ready_at[h1] <= vt) & (C1 + g <= G)) |
+                   ((c.m.ready_at[h2] <= vt) & (C2 + g <= G));
+  const bool more = (int)((fl >> 8) & 15u) < c.p.max_retries;        // not the retry that gives the cell up
+  const uint32_t efail = QD_EFAIL | ((uint32_t)(g - 1) << QD_G_SHIFT);
+  const uint32_t d = (uint32_t)c.qd | QD_LOOKED | (!can & more ? efail : 0u);
+  c.qd = pick(cand, (int32_t)d, c.qd);
 }
 
 // hosts can be added right now (a failed election then gets a host instead of a place in the queue)
@@ -987,8 +996,8 @@ __device__ __forceinline__ bool retry_is_quiet(const Ctx<F> &c, const Regs &r) {
   const uint32_t d = (uint32_t)c.qd;
   const int32_t bound_own = c.fu > c.fc ? c.fu : c.fc;                  // lane g-1: no target before this time
   const int32_t bound = __builtin_amdgcn_ds_bpermute((int)((d >> QD_G_SHIFT) & 7u) << 2, bound_own);
-  return c.lane < r.q_n && (c.qk >> 16) == QK_RETRY && (d & QD_EFAIL) != 0 &&
-         (!(c.flags() & NBOS_F_MIGRATE) || c.qt < bound);
+  const bool no_target = !(c.flags() & NBOS_F_MIGRATE);
+  return (c.lane < r.q_n) & ((c.qk >> 16) == QK_RETRY) & ((d & QD_EFAIL) != 0) & (no_target | (c.qt < bound));
 }
 
 // Up to which time a run of arrivals may be evaluated without looking at the timers: the time of the first
@@ -1000,9 +1009,9 @@ __device__ __forceinline__ int32_t retry_horizon(Ctx<F> &c, const Regs &r, int32
   if (((uint32_t)lane_get((int)c.qk, 0) >> 16) != QK_RETRY) return r.q_head_t;
   if (can_grow(c)) return r.q_head_t;
   // retries due up to `until` that have not been looked at yet
-  if (wballot(c.lane < r.q_n && (c.qk >> 16) == QK_RETRY && !((uint32_t)c.qd & QD_LOOKED) && c.qt <= until) != 0)
+  if (wballot((c.lane < r.q_n) & ((c.qk >> 16) == QK_RETRY) & (((uint32_t)c.qd & QD_LOOKED) == 0) & (c.qt <= until)) != 0)
     retry_lookahead(c, r);
-  const uint64_t loud = wballot(c.lane < r.q_n && !retry_is_quiet(c, r));
+  const uint64_t loud = wballot((c.lane < r.q_n) & !retry_is_quiet(c, r));
   const int first = loud != 0 ? (int)__builtin_ctzll(loud) : r.q_n;
   if (first == 0) return r.q_head_t;
   int32_t lim = first < r.q_n ? lane_get(c.qt, first) : (r.o_n > 0 ? r.o_min_t : NEVER);
@@ -1023,11 +1032,11 @@ __device__ __forceinline__ int32_t retry_horizon(Ctx<F> &c, const Regs &r, int32
 template <uint32_t F>
 __device__ __forceinline__ bool fire_quiet_retries(Ctx<F> &c, Regs &r, int32_t t_limit, uint64_t queued_lanes) {
   if (((uint32_t)lane_get((int)c.qk, 0) >> 16) != QK_RETRY) return false;
-  if (wballot(c.lane < r.q_n && (c.qk >> 16) == QK_RETRY && !((uint32_t)c.qd & QD_LOOKED) && c.qt <= t_limit) != 0)
+  if (wballot((c.lane < r.q_n) & ((c.qk >> 16) == QK_RETRY) & (((uint32_t)c.qd & QD_LOOKED) == 0) & (c.qt <= t_limit)) != 0)
     retry_lookahead(c, r);
   if (!((uint32_t)lane_get(c.qd, 0) & QD_EFAIL)) return false;
   if (can_grow(c)) return false;
-  const uint64_t loud = ~wballot(retry_is_quiet(c, r) && c.qt <= t_limit);
+  const uint64_t loud = ~wballot(retry_is_quiet(c, r) & (c.qt <= t_limit));
   const int n = loud != 0 ? (int)__builtin_ctzll(loud) : WAVE;        // (quiet timers are below q_n)
   if (n == 0) return false;
   const bool mine = c.lane < n;
@@ -1035,40 +1044,40 @@ __device__ __forceinline__ bool fire_quiet_retries(Ctx<F> &c, Regs &r, int32_t t
   r.t_end = r.t_end > last ? r.t_end : last;
   r.dirty |= queued_lanes;
   wave_sync();
-  const uint32_t s = c.qk & 0xFFFFu;
-  int32_t nt = c.qt;
-  bool far = false;
-  if (mine) {
-    const uint32_t fl = (uint32_t)c.m.sess[s].z;
-    const int retries = (int)((fl >> 8) & 15u) + 1;                    // below max_retries before: see retry_lookahead
-    nt = c.m.sess[s].y + retries * c.p.retry_iv;
-    far = r.o_n > 0 && !(nt < r.o_min_t || (nt == r.o_min_t && c.qk < r.o_min_k));
-    uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
-    if (far) {
-      nfl = (nfl & ~(3u << CL_KIND_SHIFT)) | (QK_RETRY << CL_KIND_SHIFT);
-      c.m.due[s] = nt;
-      c.ovf_dur[s] = c.qd & QD_DUR_MASK;
-    }
-    c.m.sess[s].z = (int)nfl;
-  }
+  const uint32_t s = mine ? c.qk & 0xFFFFu : 0u;
+  const uint32_t fl = (uint32_t)c.m.sess[s].z;
+  const int retries = (int)((fl >> 8) & 15u) + 1;                    // below max_retries before: see retry_lookahead
+  const int32_t again = c.m.sess[s].y + retries * c.p.retry_iv;
+  const int32_t nt = pick(mine, again, c.qt);
+  const bool far = mine & (r.o_n > 0) & !((nt < r.o_min_t) | ((nt == r.o_min_t) & (c.qk < r.o_min_k)));
+  const uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
+  const uint32_t ffl = (nfl & ~(3u << CL_KIND_SHIFT)) | (QK_RETRY << CL_KIND_SHIFT);
+  wave_sync();
+  *sink(c, mine, &c.m.sess[s].z) = (int32_t)(far ? ffl : nfl);
   const uint64_t far_m = wballot(far);
-  const uint64_t near_m = wballot(mine && !far);
-  const bool kept = c.lane >= n && c.lane < r.q_n;
+  if (far_m != 0) {
+    *sink(c, far, &c.m.due[s]) = nt;
+    c.ovf_dur[far ? (int)s : c.p.n_cap] = c.qd & QD_DUR_MASK;        // (one word more than sessions)
+  }
+  const uint64_t near_m = wballot(mine & !far);
+  const bool kept = (c.lane >= n) & (c.lane < r.q_n);
   r.o_n += __builtin_popcountll(far_m);
   // merge: the timers that stay where they are (kept) and those that moved on inside the registers (near)
-  int pos = kept ? c.lane - n : lane_rank(near_m);
+  const int near_rank = lane_rank(near_m);
+  int pos = kept ? c.lane - n : near_rank;
   for (uint64_t w = near_m; w != 0; w &= w - 1) {
     const int j = (int)__builtin_ctzll(w);
     const int32_t tj = lane_get(nt, j);
     const uint32_t kj = (uint32_t)lane_get((int)c.qk, j);
-    const bool before_j = c.qt < tj || (c.qt == tj && c.qk < kj);     // (kept lanes: their own key)
-    const int kept_before = __builtin_popcountll(wballot(kept && before_j));
-    if (kept && !before_j) pos++;
-    if (c.lane == j) pos += kept_before;
+    const bool before_j = (c.qt < tj) | ((c.qt == tj) & (c.qk < kj));     // (kept lanes: their own key)
+    const int kept_before = __builtin_popcountll(wballot(kept & before_j));
+    pos += kept & !before_j ? 1 : 0;
+    pos += c.lane == j ? kept_before : 0;
   }
   const int alive = r.q_n - __builtin_popcountll(far_m);
-  const bool dead = !(kept || (mine && !far));
-  if (dead) pos = alive + lane_rank(wballot(dead));
+  const bool dead = !(kept | (mine & !far));
+  const int dead_rank = lane_rank(wballot(dead));
+  pos = dead ? alive + dead_rank : pos;
   const int32_t vt = dead ? NEVER : nt;
   const int32_t vd = dead ? 0 : (mine ? (c.qd & QD_DUR_MASK) : c.qd);
   const uint32_t vk = dead ? 0xFFFFFFFFu : c.qk;
@@ -1101,65 +1110,68 @@ __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run
   const int C0 = (a0.x > vt) + (a0.y > vt) + (a0.z > vt) + (a0.w > vt) + (b0.x > vt) + (b0.y > vt) + (b0.z > vt) + (b0.w > vt);
   const int C1 = (a1.x > vt) + (a1.y > vt) + (a1.z > vt) + (a1.w > vt) + (b1.x > vt) + (b1.y > vt) + (b1.z > vt) + (b1.w > vt);
   const int C2 = (a2.x > vt) + (a2.y > vt) + (a2.z > vt) + (a2.w > vt) + (b2.x > vt) + (b2.y > vt) + (b2.z > vt) + (b2.w > vt);
-  const uint32_t k0 = (r0 <= vt && C0 + g <= G) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
-  const uint32_t k1 = (r1 <= vt && C1 + g <= G) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
-  const uint32_t k2 = (r2 <= vt && C2 + g <= G) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
+  const uint32_t k0 = (r0 <= vt) & (C0 + g <= G) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
+  const uint32_t k1 = (r1 <= vt) & (C1 + g <= G) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
+  const uint32_t k2 = (r2 <= vt) & (C2 + g <= G) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
   uint32_t kb = umin(k0, umin(k1, k2));
   if (c.flags() & NBOS_F_STICKY_EXECUTOR) {
     const uint32_t last = hw >> 30;
     const uint32_t kp = last == 1u ? k0 : (last == 2u ? k1 : (last == 3u ? k2 : 0xFFFFFFFFu));
     if (kp != 0xFFFFFFFFu) kb = kp;
   }
-  const bool won = in_run && kb != 0xFFFFFFFFu;
+  const bool won = in_run & (kb != 0xFFFFFFFFu);
   const int lead = (int)(kb & 3u);
-  const int ch = won ? (int)((kb >> 2) & 1023u) : 0;
-  // who binds where: the lowest lane that chose a host marks it
-  if (won) atomicMin(&c.m.mark[ch], c.lane);
+  const int ch = won ? (int)((kb >> 2) & 1023u) : c.lane;
+  // who binds where: the lowest lane that chose a host marks it (the other lanes mark nothing)
+  atomicMin(&c.m.mark[ch], won ? c.lane : MARK_FREE);
   wave_sync();
   const int32_t first = c.m.mark[ch];        // the lowest lane that binds on the host this lane chose
   wave_sync();
-  if (won) c.m.mark[ch] = MARK_FREE;
-  const uint64_t lost = run & wballot(in_run && !won);
-  const uint64_t bad = lost | (run & wballot(in_run && first < c.lane));
+  c.m.mark[ch] = MARK_FREE;
+  const uint64_t lost = run & wballot(in_run & !won);
+  const uint64_t bad = lost | (run & wballot(won & (first < c.lane)));
   const uint64_t below = bad ? ((1ull << __builtin_ctzll(bad)) - 1ull) : ~0ull;
   next_lost = bad != 0 && ((lost >> __builtin_ctzll(bad)) & 1u) != 0;     // the lane that ends the prefix lost its election
   const uint64_t done = run & below;
   if (__builtin_expect(done == 0, 0)) return 0;
   const bool mine = (done >> c.lane) & 1u;
   const int32_t finish = vt + vd;
-  if (mine) {
+  {
     // bind g free GPUs of the chosen host: rewrite its row
     int4 a = lead == 0 ? a0 : (lead == 1 ? a1 : a2);
     int4 b = lead == 0 ? b0 : (lead == 1 ? b1 : b2);
     int need = g;
-    if (need > 0 && a.x <= vt) { a.x = finish; need--; }
-    if (need > 0 && G > 1 && a.y <= vt) { a.y = finish; need--; }
-    if (need > 0 && G > 2 && a.z <= vt) { a.z = finish; need--; }
-    if (need > 0 && G > 3 && a.w <= vt) { a.w = finish; need--; }
-    if (need > 0 && G > 4 && b.x <= vt) { b.x = finish; need--; }
-    if (need > 0 && G > 5 && b.y <= vt) { b.y = finish; need--; }
-    if (need > 0 && G > 6 && b.z <= vt) { b.z = finish; need--; }
-    if (need > 0 && G > 7 && b.w <= vt) { b.w = finish; need--; }
-    c.m.fin[2 * ch] = a; c.m.fin[2 * ch + 1] = b;
+    auto bind = [&](int32_t &f, bool there) {
+      const bool t = there & (need > 0) & (f <= vt);
+      f = t ? finish : f;
+      need -= t ? 1 : 0;
+    };
+    bind(a.x, true);  bind(a.y, G > 1); bind(a.z, G > 2); bind(a.w, G > 3);
+    bind(b.x, G > 4); bind(b.y, G > 5); bind(b.z, G > 6); bind(b.w, G > 7);
+    int4 *const nowhere = (int4 *)(c.m.mail + 4);
+    *(mine ? &c.m.fin[2 * ch] : nowhere) = a;
+    *(mine ? &c.m.fin[2 * ch + 1] : nowhere) = b;
     const uint32_t nhw = (hw & 0x3FFFFFFFu) | ((uint32_t)(lead + 1) << 30);
-    c.m.sess[sid].x = (int)nhw; c.m.sess[sid].y = finish;
+    *sink(c, mine, &c.m.sess[sid].x) = (int32_t)nhw;
+    *sink(c, mine, &c.m.sess[sid].y) = finish;
   }
   // counters over the started lanes: order-free sums go to LDS accumulators (one ds_add per lane)
   const uint32_t n = (uint32_t)__builtin_popcountll(done);
   r.c_started += n; r.c_imm += n; r.h0 += n;
-  r.reused += (uint32_t)__builtin_popcountll(wballot(mine && (hw >> 30) == (uint32_t)lead + 1u));
-  if (mine) {
-    atomicAdd(&c.m.c64[CL_BDUR], (unsigned long long)(uint32_t)vd);
-    atomicAdd(&c.m.c64[CL_BGEXEC], (unsigned long long)(uint32_t)(g * vd));
-    atomicMax(&c.m.c32[CS_BLAZY], (uint32_t)finish);
-  }
+  r.reused += (uint32_t)__builtin_popcountll(wballot(mine & ((hw >> 30) == (uint32_t)lead + 1u)));
+  // (the other lanes add 0 to words of their own)
+  atomicAdd(&c.m.c64[mine ? CL_BDUR : c.lane], (unsigned long long)(mine ? (uint32_t)vd : 0u));
+  atomicAdd(&c.m.c64[mine ? CL_BGEXEC : c.lane], (unsigned long long)(mine ? (uint32_t)(g * vd) : 0u));
+  atomicMax(&c.m.c32[mine ? CS_BLAZY : c.lane], mine ? (uint32_t)finish : 0u);
   // digest: d * P^n + sum over started lanes of code * P^(n - 1 - rank), the sum in three limbs
   const int rank = lane_rank(done);
   const uint64_t code = decision_code(vt, NBOS_D_START, sid, (uint32_t)lead, (uint32_t)ch);
   // the terms are added up by the LDS unit, in the spare slot behind the table of powers
   wave_sync();
-  if (c.lane == 0) c.m.ppow[65] = 0;
-  if (mine) atomicAdd(&c.m.ppow[65], (unsigned long long)(code * c.m.ppow[n - 1u - (uint32_t)rank]));
+  const uint64_t term = code * c.m.ppow[(n - 1u - (uint32_t)rank) & 63u];
+  c.m.ppow[65] = 0;
+  wave_sync();
+  atomicAdd(&c.m.ppow[mine ? 65 : c.lane], (unsigned long long)(mine ? term : 0ull));
   wave_sync();
   const unsigned long long sm = c.m.ppow[65];
   const uint64_t sum = (uint64_t)uni((uint32_t)sm) | ((uint64_t)uni((uint32_t)(sm >> 32)) << 32);
@@ -1167,8 +1179,12 @@ __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run
   const uint64_t pnu = (uint64_t)uni((uint32_t)pn) | ((uint64_t)uni((uint32_t)(pn >> 32)) << 32);
   r.digest = r.digest * pnu + sum;
   if (__builtin_expect(c.dlog != nullptr, 0)) {
-    const int64_t at = (int64_t)r.n_dec + rank;
-    if (mine && at < c.p.dlog_stride) c.dlog[at] = code;
+    int64_t at = (int64_t)r.n_dec;
+    for (uint64_t w = done; w != 0; w &= w - 1, at++) {
+      const int j = (int)__builtin_ctzll(w);
+      const uint32_t lo = (uint32_t)lane_get((int)(uint32_t)code, j), hi = (uint32_t)lane_get((int)(uint32_t)(code >> 32), j);
+      if (at < c.p.dlog_stride) c.dlog[at] = (uint64_t)lo | ((uint64_t)hi << 32);
+    }
   }
   r.n_dec += n;
   return done;
@@ -1190,7 +1206,6 @@ __device__ __forceinline__ Lds lds_carve(const KParams &p, unsigned char *q) {
   m.warm = (int32_t *)q;            q += p.warm_n > 0 ? (size_t)p.HP * 16 : 0;
   // 16-byte aligned: the refill reads four times at once
   m.due = (int32_t *)q;             q += (size_t)((p.n_cap + 3) / 4 * 4) * 4;
-  m.stage = (int32_t *)q;           q += WAVE * 4;
   m.sess = (SessRec *)q;
   return m;
 }
@@ -1273,9 +1288,9 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_lds_kernel(KPara
   Ctx<F> c{p, m, lane, caplim / 1000, p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr,
         NEVER, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0};
   c.n_sess = n_sess;
-  c.ovf_dur = p.ovf_dur + (int64_t)rep * p.n_cap;
+  c.ovf_dur = p.ovf_dur + (int64_t)rep * (p.n_cap + 1);
   c.nw = (int)(blockDim.x / WAVE);
-  c.wid = (int)(threadIdx.x / WAVE);
+  c.wid = uni((int)(threadIdx.x / WAVE));
   c.dyn = dynamic_limit_matters(p, c.flags(), c.slim);
   c.n_on = p.H0;
   Regs r;
@@ -1303,13 +1318,15 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_lds_kernel(KPara
   // S1: stream the events, one per lane per tile, next tile in flight
   int64_t base = ev_lo;                     // first event of the tile held in (nt, nd, ns)
   int32_t vt = 0, vd = 0, vs = 0, nt = 0, nd = 0, ns = 0;
-  if (base + lane < ev_hi) { nt = p.ev_time[base + lane]; nd = p.ev_dur[base + lane]; ns = p.ev_sk[base + lane]; }
+  if (base < ev_hi) {
+    const int64_t at = min(base + lane, ev_hi - 1);
+    nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
+  }
 
   bool final = false;
   while (r.status == NBOS_OK) {
     SessRec rec = {0, 0, 0};                // prefetched session record of this lane's event
-    bool fast = false;                      // this lane's event is a cell of an idle placed session
-    uint64_t todo = 0;
+    uint64_t todo = 0, fastmask = 0;        // events to look at; cells of idle placed sessions
     uint32_t sid = 0;
     int32_t last_t = 0;                     // time of the tile's last event
     if (base < ev_hi) {
@@ -1317,42 +1334,45 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_lds_kernel(KPara
       const int64_t cur = base;
       last_t = lane_get(vt, (int)(ev_hi - cur < WAVE ? ev_hi - cur - 1 : WAVE - 1));
       base += WAVE;
-      if (base + lane < ev_hi) { nt = p.ev_time[base + lane]; nd = p.ev_dur[base + lane]; ns = p.ev_sk[base + lane]; }
+      if (base < ev_hi) {
+        const int64_t at = min(base + lane, ev_hi - 1);
+        nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
+      }
       const bool valid = cur + lane < ev_hi;
       const bool is_last = cur + lane == ev_hi - 1;
-      sid = valid ? ((uint32_t)vs & 0xFFFFFFu) : 0u;
+      sid = (uint32_t)vs & 0xFFFFFFu;       // (lanes beyond the last event hold that one's)
       const bool is_cell = ((uint32_t)vs >> 24) == NBOS_EV_CELL;
       c.vsid = valid ? sid : 0xFFFFFFFFu;
       wave_sync();
-      if (valid) rec = m.sess[sid];
+      rec = m.sess[sid];
       // Cells of sessions in a final state (rejected / ended) and cells that arrive while the
       // session's running cell lasts beyond them change nothing: count them, skip them. Neither
       // condition can be undone before the event's time. The last event of the trace is never
       // skipped, so timers due before it still run first.
       const uint32_t st = (uint32_t)rec.z & 7u;
-      const bool dead = st == SS_REJECTED || st == SS_ENDED;
-      const bool running = st == SS_PLACED && rec.y > vt;
-      const bool skip = valid && !is_last && (dead || (is_cell && running));
-      r.c_total += (uint32_t)__builtin_popcountll(wballot(valid && is_cell));
-      r.c_unplaced += (uint32_t)__builtin_popcountll(wballot(skip && is_cell && dead));
-      r.c_busy += (uint32_t)__builtin_popcountll(wballot(skip && is_cell && !dead));
-      fast = valid && is_cell && st == SS_PLACED && !running && !((uint32_t)rec.z & SF_ENDING);
-      todo = wballot(valid && !skip);
+      const bool dead = (st == SS_REJECTED) | (st == SS_ENDED);
+      const bool running = (st == SS_PLACED) & (rec.y > vt);
+      const bool skip = valid & !is_last & (dead | (is_cell & running));
+      r.c_total += (uint32_t)__builtin_popcountll(wballot(valid & is_cell));
+      r.c_unplaced += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & dead));
+      r.c_busy += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & !dead));
+      fastmask = wballot(valid & is_cell & (st == SS_PLACED) & !running & (((uint32_t)rec.z & SF_ENDING) == 0));
+      todo = wballot(valid & !skip);
       r.dirty = 0;
       if (batching) {
         // a lane whose session may also belong to an earlier lane of the tile keeps out of the rounds
         const uint32_t b = sid & dup_mask;
-        if (valid) atomicMin(&m.mark[b], lane);
+        atomicMin(&m.mark[b], lane);        // (lanes beyond the last event come after it: they change nothing)
         wave_sync();
-        const bool dup = valid && m.mark[b] < lane;
+        const bool dup = valid & (m.mark[b] < lane);
         wave_sync();
-        if (valid) m.mark[b] = MARK_FREE;
+        m.mark[b] = MARK_FREE;
         // the buckets are few (a lane in eight shares one with an earlier lane by chance): keep only the
         // lanes that really have their session in an earlier lane
         for (uint64_t w = wballot(dup); w != 0; w &= w - 1) {
           const int j = (int)__builtin_ctzll(w);
           const uint32_t sj = (uint32_t)lane_get((int)sid, j);
-          if (wballot(valid && sid == sj && lane < j) != 0) r.dirty |= 1ull << j;
+          if (wballot((sid == sj) & (lane < j)) != 0) r.dirty |= 1ull << j;
         }
       }
       if (ev_hi - cur <= WAVE) {
@@ -1365,7 +1385,6 @@ __global__ void __launch_bounds__(MAX_WAVES * WAVE) nbos_replay_lds_kernel(KPara
       const int32_t bl = (int32_t)uni(m.c32[CS_BLAZY]);       // finish times bound by the rounds
       r.lazy_max = r.lazy_max > bl ? r.lazy_max : bl;
     }
-    const uint64_t fastmask = wballot(fast);
     PROF(PC_TILE, 1);
     const uint64_t queued_lanes = wballot(((uint32_t)rec.z & 7u) == SS_QUEUED);
     bool hz_known = false;

@@ -1224,7 +1224,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
   c.vsid = 0xFFFFFFFFu;
   c.fu = 0;
   c.dyn = dynamic_limit_matters(p, c.flags(), c.slim);
-  c.cl_cur = p.cl_cursor + (int64_t)rep * p.n_cap;
+  c.cl_cur = p.cl_cursor + (int64_t)rep * (p.n_cap + 1);
   c.cl_dur = p.ev_dur + ev_lo; c.cl_sk = p.ev_sk + ev_lo; c.cl_chain = p.cl_chain + ev_lo;
   c.qx = 0; c.qnx = -1; c.qnth = 0;
   Regs r;
@@ -1265,8 +1265,8 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
           const int32_t e = load ? c.qd : 0;                   // (the lanes with nothing to load read event 0)
           const int2 ch = c.cl_chain[e];
           const int32_t x = c.cl_dur[e] | (int32_t)(((uint32_t)c.cl_sk[e] >> 24) << 28) | CLX_LOADED;
-          c.qx = load ? x : c.qx;
-          c.qnx = load ? ch.x : c.qnx; c.qnth = load ? ch.y : c.qnth;
+          c.qx = pick(load, x, c.qx);
+          c.qnx = pick(load, ch.x, c.qnx); c.qnth = pick(load, ch.y, c.qnth);
         }
         const int32_t now = r.q_head_t;
         const uint32_t key = (uint32_t)lane_get((int)c.qk, 0);

@@ -458,9 +458,9 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     if (policy == NBOS_F_MIGRATE && !force_generic) set_reg_closed_kernel<NBOS_F_MIGRATE | NBOS_F_CLOSED_LOOP>(h, nj);
     else set_reg_closed_kernel<kRuntimeClosed>(h, nj);
   } else if (closed_loop) {
-    // 12 bytes of record and 4 of timer per session; 64 staged sessions
+    // 12 bytes of record and 4 of timer per session
     h->lds_bytes = LDS_HEAD + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
-                   (n_cap + 3) / 4 * 16 + WAVE * 4;
+                   (n_cap + 3) / 4 * 16;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     // instances for the common flag sets, as for the other kernels
     const uint32_t policy = cfg->flags & kPolicyFlags;
@@ -475,9 +475,9 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     const int32_t rc = choose_reg_kernel(h, maxlds);
     if (rc != NBOS_OK) return rc;
   } else {
-    // 12 bytes of record and 4 of timer per session; 64 staged sessions
+    // 12 bytes of record and 4 of timer per session
     h->lds_bytes = LDS_HEAD + 66 * 8 + ldsk::MAIL_WORDS * 4 + (size_t)HP * (32 + 12 + (warm_pool ? 16 : 0)) + n_cap * 12 +
-                   (n_cap + 3) / 4 * 16 + WAVE * 4;
+                   (n_cap + 3) / 4 * 16;
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     // same idea as for the register kernel; its batches are small (the LDS footprint allows few
     // workgroups per compute unit), so the instance compiled for the flag set is used whenever
@@ -529,10 +529,10 @@ int32_t allocate_buffers(nbos_replay *h, const Shape &sh) {
   if (hipMalloc(&h->d_bill, sizeof(nbos_bill) * n) != hipSuccess) return NBOS_E_NOMEM;
   // durations of queued cells whose timers wait outside the sorted registers (open-loop replay kernels)
   const bool queued_durations = !(cfg->flags & (NBOS_F_BATCH_MODE | NBOS_F_CLOSED_LOOP));
-  if (queued_durations && hipMalloc(&h->d_ovf, sizeof(int32_t) * n * (size_t)sh.n_cap) != hipSuccess) return NBOS_E_NOMEM;
+  if (queued_durations && hipMalloc(&h->d_ovf, sizeof(int32_t) * n * ((size_t)sh.n_cap + 1)) != hipSuccess) return NBOS_E_NOMEM;
   if (cfg->flags & NBOS_F_CLOSED_LOOP) {
-    // one allocation: chain[total_ev] (two words each), cursor[n_replays][n_cap]; the chains are linked here
-    const size_t words = 2 * (size_t)sh.total_ev + n * (size_t)sh.n_cap;
+    // one allocation: chain[total_ev] (two words each), cursor[n_replays][n_cap + 1]; the chains are linked here
+    const size_t words = 2 * (size_t)sh.total_ev + n * ((size_t)sh.n_cap + 1);
     if (hipMalloc(&h->d_chain, sizeof(int32_t) * (words > 0 ? words : 1)) != hipSuccess) return NBOS_E_NOMEM;
     const size_t chain_lds = (size_t)sh.n_cap * 12;
     HIP_TRY(hipFuncSetAttribute((const void *)ldsk::nbos_closed_chain_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
