@@ -145,6 +145,15 @@ __device__ __forceinline__ int32_t pick(bool c, int32_t a, int32_t b) {
   return (a & m) | (b & ~m);
 }
 
+// The value again, in a way that keeps the compiler from working out what depends on it before the loop: a
+// comparison with a lane's number is one instruction, its result kept over the whole kernel is a pair of
+// scalar registers, and those are spilled to vector lanes (two reads for each use).
+__device__ __forceinline__ int fresh_lane(int lane) { asm volatile("" : "+v"(lane)); return lane; }
+__device__ __forceinline__ int fresh(int v) { asm volatile("" : "+s"(v)); return v; }
+
+// the median of three (one v_med3_i32)
+__device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }
+
 // wave-wide ballot straight from the predicate (no int round trip)
 __device__ __forceinline__ uint64_t wballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
@@ -194,19 +203,23 @@ constexpr size_t LDS_LEAST = 512;              // what the adds below may touch 
 
 template <class L>
 __device__ __forceinline__ void c32_add(L &m, int lane, int idx, uint32_t v) {
+  lane = fresh_lane(lane);
   atomicAdd(&m.c32[(idx + lane) & (WAVE - 1)], lane == 0 ? v : 0u);
 }
 template <class L>
 __device__ __forceinline__ void c32_max(L &m, int lane, int idx, uint32_t v) {
+  lane = fresh_lane(lane);
   atomicMax(&m.c32[(idx + lane) & (WAVE - 1)], lane == 0 ? v : 0u);
 }
 template <class L>
 __device__ __forceinline__ void c64_add(L &m, int lane, int idx, int64_t v) {
+  lane = fresh_lane(lane);
   atomicAdd(&m.c64[(idx + lane) & (WAVE - 1)], lane == 0 ? (unsigned long long)v : 0ull);
 }
 template <class L>
 __device__ __forceinline__ void hist_add(L &m, int lane, int32_t delay) {        // delay > 0
   const int b = 32 - __builtin_clz((uint32_t)delay);
+  lane = fresh_lane(lane);
   atomicAdd(&m.hist[((b > 31 ? 31 : b) + lane) & (WAVE - 1)], lane == 0 ? 1u : 0u);
 }
 

@@ -93,9 +93,6 @@ __device__ __forceinline__ void decide(C &c, State &r, int32_t now, uint32_t out
   r.n_dec++;
 }
 
-// the median of three (one v_med3_i32)
-__device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }
-
 // smallest key at time T: the host that takes the next job, if that fits (see fits)
 template <int NCH>
 __device__ __forceinline__ uint32_t best_host(Ctx<NCH> &c, int32_t T) {

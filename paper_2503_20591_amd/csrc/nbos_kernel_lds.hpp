@@ -4,9 +4,13 @@
 // share of every scan over all hosts (see "helper waves" below).
 //
 // LDS per replay
-//   fin[h][8]    per-GPU "busy until" times, one 32-byte row per host. A GPU is committed at time t
-//                iff fin > t; binding g GPUs for a cell (paper Section 3.3) = writing its finish time
-//                into g free GPUs of the row. Completions need no timer: every timer due at or before
+//   fin[h][8]    per-GPU "busy until" times, one 32-byte row per host, sorted ascending; entries beyond G hold
+//                NEVER (counts are of 8 GPUs: the same number too high on every host). A GPU is committed at
+//                time t iff fin > t, the host has g idle GPUs from fin[g-1] on (if nothing new is bound);
+//                binding g GPUs for a cell (paper Section 3.3) = the g smallest entries leave and g copies
+//                of its finish time come in, new[k] = median(old[k], finish, old[k + g]). (With unsorted rows
+//                every look at "from when on" took a sorting network: 768 hosts 178 ms, with sorted rows
+//                170 ms.) Completions need no timer: every timer due at or before
 //                an item runs before that item and a completion only lowers C, so "released once
 //                the clock has passed fin" is exact.
 //   ready_at[h]  0 for initial hosts, NEVER while off, boot completion time while provisioning
@@ -268,26 +272,21 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
 }
 
 // ---- host helpers -------------------------------------------------------------------------------
-// committed GPUs of host h at time `now` (GPUs beyond G keep fin = 0 and never count)
+// committed GPUs of host h at time `now` (those beyond G, held for ever, included)
 template <uint32_t F>
 __device__ __forceinline__ int committed(const Ctx<F> &c, int h, int32_t now) {
   const int4 a = c.m.fin[2 * h], b = c.m.fin[2 * h + 1];
   return (a.x > now) + (a.y > now) + (a.z > now) + (a.w > now) + (b.x > now) + (b.y > now) + (b.z > now) + (b.w > now);
 }
 
-// free GPUs (bits of the low byte) below GPU k
-__device__ __forceinline__ int gpu_rank(uint32_t free_mask, int k) { return __builtin_popcount(free_mask & ((1u << k) - 1u)); }
-
-// bind g free GPUs of host h until `finish` (lane = GPU; every eighth lane does the same)
+// bind g free GPUs of host h until `finish` (lane = entry of the row; every eighth lane does the same)
 template <uint32_t F>
-__device__ __forceinline__ void bind_gpus(Ctx<F> &c, int h, int g, int32_t now, int32_t finish) {
+__device__ __forceinline__ void bind_gpus(Ctx<F> &c, int h, int g, int32_t finish) {
   wave_sync();
   int32_t *row = (int32_t *)&c.m.fin[2 * h];
   const int k = c.lane & 7;
-  const int32_t f = row[k];
-  const bool fr = (k < c.p.G) & (f <= now);
-  const int rank = gpu_rank((uint32_t)wballot(fr), k);
-  row[k] = fr & (rank < g) ? finish : f;
+  const int32_t own = row[k], up = row[(k + g) & 7];
+  row[k] = med3(own, finish, k + g < NGPU ? up : NEVER);
 }
 
 // ---- helper waves ------------------------------------------------------------------------------------
@@ -367,7 +366,7 @@ __device__ __forceinline__ uint32_t best_host_part(const Ctx<F> &c, int32_t now,
     // is still open whether any host has g idle GPUs)
     if (wballot(capped) == 0 && idle_seen) continue;
     const int C = committed(c, h, now);
-    const bool roomy = (ra <= now) & (C + g <= c.p.G);
+    const bool roomy = (ra <= now) & (C + g <= NGPU);
     idle_seen = idle_seen | (wballot(roomy) != 0);
     const uint32_t key = ((uint32_t)C << 22) | ((uint32_t)S << 10) | (uint32_t)h;
     best = umin(best, capped & roomy ? key : 0xFFFFFFFFu);
@@ -401,41 +400,19 @@ __device__ __forceinline__ int32_t min_subscription(const Ctx<F> &c) {
   return (int32_t)wave_min(best);
 }
 
-__device__ __forceinline__ void order2(int32_t &a, int32_t &b) {
-  const int32_t lo = min(a, b), hi = max(a, b);
-  a = lo; b = hi;
-}
-
-// the busy-until times of one host's GPUs in ascending order (GPUs beyond G count as never free):
-// the 19-comparator network for 8 inputs; returns the g-th smallest
-__device__ __forceinline__ int32_t kth_free_time(const int4 a, const int4 b, int G, int g) {
-  int32_t v0 = a.x, v1 = G > 1 ? a.y : NEVER, v2 = G > 2 ? a.z : NEVER, v3 = G > 3 ? a.w : NEVER;
-  int32_t v4 = G > 4 ? b.x : NEVER, v5 = G > 5 ? b.y : NEVER, v6 = G > 6 ? b.z : NEVER, v7 = G > 7 ? b.w : NEVER;
-  order2(v0, v1); order2(v2, v3); order2(v4, v5); order2(v6, v7);
-  order2(v0, v2); order2(v1, v3); order2(v4, v6); order2(v5, v7);
-  order2(v1, v2); order2(v5, v6);
-  order2(v0, v4); order2(v1, v5); order2(v2, v6); order2(v3, v7);
-  order2(v2, v4); order2(v3, v5);
-  order2(v1, v2); order2(v3, v4); order2(v5, v6);
-  v6 = g & 1 ? v6 : v7;   v4 = g & 1 ? v4 : v5;   v2 = g & 1 ? v2 : v3;   v0 = g & 1 ? v0 : v1;      // a choice by the bits of g - 1
-  v4 = (g - 1) & 2 ? v6 : v4;   v0 = (g - 1) & 2 ? v2 : v0;
-  return (g - 1) & 4 ? v4 : v0;
-}
-
 // Earliest time at which some host that is on could have g idle GPUs if nothing new were committed:
 // min over hosts of max(ready_at, g-th smallest busy-until time of the host's GPUs). Later commits
 // only push it back, so no election or migration for a request of g GPUs can succeed before it, as
 // long as no host is added (boot_host lowers the stored bound). `capped`: the same minimum over the
 // hosts that hold at most `room` subscribed GPUs, i.e. that pass the subscription cap for the request
 // (Section 3.4.1): no migration target before it, as long as no host is added and no host's
-// subscription shrinks (cap_bound_host_freed lowers the stored bound then). One lane sorts one host's row.
+// subscription shrinks (cap_bound_host_freed lowers the stored bound then).
 template <uint32_t F>
 __device__ __forceinline__ int32_t earliest_idle_part(const Ctx<F> &c, int g, int32_t room, int32_t &capped) {
-  const int G = c.p.G;
   int32_t best = NEVER, best_cap = NEVER;
   for (int h0 = c.wid * WAVE; h0 < c.p.HP; h0 += WAVE * c.nw) {
     const int h = h0 + c.lane;
-    int32_t y = kth_free_time(c.m.fin[2 * h], c.m.fin[2 * h + 1], G, g);
+    int32_t y = ((const int32_t *)c.m.fin)[NGPU * h + g - 1];
     const int32_t ra = c.m.ready_at[h];
     y = y > ra ? y : ra;
     best = best < y ? best : y;
@@ -469,7 +446,7 @@ __device__ __forceinline__ void cap_bound_host_freed(Ctx<F> &c, int h, int32_t s
   if (wballot((c.lane < NGPU) & (c.fc > now)) == 0) return;  // every bound lies in the past already: as good as none
   wave_sync();
   const int g = (c.lane & 7) + 1;
-  int32_t y = kth_free_time(c.m.fin[2 * h], c.m.fin[2 * h + 1], c.p.G, g);
+  int32_t y = ((const int32_t *)c.m.fin)[NGPU * h + g - 1];
   const int32_t ra = c.m.ready_at[h];
   y = y > ra ? y : ra;
   c.fc = (c.lane < NGPU) & (s_new + g <= c.slim) & (y < c.fc) ? y : c.fc;
@@ -491,7 +468,8 @@ __device__ __forceinline__ void cl_schedule(Ctx<F> &c, Regs &r, uint32_t s, int3
 // host h: S | replicas << 16 changes by `by` (one ds_add, nothing to wait for; the other lanes add 0 to neighbours)
 template <uint32_t F>
 __device__ __forceinline__ void subscribe(const Ctx<F> &c, int h, uint32_t by) {
-  atomicAdd(&c.m.hsn[h ^ c.lane], c.lane == 0 ? by : 0u);
+  const int lane = fresh_lane(c.lane);
+  atomicAdd(&c.m.hsn[h ^ lane], lane == 0 ? by : 0u);
 }
 
 // Placement candidates among this wave's chunks of hosts (Sections 3.2.1, 3.4.1): ready and under the cap;
@@ -506,7 +484,7 @@ __device__ __forceinline__ void place_part(const Ctx<F> &c, int32_t now, int32_t
   for (int j = 0; j < MAXCH; j++) {
     keys[j] = 0xFFFFFFFFu;
     const int h0 = (j * c.nw + c.wid) * WAVE, h = h0 + c.lane;
-    if (h0 < c.p.HP) {
+    if (h0 < fresh(c.p.HP)) {
       const int S = (int)(c.m.hsn[h] & 0xFFFFu);
       const uint32_t key = ((uint32_t)committed(c, h, now) << 22) | ((uint32_t)S << 10) | (uint32_t)h;
       keys[j] = (c.m.ready_at[h] <= now) & (S <= room) ? key : 0xFFFFFFFFu;
@@ -596,8 +574,9 @@ template <uint32_t F>
 __device__ __forceinline__ void end_session(Ctx<F> &c, Regs &r, uint32_t s, uint32_t hw, uint32_t fl, int32_t now) {
   const int g = (int)((fl >> 3) & 7u) + 1;
   const uint32_t sub = (uint32_t)g | (1u << 16);
-  const int hl = (int)((hw >> ((10 * c.lane) & 31)) & 1023u);   // three distinct hosts, one lane each
-  atomicSub(&c.m.hsn[c.lane < 3 ? hl : c.lane], c.lane < 3 ? sub : 0u);
+  const int lane = fresh_lane(c.lane);
+  const int hl = (int)((hw >> ((10 * lane) & 31)) & 1023u);     // three distinct hosts, one lane each
+  atomicSub(&c.m.hsn[lane < 3 ? hl : lane], lane < 3 ? sub : 0u);
   r.min_s = -1;
   if (!((c.flags() & NBOS_F_DYNAMIC_SR) && c.dyn)) {
     wave_sync();
@@ -658,7 +637,6 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
                                            int32_t t_submit, int32_t dur) {
   PROF_SUB_BEGIN();
   wave_sync();
-  const int G = c.p.G;
   const int g = (int)((fl >> 3) & 7u) + 1;
   const uint32_t h0 = hw & 1023u, h1 = (hw >> 10) & 1023u, h2 = (hw >> 20) & 1023u;
   // Known in advance that no host has g idle GPUs yet? Then neither election nor migration can work.
@@ -668,19 +646,18 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
   rr = rr > 2 ? 2 : rr;
   const int k = c.lane & 7;
   const int hr = (int)((hw >> (10 * rr)) & 1023u);
-  const bool act = c.lane < 24;
   int32_t *row = (int32_t *)&c.m.fin[2 * hr];
-  const int32_t f = row[k];
+  const int32_t f = row[k], up = row[(k + g) & 7];
   const int32_t ra = c.m.ready_at[hr];
-  const uint64_t busy = wballot(act & (f > now));
+  const uint64_t busy = wballot(f > now);
   const uint64_t rdy = wballot(ra <= now);
   const int C0 = __builtin_popcount((uint32_t)busy & 0xFFu), C1 = __builtin_popcount((uint32_t)(busy >> 8) & 0xFFu),
             C2 = __builtin_popcount((uint32_t)(busy >> 16) & 0xFFu);
   const int ok0 = (int)(rdy & 1u), ok1 = (int)((rdy >> 8) & 1u), ok2 = (int)((rdy >> 16) & 1u);
   if (!hopeless) {
-    const uint32_t k0 = (ok0 && C0 + g <= G) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
-    const uint32_t k1 = (ok1 && C1 + g <= G) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
-    const uint32_t k2 = (ok2 && C2 + g <= G) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
+    const uint32_t k0 = (ok0 && C0 + g <= NGPU) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
+    const uint32_t k1 = (ok1 && C1 + g <= NGPU) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
+    const uint32_t k2 = (ok2 && C2 + g <= NGPU) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
     uint32_t kb = umin(k0, umin(k1, k2));
     if (c.flags() & NBOS_F_STICKY_EXECUTOR) {
       // variant: the replica that ran the previous cell leads again if its host can bind
@@ -690,10 +667,9 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
     }
     if (kb != 0xFFFFFFFFu) {
       const int lead = (int)(kb & 3u), hl = (int)((kb >> 2) & 1023u);
-      // (every lane writes the GPU it has read: the lead's free ones get the new time; lanes 24 up do what 16 to 23 do)
-      const bool fr = (k < G) & (f <= now);
-      const int rank = gpu_rank((uint32_t)(wballot(fr) >> (8 * lead)), k);
-      row[k] = (rr == lead) & fr & (rank < g) ? now + dur : f;
+      // (every lane writes the entry it has read, the lead's row as it is now; lanes 24 up do what 16 to 23 do)
+      const int32_t bound = med3(f, now + dur, k + g < NGPU ? up : NEVER);
+      row[k] = rr == lead ? bound : f;
       if (now == t_submit) r.c_imm++;
       start_cell(c, r, s, hw, fl, lead, hl, now, now, t_submit, dur, NBOS_D_START);
       return (Ctx<F>::closed || (fl & SF_ENDING)) ? -1 : NEVER;      // (those push a timer of their own)
@@ -772,7 +748,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
       wave_sync();
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
       PROF_SUB(PC_A_VICTIM);
-      bind_gpus(c, dst, g, now, start + dur);
+      bind_gpus(c, dst, g, start + dur);
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, outcome);
       PROF_SUB(PC_A_BIND);
@@ -785,7 +761,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
       const int h = boot_host(c, r, now, moved);
       c32_max(c.m, c.lane, CS_PEAK, (uint32_t)c.n_on);
-      bind_gpus(c, h, g, now, start + dur);
+      bind_gpus(c, h, g, start + dur);
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, h, now, start, t_submit, dur, NBOS_D_SCALE_CELL);
     }
@@ -861,7 +837,7 @@ __device__ __forceinline__ void tick_part(const Ctx<F> &c, int32_t now, int &A, 
     const bool ready = c.m.ready_at[h] <= now;
     A += __builtin_popcountll(wballot(ready));
     Z += __builtin_popcountll(wballot(ready & ((c.m.hsn[h] >> 16) == 0)));
-    if (autoscale) busy += (uint32_t)committed(c, h, now);
+    if (autoscale) busy += (uint32_t)(committed(c, h, now) - (NGPU - c.p.G));
   }
   sum_c = autoscale ? (uint32_t)wave_sum(busy) : 0u;
 }
@@ -968,7 +944,6 @@ __device__ __forceinline__ void on_session_end(Ctx<F> &c, Regs &r, uint32_t s, u
 template <uint32_t F>
 __device__ __forceinline__ void retry_lookahead(Ctx<F> &c, const Regs &r) {
   wave_sync();
-  const int G = c.p.G;
   const bool cand = (c.lane < r.q_n) & ((c.qk >> 16) == QK_RETRY) & (((uint32_t)c.qd & QD_LOOKED) == 0);
   const SessRec rec = c.m.sess[cand ? c.qk & 0xFFFFu : 0u];
   const uint32_t hw = (uint32_t)rec.x, fl = (uint32_t)rec.z;
@@ -976,8 +951,8 @@ __device__ __forceinline__ void retry_lookahead(Ctx<F> &c, const Regs &r) {
   const int32_t vt = c.qt;
   const uint32_t h0 = hw & 1023u, h1 = (hw >> 10) & 1023u, h2 = (hw >> 20) & 1023u;
   const int C0 = committed(c, (int)h0, vt), C1 = committed(c, (int)h1, vt), C2 = committed(c, (int)h2, vt);
-  const bool can = ((c.m.ready_at[h0] <= vt) & (C0 + g <= G)) | ((c.m.ready_at[h1] <= vt) & (C1 + g <= G)) |
-                   ((c.m.ready_at[h2] <= vt) & (C2 + g <= G));
+  const bool can = ((c.m.ready_at[h0] <= vt) & (C0 + g <= NGPU)) | ((c.m.ready_at[h1] <= vt) & (C1 + g <= NGPU)) |
+                   ((c.m.ready_at[h2] <= vt) & (C2 + g <= NGPU));
   const bool more = (int)((fl >> 8) & 15u) < c.p.max_retries;        // not the retry that gives the cell up
   const uint32_t efail = QD_EFAIL | ((uint32_t)(g - 1) << QD_G_SHIFT);
   const uint32_t d = (uint32_t)c.qd | QD_LOOKED | (!can & more ? efail : 0u);
@@ -1097,7 +1072,6 @@ template <uint32_t F>
 __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run, int32_t vt, int32_t vd, uint32_t sid,
                                                 const SessRec &rec, bool &next_lost) {
   wave_sync();
-  const int G = c.p.G;
   const bool in_run = (run >> c.lane) & 1u;
   const uint32_t hw = (uint32_t)rec.x, fl = (uint32_t)rec.z;
   const int g = (int)((fl >> 3) & 7u) + 1;
@@ -1110,9 +1084,9 @@ __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run
   const int C0 = (a0.x > vt) + (a0.y > vt) + (a0.z > vt) + (a0.w > vt) + (b0.x > vt) + (b0.y > vt) + (b0.z > vt) + (b0.w > vt);
   const int C1 = (a1.x > vt) + (a1.y > vt) + (a1.z > vt) + (a1.w > vt) + (b1.x > vt) + (b1.y > vt) + (b1.z > vt) + (b1.w > vt);
   const int C2 = (a2.x > vt) + (a2.y > vt) + (a2.z > vt) + (a2.w > vt) + (b2.x > vt) + (b2.y > vt) + (b2.z > vt) + (b2.w > vt);
-  const uint32_t k0 = (r0 <= vt) & (C0 + g <= G) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
-  const uint32_t k1 = (r1 <= vt) & (C1 + g <= G) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
-  const uint32_t k2 = (r2 <= vt) & (C2 + g <= G) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
+  const uint32_t k0 = (r0 <= vt) & (C0 + g <= NGPU) ? (((uint32_t)C0 << 12) | (h0 << 2) | 0u) : 0xFFFFFFFFu;
+  const uint32_t k1 = (r1 <= vt) & (C1 + g <= NGPU) ? (((uint32_t)C1 << 12) | (h1 << 2) | 1u) : 0xFFFFFFFFu;
+  const uint32_t k2 = (r2 <= vt) & (C2 + g <= NGPU) ? (((uint32_t)C2 << 12) | (h2 << 2) | 2u) : 0xFFFFFFFFu;
   uint32_t kb = umin(k0, umin(k1, k2));
   if (c.flags() & NBOS_F_STICKY_EXECUTOR) {
     const uint32_t last = hw >> 30;
@@ -1140,14 +1114,17 @@ __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run
     // bind g free GPUs of the chosen host: rewrite its row
     int4 a = lead == 0 ? a0 : (lead == 1 ? a1 : a2);
     int4 b = lead == 0 ? b0 : (lead == 1 ? b1 : b2);
-    int need = g;
-    auto bind = [&](int32_t &f, bool there) {
-      const bool t = there & (need > 0) & (f <= vt);
-      f = t ? finish : f;
-      need -= t ? 1 : 0;
-    };
-    bind(a.x, true);  bind(a.y, G > 1); bind(a.z, G > 2); bind(a.w, G > 3);
-    bind(b.x, G > 4); bind(b.y, G > 5); bind(b.z, G > 6); bind(b.w, G > 7);
+    // the row's entries g places up (g differs from lane to lane: one, two, four, eight places by the bits of g)
+    const bool g1 = (g & 1) != 0, g2 = (g & 2) != 0, g4 = (g & 4) != 0, g8 = g == 8;
+    int32_t u0 = g1 ? a.y : a.x, u1 = g1 ? a.z : a.y, u2 = g1 ? a.w : a.z, u3 = g1 ? b.x : a.w;
+    int32_t u4 = g1 ? b.y : b.x, u5 = g1 ? b.z : b.y, u6 = g1 ? b.w : b.z, u7 = g1 ? NEVER : b.w;
+    u0 = g2 ? u2 : u0; u1 = g2 ? u3 : u1; u2 = g2 ? u4 : u2; u3 = g2 ? u5 : u3;
+    u4 = g2 ? u6 : u4; u5 = g2 ? u7 : u5; u6 = g2 ? NEVER : u6; u7 = g2 ? NEVER : u7;
+    u0 = g4 ? u4 : u0; u1 = g4 ? u5 : u1; u2 = g4 ? u6 : u2; u3 = g4 ? u7 : u3;
+    u4 = g4 ? NEVER : u4; u5 = g4 ? NEVER : u5; u6 = g4 ? NEVER : u6; u7 = g4 ? NEVER : u7;
+    const int32_t f8 = g8 ? NEVER : 0;            // (eight places up is nothing)
+    a = make_int4(med3(a.x, finish, max(u0, f8)), med3(a.y, finish, max(u1, f8)), med3(a.z, finish, max(u2, f8)), med3(a.w, finish, max(u3, f8)));
+    b = make_int4(med3(b.x, finish, max(u4, f8)), med3(b.y, finish, max(u5, f8)), med3(b.z, finish, max(u6, f8)), med3(b.w, finish, max(u7, f8)));
     int4 *const nowhere = (int4 *)(c.m.mail + 4);
     *(mine ? &c.m.fin[2 * ch] : nowhere) = a;
     *(mine ? &c.m.fin[2 * ch + 1] : nowhere) = b;
@@ -1222,7 +1199,7 @@ __device__ __forceinline__ void lds_init(const KParams &p, const Lds &m, int s_l
     unsigned long long pw = 1;
     for (int i = 0; i <= 64; i++) { m.ppow[i] = pw; pw *= DIGEST_PRIME; }
   }
-  for (int i = tid; i < 2 * p.HP; i += nt) m.fin[i] = make_int4(0, 0, 0, 0);
+  for (int i = tid; i < NGPU * p.HP; i += nt) ((int32_t *)m.fin)[i] = (i & 7) < p.G ? 0 : NEVER;
   for (int h = tid; h < p.HP; h += nt) {
     m.ready_at[h] = h < p.H0 ? 0 : NEVER;
     m.mark[h] = MARK_FREE;

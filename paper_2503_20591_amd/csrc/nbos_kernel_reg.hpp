@@ -4,7 +4,8 @@
 //
 // GPUs:   fin[j], j < NJ = ceil(hosts_max / 8). Lane L = (hl = L >> 3, k = L & 7) holds in fin[j] the
 //         "busy until" time of GPU k of host 8 j + hl. A GPU is committed at time t iff fin > t, so
-//         the ballot of (fin[j] > now) is a 64-bit word with one byte of busy-GPU bits per host.
+//         the ballot of (fin[j] > now) is a 64-bit word with one byte of busy-GPU bits per host. GPUs beyond
+//         G are held for ever: counts are of 8, the same number too high on every host.
 //         Binding g GPUs for a cell (paper Section 3.3) = writing its finish time into the g lowest
 //         free GPUs of the host byte (ballot + lane rank). Completions need no timer: every timer
 //         due at or before an item runs before that item and a completion only lowers C, so
@@ -256,7 +257,7 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
 }
 
 // ---- hosts ----------------------------------------------------------------------------------------
-// committed GPUs of host = lane at time `now`: byte (lane & 7) of the ballot of register (lane >> 3)
+// committed GPUs of host = lane at time `now` (those beyond G included): byte (lane & 7) of the ballot of register (lane >> 3)
 template <int NJ, uint32_t F>
 __device__ __forceinline__ int committed(const Ctx<NJ, F> &c, int32_t now) {
   const int sh = 8 * (c.lane & 7), grp = c.lane >> 3;
@@ -274,7 +275,7 @@ __device__ __forceinline__ int committed(const Ctx<NJ, F> &c, int32_t now) {
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void bind_gpus(Ctx<NJ, F> &c, int h, int g, int32_t now, int32_t finish) {
   const int j = h >> 3, hl = h & 7;
-  const bool mine = ((c.lane >> 3) == hl) & ((c.lane & 7) < c.p.G);
+  const bool mine = (c.lane >> 3) == hl;
 #pragma unroll
   for (int jj = 0; jj < NJ; jj++) {
     if (jj == j) {
@@ -310,11 +311,10 @@ __device__ __forceinline__ int boot_host(Ctx<NJ, F> &c, Regs &r, int32_t now, ui
 // reach all 8 lanes of the group).
 template <int NJ, uint32_t F>
 __device__ __forceinline__ int32_t earliest_idle(const Ctx<NJ, F> &c, int g) {
-  const bool used = (c.lane & 7) < c.p.G;
   int32_t best = NEVER;
 #pragma unroll
   for (int j = 0; j < NJ; j++) {
-    const int32_t f = used ? c.fin[j] : NEVER;
+    const int32_t f = c.fin[j];
     const int32_t mir = __builtin_amdgcn_update_dpp(f, f, 0x141, 0xF, 0xF, false);   // row_half_mirror
     int cnt = 1;
     cnt += __builtin_amdgcn_update_dpp(f, f, 0x39, 0xF, 0xF, false) <= f ? 1 : 0;      // quad_perm [1,2,3,0]
@@ -510,7 +510,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
   uint32_t kb = 0xFFFFFFFFu;
   if (!hopeless) {
     C = committed(c, now);
-    const bool can = (c.hr <= now) & (C + g <= c.p.G);       // a ready host with g idle GPUs
+    const bool can = (c.hr <= now) & (C + g <= NGPU);       // a ready host with g idle GPUs
     idle_ok = wballot(can);
     // (a) election, Section 3.2.2: among the session's hosts that can bind, fewest committed GPUs, then
     // lowest host index: the smallest of the three hosts' keys
@@ -671,7 +671,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
     const int g = (int)((fl >> 3) & 7u) + 1;
     if (now >= lane_get(c.fu, g - 1)) {
       const int C = committed(c, now);
-      const bool can = (c.hr <= now) & (C + g <= c.p.G);
+      const bool can = (c.hr <= now) & (C + g <= NGPU);
       if (elect(c, hw, can ? (uint32_t)c.lane : 0xFFFFFFFFu) != 0xFFFFFFFFu) break;   // the election succeeds
       const uint64_t idle_ok = wballot(can);
       if (idle_ok == 0) {
@@ -760,6 +760,7 @@ __device__ __forceinline__ void tick(Ctx<NJ, F> &c, Regs &r, int32_t now) {
     uint32_t sum_c = 0;
 #pragma unroll
     for (int j = 0; j < NJ; j++) sum_c += (uint32_t)__builtin_popcountll(wballot(c.fin[j] > now));
+    sum_c -= (uint32_t)(8 * NJ * (NGPU - c.p.G));            // (GPUs that are not there)
     const uint32_t per_host = 1000u * (uint32_t)c.p.G;
     const int want = (int)(((uint32_t)c.p.f_milli * sum_c + per_host - 1u) / per_host) + c.p.buffer;
     wave_sync();
@@ -898,7 +899,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   Ctx<NJ, F> c{p, m, lane, n_sess, caplim / 1000, p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr,
                p.ovf_dur + (int64_t)rep * p.n_cap};
 #pragma unroll
-  for (int j = 0; j < NJ; j++) c.fin[j] = 0;
+  for (int j = 0; j < NJ; j++) c.fin[j] = (lane & 7) < p.G ? 0 : NEVER;
   c.hr = lane < p.H0 ? 0 : NEVER;
   c.hs = 0;
   c.qt = NEVER; c.qd = 0; c.qk = 0xFFFFFFFFu;
@@ -1001,7 +1002,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
         // election (Section 3.2.2) on the vector side: every host's key (committed GPUs, index), or all
         // ones where it cannot bind; the keys of the session's three hosts are read and compared
         const int C = committed(c, t);
-        const uint32_t key = (c.hr <= t) & (C + g <= c.p.G) ? (((uint32_t)C << 6) | (uint32_t)c.lane) : 0xFFFFFFFFu;
+        const uint32_t key = (c.hr <= t) & (C + g <= NGPU) ? (((uint32_t)C << 6) | (uint32_t)c.lane) : 0xFFFFFFFFu;
         const uint32_t kb = elect(c, hw, key);
         if (kb == 0xFFFFFFFFu) break;                         // every replica yields
         const int hl = (int)(kb & 63u);
@@ -1141,7 +1142,7 @@ __device__ __forceinline__ int32_t cl_failing_retries(Ctx<NJ, F> &c, Regs &r, in
     const int g = (int)((fl >> 3) & 7u) + 1;
     if (now >= lane_get(c.fu, g - 1)) {
       const int C = committed(c, now);
-      const bool can = (c.hr <= now) & (C + g <= c.p.G);
+      const bool can = (c.hr <= now) & (C + g <= NGPU);
       if (elect(c, hw, can ? (uint32_t)c.lane : 0xFFFFFFFFu) != 0xFFFFFFFFu) break;   // the election succeeds
       const uint64_t idle_ok = wballot(can);
       if (idle_ok == 0) {
@@ -1217,7 +1218,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
   const int32_t caplim = p.cap_milli[rep] * p.G * 3;
   Ctx<NJ, F> c{p, m, lane, n_sess, caplim / 1000, p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr, nullptr};
 #pragma unroll
-  for (int j = 0; j < NJ; j++) c.fin[j] = 0;
+  for (int j = 0; j < NJ; j++) c.fin[j] = (lane & 7) < p.G ? 0 : NEVER;
   c.hr = lane < p.H0 ? 0 : NEVER;
   c.hs = 0;
   c.qt = NEVER; c.qd = 0; c.qk = 0xFFFFFFFFu;
