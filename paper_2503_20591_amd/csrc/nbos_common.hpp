@@ -233,6 +233,34 @@ __device__ __forceinline__ int32_t stage_hits(int32_t staged, int lane, int at, 
   return lane < at ? staged : got;
 }
 
+// Lane i < cnt holds a timer (t, key): how many of the cnt timers come before it. The other lanes hold NEVER and all
+// ones, and get what they get. Times alone decide unless two are equal - then the ranks do not add up to
+// 0 + 1 + ... + (cnt - 1) - so a timer costs one lane read, one comparison and one addition per other timer; timers
+// of one instant are told apart by a second count over times and keys. Bound by the chain of lane reads: 40 timers
+// took 440 instructions with times and keys compared from the start.
+__device__ __forceinline__ int timer_ranks(int lane, int cnt, int32_t t, uint32_t key) {
+  int rank = 0;
+  for (int j0 = 0; j0 < cnt; j0 += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; j++) rank += lane_get(t, j0 + j) < t ? 1 : 0;      // (NEVER is before nothing)
+  }
+  int sum = lane < cnt ? rank : 0;                 // at most 63 each, 2,016 in all
+  sum += (int)dpp<0xB1>((uint32_t)sum);
+  sum += (int)dpp<0x4E>((uint32_t)sum);
+  sum += (int)dpp<0x141>((uint32_t)sum);
+  sum += (int)dpp<0x140>((uint32_t)sum);
+  const int total = lane_get(sum, 0) + lane_get(sum, 16) + lane_get(sum, 32) + lane_get(sum, 48);
+  if (total != cnt * (cnt - 1) / 2) {
+    rank = 0;
+    for (int j = 0; j < cnt; j++) {
+      const int32_t tj = lane_get(t, j);
+      const uint32_t kj = (uint32_t)lane_get((int)key, j);
+      rank += (tj < t) | ((tj == t) & (kj < key)) ? 1 : 0;
+    }
+  }
+  return rank;
+}
+
 // Can the dynamic limit of Section 3.4.1 ever admit a host that the replay's own cap turns away? Not while
 // every host that is on holds at most slim subscribed GPUs and more hosts are on than a request has GPUs:
 // (S + g) n <= sum S + g <= n slim + g gives S + g <= slim + g / n, i.e. S + g <= slim for g < n. A host's

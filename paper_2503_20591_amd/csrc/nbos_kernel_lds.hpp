@@ -152,6 +152,118 @@ __device__ __forceinline__ void ovf_push(Ctx<F> &c, Regs &r, int32_t t, uint32_t
   r.o_n++;
 }
 
+// ---- host helpers -------------------------------------------------------------------------------
+// committed GPUs of host h at time `now` (those beyond G, held for ever, included)
+template <uint32_t F>
+__device__ __forceinline__ int committed(const Ctx<F> &c, int h, int32_t now) {
+  const int4 a = c.m.fin[2 * h], b = c.m.fin[2 * h + 1];
+  return (a.x > now) + (a.y > now) + (a.z > now) + (a.w > now) + (b.x > now) + (b.y > now) + (b.z > now) + (b.w > now);
+}
+
+// bind g free GPUs of host h until `finish` (lane = entry of the row; every eighth lane does the same)
+template <uint32_t F>
+__device__ __forceinline__ void bind_gpus(Ctx<F> &c, int h, int g, int32_t finish) {
+  wave_sync();
+  int32_t *row = (int32_t *)&c.m.fin[2 * h];
+  const int k = c.lane & 7;
+  const int32_t own = row[k], up = row[(k + g) & 7];
+  row[k] = med3(own, finish, k + g < NGPU ? up : NEVER);
+}
+
+// ---- helper waves ------------------------------------------------------------------------------------
+// A scan over all hosts is split by chunks of 64 hosts: wave w of the nw waves of the workgroup takes the
+// chunks w, w + nw, ... The wave that runs the replay (wave 0) writes what is to be scanned into the mail
+// words and meets the helpers at a barrier; each wave scans its chunks and reduces them; the helpers leave
+// their results in the mail words, a second barrier, and wave 0 combines the nw results. Between scans the
+// helpers sleep at the first barrier and take no issue slots. Every scan costs wave 0 exactly two barriers,
+// every helper the same two; HC_EXIT ends the helpers' loop with one barrier on both sides.
+// mail[0..3] = command, time, request g, room under the cap; mail[8 + 4 w + i] = result i of wave w.
+enum { HC_EXIT = 0, HC_BEST_HOST, HC_EARLIEST_IDLE, HC_PLACE, HC_TICK, HC_REFILL };
+// (more than four waves gain nothing measurable: 12 chunks of hosts on 4 / 6 / 8 / 12 waves take 269 / 265 / 266 /
+// 269 ms on the 768-host workload, and a workgroup of more than 256 threads leaves the compiler fewer registers)
+constexpr int MAX_WAVES = 4, MAIL_WORDS = 8 + 4 * MAX_WAVES;
+
+template <uint32_t F>
+__device__ __forceinline__ void helpers_go(const Ctx<F> &c, int cmd, int32_t now, int g, int32_t room) {
+  if (c.nw == 1) return;
+  *(int4 *)c.m.mail = make_int4(cmd, now, g, room);
+  __syncthreads();
+}
+template <uint32_t F>
+__device__ __forceinline__ void helpers_done(const Ctx<F> &c) {
+  if (c.nw > 1) __syncthreads();
+}
+// result i of helper wave w, as a uniform value (after helpers_done)
+template <uint32_t F>
+__device__ __forceinline__ uint32_t helper_result(const Ctx<F> &c, int w, int i) {
+  return uni((uint32_t)c.m.mail[8 + 4 * w + i]);
+}
+
+// ---- refill of the sorted timers ---------------------------------------------------------------------
+// This wave's share of the timers that wait in the session records (due[] is padded with NEVER to a multiple of
+// four; wave w takes the blocks of 256 sessions w, w + nw, ...): the sessions of those due at or before T, side by
+// side in the lanes of `staged` (the first 64 of them), their number, and the earliest time beyond T. The next four
+// times per lane are in flight while the current ones are looked at; a time inside the window is rare (one or two
+// in a block), so only the words that have one are staged. Bound by the latency of the scan, once per about 40 timers:
+// with one wave and all four words of a block staged, a refill over 8,000 sessions took 26,000 clocks, 30 % of the
+// closed loops on 512 to 768 hosts (256 replays of 250,000 cells: 181.5 ms; now 129.0).
+template <uint32_t F>
+__device__ __forceinline__ int refill_part(const Ctx<F> &c, int32_t T, int first, int stride, int32_t &staged, int32_t &left) {
+  const int4 *due4 = (const int4 *)c.m.due;
+  const int quads = (c.n_sess + 3) >> 2;
+  int cnt = 0;
+  int32_t mn = NEVER;
+  staged = 0;
+  int4 next = due4[min(first + c.lane, quads - 1)];
+  for (int q0 = first; q0 < quads; q0 += stride) {
+    const int q = q0 + c.lane, s0 = 4 * q;
+    const int4 d = next;
+    next = due4[min(q + stride, quads - 1)];
+    const bool in = q < quads;
+    const int32_t lo = in ? min(min(d.x, d.y), min(d.z, d.w)) : NEVER;
+    if (wballot(lo <= T) != 0) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int32_t dj = in ? (j == 0 ? d.x : j == 1 ? d.y : j == 2 ? d.z : d.w) : NEVER;
+        const bool hit = dj <= T;
+        const uint64_t b = wballot(hit);
+        if (b != 0) {
+          staged = cnt < WAVE ? stage_hits(staged, c.lane, cnt, hit, b, s0 + j) : staged;
+          cnt += __builtin_popcountll(b);
+        }
+        mn = hit ? mn : min(dj, mn);
+      }
+    } else {
+      mn = min(lo, mn);
+    }
+  }
+  left = (int32_t)wave_min((uint32_t)mn);
+  return cnt;
+}
+
+// The same over all sessions. From 1,024 sessions on the helper waves take their share (below that the two
+// barriers cost what they save): every wave leaves the sessions it has found in its 64 words of mark[], which is
+// idle (MARK_FREE) outside a round and is made so again; four waves are there from 256 hosts on, so the words are too.
+template <uint32_t F>
+__device__ __forceinline__ int refill_scan(Ctx<F> &c, int32_t T, int32_t &staged, int32_t &left) {
+  if (c.nw == 1 || c.n_sess <= 4 * 4 * WAVE) return refill_part(c, T, 0, WAVE, staged, left);
+  helpers_go(c, HC_REFILL, T, 0, 0);
+  const int n0 = refill_part(c, T, 0, WAVE * c.nw, staged, left);
+  c.m.mark[c.lane] = staged;
+  helpers_done(c);
+  int cnt = n0, below = n0, at = c.lane;
+  for (int w = 1; w < c.nw; w++) {
+    const int n = (int)helper_result(c, w, 0);
+    at += c.lane >= cnt ? WAVE - below : 0;          // (lane - the hits of the waves before) + 64 w
+    cnt += n; below = n;
+    left = min(left, (int32_t)helper_result(c, w, 1));
+  }
+  staged = c.m.mark[min(at & 0xFFFF, WAVE * c.nw - 1)];
+  wave_sync();
+  for (int w = 0; w < c.nw; w++) c.m.mark[w * WAVE + c.lane] = MARK_FREE;
+  return cnt;
+}
+
 // Registers empty: all timers that are due within a window after the earliest one move
 // from the session records into the registers at once, at most 64. A window takes whole instants, so
 // everything taken is earlier than everything left behind whatever the kinds. The window adapts to
@@ -170,31 +282,7 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   for (;;) {
     const int64_t lim = (int64_t)r.o_min_t + win;
     const int32_t T = lim < NEVER - 1 ? (int32_t)lim : NEVER - 1;
-    cnt = 0;
-    int32_t mn = NEVER;                          // earliest time beyond the window, per lane
-    // four sessions per lane and step (due[] is padded with NEVER to a multiple of four)
-    const int4 *due4 = (const int4 *)c.m.due;
-    const int quads = (c.n_sess + 3) >> 2;
-    for (int q0 = 0; q0 < quads; q0 += WAVE) {
-      const int q = q0 + c.lane, s0 = 4 * q;
-      const int4 d = due4[min(q, quads - 1)];
-      const bool in = q < quads;
-      const int32_t lo = in ? min(min(d.x, d.y), min(d.z, d.w)) : NEVER;
-      if (wballot(lo <= T) != 0) {               // rare: some of these timers are inside the window
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const int32_t dj = j == 0 ? d.x : j == 1 ? d.y : j == 2 ? d.z : d.w;
-          const bool hit = in & (dj <= T);
-          const uint64_t b = wballot(hit);
-          staged = cnt < WAVE ? stage_hits(staged, c.lane, cnt, hit, b, s0 + j) : staged;
-          cnt += __builtin_popcountll(b);
-          mn = hit | !in ? mn : min(dj, mn);
-        }
-      } else {
-        mn = lo < mn ? lo : mn;
-      }
-    }
-    left = (int32_t)wave_min((uint32_t)mn);
+    cnt = refill_scan(c, T, staged, left);
     if (cnt == 0) {                              // the stored bound was below the earliest time: use that
       if (left == NEVER) { r.o_n = 0; r.o_min_t = NEVER; return; }      // nothing waits (not reached: o_n counts them)
       r.o_min_t = left;
@@ -237,23 +325,21 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   // the cursors / durations were written by lane 0 when the timers were scheduled: the fence makes this
   // wave's own stores visible to its other lanes
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  int32_t x = 0, nx = -1, nth = 0;
+  [[maybe_unused]] int32_t dur = 0, sk = 0;
+  [[maybe_unused]] int2 ch = make_int2(-1, 0);
+  const bool ev = (own_key >> 16) != QK_END;
   if constexpr (Ctx<F>::closed) {
     e = c.cl_cur[s];
-    const bool ev = (own_key >> 16) != QK_END;
     const int32_t at = ev ? e : 0;
-    const int2 ch = c.cl_chain[at];
-    const int32_t own_x = c.cl_dur[at] | (int32_t)(((uint32_t)c.cl_sk[at] >> 24) << 28) | CLX_LOADED;
-    x = ev ? own_x : 0;
-    nx = ev ? ch.x : -1; nth = ev ? ch.y : 0;
+    ch = c.cl_chain[at]; dur = c.cl_dur[at]; sk = c.cl_sk[at];
   } else {
     e = c.ovf_dur[s];                            // qd carries the queued cell's duration (of a deferred end: not looked at)
   }
-  int rank = 0;
-  for (int j = 0; j < cnt; j++) {
-    const int32_t tj = lane_get(t, j);
-    const uint32_t kj = (uint32_t)lane_get((int)key, j);
-    rank += (tj < t) | ((tj == t) & (kj < key)) ? 1 : 0;
+  const int rank = timer_ranks(c.lane, cnt, t, key);      // (the gathers are in flight meanwhile)
+  [[maybe_unused]] int32_t x = 0, nx = -1, nth = 0;
+  if constexpr (Ctx<F>::closed) {
+    x = ev ? dur | (int32_t)(((uint32_t)sk >> 24) << 28) | CLX_LOADED : 0;
+    nx = ev ? ch.x : -1; nth = ev ? ch.y : 0;
   }
   // lanes beyond cnt hold the largest key: their rank is cnt, any order among them will do
   const int dst = take ? rank : c.lane;
@@ -269,53 +355,6 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   r.o_n -= cnt;
   r.o_min_t = r.o_n > 0 ? left : NEVER;
   r.o_min_k = 0;                                 // a lower bound: pushes for that very instant wait in the records
-}
-
-// ---- host helpers -------------------------------------------------------------------------------
-// committed GPUs of host h at time `now` (those beyond G, held for ever, included)
-template <uint32_t F>
-__device__ __forceinline__ int committed(const Ctx<F> &c, int h, int32_t now) {
-  const int4 a = c.m.fin[2 * h], b = c.m.fin[2 * h + 1];
-  return (a.x > now) + (a.y > now) + (a.z > now) + (a.w > now) + (b.x > now) + (b.y > now) + (b.z > now) + (b.w > now);
-}
-
-// bind g free GPUs of host h until `finish` (lane = entry of the row; every eighth lane does the same)
-template <uint32_t F>
-__device__ __forceinline__ void bind_gpus(Ctx<F> &c, int h, int g, int32_t finish) {
-  wave_sync();
-  int32_t *row = (int32_t *)&c.m.fin[2 * h];
-  const int k = c.lane & 7;
-  const int32_t own = row[k], up = row[(k + g) & 7];
-  row[k] = med3(own, finish, k + g < NGPU ? up : NEVER);
-}
-
-// ---- helper waves ------------------------------------------------------------------------------------
-// A scan over all hosts is split by chunks of 64 hosts: wave w of the nw waves of the workgroup takes the
-// chunks w, w + nw, ... The wave that runs the replay (wave 0) writes what is to be scanned into the mail
-// words and meets the helpers at a barrier; each wave scans its chunks and reduces them; the helpers leave
-// their results in the mail words, a second barrier, and wave 0 combines the nw results. Between scans the
-// helpers sleep at the first barrier and take no issue slots. Every scan costs wave 0 exactly two barriers,
-// every helper the same two; HC_EXIT ends the helpers' loop with one barrier on both sides.
-// mail[0..3] = command, time, request g, room under the cap; mail[8 + 4 w + i] = result i of wave w.
-enum { HC_EXIT = 0, HC_BEST_HOST, HC_EARLIEST_IDLE, HC_PLACE, HC_TICK };
-// (more than four waves gain nothing measurable: 12 chunks of hosts on 4 / 6 / 8 / 12 waves take 269 / 265 / 266 /
-// 269 ms on the 768-host workload, and a workgroup of more than 256 threads leaves the compiler fewer registers)
-constexpr int MAX_WAVES = 4, MAIL_WORDS = 8 + 4 * MAX_WAVES;
-
-template <uint32_t F>
-__device__ __forceinline__ void helpers_go(const Ctx<F> &c, int cmd, int32_t now, int g, int32_t room) {
-  if (c.nw == 1) return;
-  *(int4 *)c.m.mail = make_int4(cmd, now, g, room);
-  __syncthreads();
-}
-template <uint32_t F>
-__device__ __forceinline__ void helpers_done(const Ctx<F> &c) {
-  if (c.nw > 1) __syncthreads();
-}
-// result i of helper wave w, as a uniform value (after helpers_done)
-template <uint32_t F>
-__device__ __forceinline__ uint32_t helper_result(const Ctx<F> &c, int w, int i) {
-  return uni((uint32_t)c.m.mail[8 + 4 * w + i]);
 }
 
 // lowest host index that is off (the caller has checked that one exists)
@@ -863,6 +902,11 @@ __device__ __forceinline__ void helper_loop(const Ctx<F> &c) {
     } else if (what == HC_PLACE) {
       if (c.nw == MAX_WAVES) place_part<NBOS_MAX_HOSTS / WAVE / MAX_WAVES>(c, now, room, r0, r1, r2);
       else place_part<NBOS_MAX_HOSTS / WAVE>(c, now, room, r0, r1, r2);
+    } else if (what == HC_REFILL) {
+      int32_t staged, left;
+      r0 = (uint32_t)refill_part(c, now, c.wid * WAVE, WAVE * c.nw, staged, left);
+      r1 = (uint32_t)left;
+      c.m.mark[c.wid * WAVE + c.lane] = staged;
     } else {
       int A, Z;
       tick_part(c, now, A, Z, r2);

@@ -235,12 +235,7 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
     // session was queued or ending when the tile was loaded (or its lanes are stale already)
     r.dirty |= r.slow_lanes;
   }
-  int rank = 0;
-  for (int j = 0; j < cnt; j++) {
-    const int32_t tj = lane_get(t, j);
-    const uint32_t kj = (uint32_t)lane_get((int)key, j);
-    rank += (tj < t) | ((tj == t) & (kj < key)) ? 1 : 0;
-  }
+  const int rank = timer_ranks(c.lane, cnt, t, key);
   const int dst = take ? rank : c.lane;          // a permutation: the timers taken in order, the rest where they are
   c.qt = __builtin_amdgcn_ds_permute(dst << 2, t);
   c.qk = (uint32_t)__builtin_amdgcn_ds_permute(dst << 2, (int)key);

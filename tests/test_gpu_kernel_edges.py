@@ -30,3 +30,21 @@ def test_batch_kernel_at_its_chunk_edges(rp, oracle, hosts, G, grow):  # noqa: F
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
     assert st["cells_queued"].max() > 0
+
+
+@pytest.mark.parametrize("closed", [False, True], ids=["open", "closed"])
+@pytest.mark.parametrize("hosts,sessions,step_ms", [(256, 1024, 1), (256, 1025, 1), (256, 1028, 1000), (257, 2049, 60_000),
+                                                    (320, 4099, 1), (300, 3000, 600_000), (65, 1300, 1000)])
+def test_refill_of_the_sorted_timers(rp, oracle, hosts, sessions, step_ms, closed):  # noqa: F811
+    # many more timers than the 64 sorted ones, alone in their millisecond or hundreds at one instant; the helper
+    # waves take part in the scan from 256 hosts and more than 1,024 sessions on
+    on_grid = lambda v: np.maximum(v // step_ms, 1) * step_ms  # noqa: E731
+    tr = tg.make_trace(5, sessions, sessions * 6, ramp_ms=300_000, gpus=lambda r, n: tg.gpus_uniform(r, n),
+                       gap=lambda r, s: on_grid(tg.exp_ms(r, 40.0, s)), dur=lambda r, s: on_grid(tg.lognormal_ms(r, 200.0, 1.0, s)),
+                       with_end=True)
+    tr = (tr[0] // step_ms * step_ms, *tr[1:])
+    flags = tg.F_MIGRATE | (tg.F_CLOSED_LOOP if closed else 0)
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, flags=flags), [tr], [0, 0], [1500, 4000], "refill")
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert closed or st["cells_queued"].max() > 64
