@@ -278,6 +278,7 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   int cnt;
   int32_t staged = 0;                            // the sessions whose timers come in, one per lane
   int32_t left;                                  // earliest time left behind
+  uint32_t left_k = 0;                           // ... and a lower bound of the keys left behind at that time
   int32_t win = r.cl_win;
   for (;;) {
     const int64_t lim = (int64_t)r.o_min_t + win;
@@ -302,6 +303,7 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
       staged = (int32_t)(best & 0xFFFFu);
       cnt = 1;
       left = T;
+      left_k = best;                             // (all that stay are later; a timer pushed before it belongs into the registers)
       break;
     }
     win = (int32_t)((int64_t)win * 40 / cnt);    // aim at 40 of the 64 registers
@@ -354,7 +356,7 @@ __device__ __forceinline__ void refill(Ctx<F> &c, Regs &r) {
   r.q_n = cnt;
   r.o_n -= cnt;
   r.o_min_t = r.o_n > 0 ? left : NEVER;
-  r.o_min_k = 0;                                 // a lower bound: pushes for that very instant wait in the records
+  r.o_min_k = left_k;                            // a lower bound: pushes for that very instant wait in the records
 }
 
 // lowest host index that is off (the caller has checked that one exists)
