@@ -151,6 +151,9 @@ __device__ __forceinline__ int32_t pick(bool c, int32_t a, int32_t b) {
 __device__ __forceinline__ int fresh_lane(int lane) { asm volatile("" : "+v"(lane)); return lane; }
 __device__ __forceinline__ int fresh(int v) { asm volatile("" : "+s"(v)); return v; }
 
+// the lanes of a mask, as the per-lane condition it is (a select reads the scalar pair)
+__device__ __forceinline__ bool in_mask(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // the median of three (one v_med3_i32)
 __device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }
 
@@ -298,8 +301,7 @@ __device__ __forceinline__ int32_t cap_room(const C &c, int g) {
 constexpr uint64_t DIGEST_PRIME = 0x100000001B3ULL;
 __device__ __forceinline__ uint64_t decision_code(int32_t now, uint32_t outcome, uint32_t s, uint32_t slot,
                                                   uint32_t host) {
-  return (uint64_t)host | ((uint64_t)slot << 10) | ((uint64_t)outcome << 12) | ((uint64_t)s << 16) |
-         ((uint64_t)(uint32_t)now << 32);
+  return (uint64_t)(host | (slot << 10) | (outcome << 12) | (s << 16)) | ((uint64_t)(uint32_t)now << 32);
 }
 template <class C, class R>
 __device__ __forceinline__ void decide(C &c, R &r, int32_t now, uint32_t outcome, uint32_t s, uint32_t slot,

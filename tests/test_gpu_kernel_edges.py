@@ -48,3 +48,20 @@ def test_refill_of_the_sorted_timers(rp, oracle, hosts, sessions, step_ms, close
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
     assert closed or st["cells_queued"].max() > 64
+
+
+@pytest.mark.parametrize("flags", [0, tg.F_MIGRATE, tg.F_MIGRATE | tg.F_SCALE_OUT, tg.F_MIGRATE | tg.F_STICKY_EXECUTOR],
+                         ids=["plain", "migrate", "grow", "sticky"])
+@pytest.mark.parametrize("hosts,sessions,cells,longest", [(3, 1, 1, False), (8, 3, 60, False), (9, 7, 57, True), (24, 20, 45, False),
+                                                          (33, 32, 97, True), (64, 64, 65, True), (64, 60, 1000, False)])
+def test_starts_at_once_in_the_register_kernel(rp, oracle, hosts, sessions, cells, longest, flags):  # noqa: F811
+    # sums over the cells that start at once are made per tile of 64 events: first and last tiles of any fill, the
+    # longest cells on all GPUs of a host (the largest GPU time a lane can bring)
+    tr = tg.make_trace(11, sessions, cells, ramp_ms=60_000,
+                       gpus=(lambda r, n: np.full(n, 8, np.uint8)) if longest else tg.gpus_uniform,
+                       gap=lambda r, s: tg.exp_ms(r, 100.0, s),
+                       dur=lambda r, s: np.full(s, tg.MAX_DUR_MS, np.int64) if longest else tg.exp_ms(r, 20.0, s))
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=min(hosts + 5, 64), flags=flags), [tr], [0, 0], [2000, 5000], "at_once")
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert st["cells_immediate"].max() > 0
