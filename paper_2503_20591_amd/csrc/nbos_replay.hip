@@ -481,7 +481,8 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
     // same idea as for the register kernel; its batches are small (the LDS footprint allows few
     // workgroups per compute unit), so the instance compiled for the flag set is used whenever
-    // there is one
+    // there is one (migration and scale-out, 200 to 300 hosts, 256 replays of 90,000 cells: 35.6 ms with the
+    // flags read at run time, 29.9 with the instance)
     const uint32_t policy = cfg->flags & kPolicyFlags;
     constexpr uint32_t kAllScaling = NBOS_F_MIGRATE | NBOS_F_SCALE_OUT | NBOS_F_SCALE_IN;
     constexpr uint32_t kAutoScaler = NBOS_F_MIGRATE | NBOS_F_SCALE_IN | NBOS_F_AUTOSCALE | NBOS_F_DYNAMIC_SR;
@@ -489,6 +490,7 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     else if (policy == kAllScaling) set_lds_kernel<kAllScaling>(h);
     else if (policy == kAutoScaler) set_lds_kernel<kAutoScaler>(h);
     else if (policy == NBOS_F_MIGRATE) set_lds_kernel<NBOS_F_MIGRATE>(h);
+    else if (policy == (NBOS_F_MIGRATE | NBOS_F_SCALE_OUT)) set_lds_kernel<NBOS_F_MIGRATE | NBOS_F_SCALE_OUT>(h);
     else set_lds_kernel<kRuntimeFlags>(h);
   }
   HIP_TRY(hipFuncSetAttribute(h->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->lds_bytes));
