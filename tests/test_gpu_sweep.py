@@ -62,3 +62,23 @@ def test_relationships_of_the_evaluation(study):
             # pays a container start per cell (section "Interactivity")
             assert x["immediate"] > 0.8
             assert x["batch_mean_delay_s"] >= 15.0 and x["mean_delay_s"] < 0.5 * x["batch_mean_delay_s"]
+
+
+def test_rows_do_not_depend_on_the_stream_or_the_thread(study):
+    # the two policies run on two streams: from another current stream, and from two threads at a time, the same rows
+    import threading
+    import torch
+    from paper_2503_20591_amd import sweep
+    batch, rows = study
+    out = [None, None]
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            out[k] = sweep.run_policies(batch, batch_start_delay_ms=15_000)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert out[0] == rows and out[1] == rows
