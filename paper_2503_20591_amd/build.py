@@ -19,7 +19,11 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                # almost all control flow is wave-uniform: leave regions without a divergent branch as they are written
                # (by default they are rebuilt too, with a flag in a scalar register pair for every join; measured:
                # 30 hosts 37.5 -> 35.7 ms, 64 hosts 94.3 -> 89.6 ms, closed loops 78.8 -> 74.3 and 194.6 -> 188.2 ms)
-               "-mllvm", "-structurizecfg-skip-uniform-regions=1"]
+               "-mllvm", "-structurizecfg-skip-uniform-regions=1",
+               # a block that is only reached by a branch begins on a 64-byte line: a lone wave waits for every fetch
+               # (measured: 64 hosts 70.2 -> 68.0 ms, 30 hosts 28.5 -> 28.0, closed loops 57.8 -> 55.5 and 131.1 -> 128.8,
+               # 768 hosts 167.6 -> 166.1; Batch 151.7 -> 152.6; 32 and 128 bytes: the same)
+               "-mllvm", "-align-all-nofallthru-blocks=6"]
 
 
 def _hipcc(out: str, extra: list[str], verbose: bool) -> str:
