@@ -65,3 +65,16 @@ def test_starts_at_once_in_the_register_kernel(rp, oracle, hosts, sessions, cell
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
     assert st["cells_immediate"].max() > 0
+
+
+@pytest.mark.parametrize("flags", [0, tg.F_SCALE_IN, tg.F_CLOSED_LOOP], ids=["plain", "shrink", "closed"])
+@pytest.mark.parametrize("hosts,G", [(3, 8), (8, 3), (9, 8), (33, 2), (64, 8)])
+def test_retries_skipped_where_cells_do_not_migrate(rp, oracle, hosts, G, flags):  # noqa: F811
+    # without migration a queued cell waits for its session's own three hosts: retries before they can have the GPUs
+    # idle are skipped, and the ones that are left start, fail again or give the cell up at the same times
+    tr = crowded(21, hosts, G, 4, 5, gap_s=60.0, dur_s=90.0, with_end=True)
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, min_hosts=max(3, hosts // 2), gpus_per_host=G, flags=flags),
+                [tr], [0, 0], [1500, 6000], "own")
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert st["cells_queued"].max() > 0 and st["cells_started"].max() > st["cells_immediate"].max()
