@@ -46,16 +46,19 @@ def run_policies(batch: tg.TraceBatch, batch_start_delay_ms: int = 15_000,
     as_batch = _with_config(batch, flags=tg.F_BATCH_MODE | (batch.config["flags"] & tg.F_SCALE_OUT),
                                  batch_start_delay_ms=batch_start_delay_ms)
     # A study's replays leave most of the chip idle and last as long as their longest one, so the two policies run
-    # side by side, the Batch baseline on a stream of its own (20 replays of 60,000 cells each: 51.5 ms one after
-    # the other, 29.7 ms side by side). Both handles exist before either runs (making one waits for the device), and
-    # both are closed, which waits for their streams, before the traces they share are let go.
+    # side by side, each on a stream of its own (20 replays of 60,000 cells each: 51.5 ms one after the other, 30.2 ms
+    # side by side). Streams share four hardware queues, and one of the two would wait on the other's: two new streams
+    # in a row have different ones but for one call in sixteen (31.4 ms on average), a new one and the current one but for
+    # one in four (34.8). Both handles exist before either runs (making one waits for the device), and both are closed,
+    # which waits for their streams, before the traces they share are let go.
     here = torch.cuda.current_stream(dev["cap_milli"].device)
-    beside = torch.cuda.Stream(device=dev["cap_milli"].device)
-    beside.wait_stream(here)
+    streams = [torch.cuda.Stream(device=dev["cap_milli"].device) for _ in range(2)]
+    for st in streams:
+        st.wait_stream(here)
     with contextlib.ExitStack() as handles:
-        h_nb = replay.Replay(batch.config, dev, stream=here)
+        h_nb = replay.Replay(batch.config, dev, stream=streams[0])
         handles.callback(h_nb.close)
-        h_ba = replay.Replay(as_batch.config, dev, stream=beside)
+        h_ba = replay.Replay(as_batch.config, dev, stream=streams[1])
         handles.callback(h_ba.close)
         h_ba.run()
         h_nb.run()
