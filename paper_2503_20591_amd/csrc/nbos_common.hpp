@@ -139,6 +139,17 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Times that every lane works out although only some lanes' are looked at: a lane without a timer or a cell of its
+// own holds NEVER, or what belongs to others, and its sum may leave the type's range. They wrap: of a signed sum that
+// leaves its range nothing that is computed from it is defined, and neither & nor pick shields the lanes that count.
+__host__ __device__ __forceinline__ int32_t wrap_add(int32_t a, int32_t b) { return (int32_t)((uint32_t)a + (uint32_t)b); }
+// a closed loop's next event: think time after the finish of the cell that started at t
+__host__ __device__ __forceinline__ int32_t next_event_time(int32_t t, int32_t dur, int32_t think) { return wrap_add(wrap_add(t, dur), think); }
+// the n-th retry of a cell
+__host__ __device__ __forceinline__ int32_t retry_time(int32_t t_submit, int32_t n, int32_t interval) {
+  return wrap_add(t_submit, (int32_t)((uint32_t)n * (uint32_t)interval));
+}
+
 // c ? a : b without a branch, whatever a and b take to work out (the compiler likes to move that into an arm)
 __device__ __forceinline__ int32_t pick(bool c, int32_t a, int32_t b) {
   const int32_t m = c ? -1 : 0;

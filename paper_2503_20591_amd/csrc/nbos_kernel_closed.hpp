@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(WAVE) nbos_closed_chain_kernel(const int64_t *
 template <uint32_t F>
 __device__ __forceinline__ void cl_after_round(Ctx<F> &c, Regs &r, int n) {
   const bool succ = (c.lane < n) & (c.qnx >= 0);
-  const int32_t ts = pick(succ, c.qt + (c.qx & 0x0FFFFFFF) + c.qnth, 0);   // in range: checked before the round
+  const int32_t ts = pick(succ, next_event_time(c.qt, c.qx & 0x0FFFFFFF, c.qnth), 0);   // in range: checked before the round
   const int32_t es = c.qnx;
   const uint32_t ss = c.qk & 0xFFFFu;
   c.cl_cur[succ ? (int)ss : c.p.n_cap] = es;        // (one word more than sessions)

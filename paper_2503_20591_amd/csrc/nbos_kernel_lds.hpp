@@ -1068,7 +1068,7 @@ __device__ __forceinline__ bool fire_quiet_retries(Ctx<F> &c, Regs &r, int32_t t
   const uint32_t s = mine ? c.qk & 0xFFFFu : 0u;
   const uint32_t fl = (uint32_t)c.m.sess[s].z;
   const int retries = (int)((fl >> 8) & 15u) + 1;                    // below max_retries before: see retry_lookahead
-  const int32_t again = c.m.sess[s].y + retries * c.p.retry_iv;
+  const int32_t again = retry_time(c.m.sess[s].y, retries, c.p.retry_iv);
   const int32_t nt = pick(mine, again, c.qt);
   const bool far = mine & (r.o_n > 0) & !((nt < r.o_min_t) | ((nt == r.o_min_t) & (c.qk < r.o_min_k)));
   const uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
@@ -1155,7 +1155,7 @@ __device__ __forceinline__ uint64_t batch_round(Ctx<F> &c, Regs &r, uint64_t run
   const uint64_t done = run & below;
   if (__builtin_expect(done == 0, 0)) return 0;
   const bool mine = (done >> c.lane) & 1u;
-  const int32_t finish = vt + vd;
+  const int32_t finish = wrap_add(vt, vd);       // (of lanes that run no cell: anything)
   {
     // bind g free GPUs of the chosen host: rewrite its row
     int4 a = lead == 0 ? a0 : (lead == 1 ? a1 : a2);

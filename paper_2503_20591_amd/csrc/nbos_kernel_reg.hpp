@@ -142,7 +142,7 @@ __device__ __forceinline__ void ovf_push(Ctx<NJ, F> &c, Regs &r, int32_t t, uint
 template <int NJ, uint32_t F>
 __device__ __forceinline__ int32_t waiting_time(const Ctx<NJ, F> &c, const int2 rec) {
   const uint32_t fl = (uint32_t)rec.x;
-  const int32_t at = rec.y + (int32_t)((fl >> 8) & 15u) * c.p.retry_iv;
+  const int32_t at = retry_time(rec.y, (int32_t)((fl >> 8) & 15u), c.p.retry_iv);
   return (fl & 7u) == SS_QUEUED ? at : rec.y;
 }
 
