@@ -75,13 +75,13 @@ enum { H_OFF = 0, H_BOOT = 1, H_READY = 2 };
 enum { S_UNPLACED = 0, S_IDLE = 1, S_BUSY = 2, S_REJECTED = 3, S_ENDED = 4 };
 enum { T_COMPLETE = 0, T_HOST_READY = 1, T_RETRY = 2, T_NEXT = 3, T_TICK = 4 };
 
-typedef struct { int32_t time; int32_t prio; int32_t id; } tmr;
+typedef struct { int64_t time; int32_t prio; int32_t id; } tmr;
 
 typedef struct {
   int state;
-  int32_t ready_at;
+  int64_t ready_at;
   int C, S, nrep;
-  int32_t warm[4];    /* when each pre-warmed container is (again) available */
+  int64_t warm[4];    /* when each pre-warmed container is (again) available */
 } host_rec;
 
 typedef struct {
@@ -106,7 +106,7 @@ typedef struct {
   sess_rec *sess;
   int n_sess;
   tmr *heap; int n_heap, cap_heap;
-  int32_t clock;
+  int64_t clock;            /* (64 bits, as all times ahead of it: a closed loop's lag can carry those out of 32) */
   int n_on;                 /* hosts not off        */
   int64_t sum_S, sum_C;     /* cluster totals       */
   int64_t n_replicas;       /* placed replicas      */
@@ -130,7 +130,7 @@ static int tmr_less(const tmr *a, const tmr *b) {
   if (a->prio != b->prio) return a->prio < b->prio;
   return a->id < b->id;
 }
-static void heap_push(sim *m, int32_t time, int prio, int id) {
+static void heap_push(sim *m, int64_t time, int prio, int id) {
   if (m->n_heap == m->cap_heap) {
     int nc = m->cap_heap * 2;
     tmr *nh = (tmr *)realloc(m->heap, (size_t)nc * sizeof(tmr));
@@ -174,8 +174,8 @@ static void decide(sim *m, int outcome, int s, int slot, int host) {
 }
 
 /* Move the clock; the integrals of provisioned and subscribed GPUs grow with it. */
-static void advance(sim *m, int32_t t) {
-  int64_t dt = (int64_t)t - m->clock;
+static void advance(sim *m, int64_t t) {
+  int64_t dt = t - m->clock;
   m->r.gpu_ms_provisioned += (int64_t)m->n_on * m->G * dt;
   m->r.sub_gpu_ms += m->sum_S * dt;
   m->r.replica_ms += m->n_replicas * dt;
@@ -274,10 +274,10 @@ static void on_session_start(sim *m, int s) {
 }
 
 /* ---- a cell starts: Section 3.3 (bind GPUs), metrics of sections "Resource Usage & Efficiency", "Interactivity" and "Task Completion Time" - */
-static void start_cell(sim *m, int s, int slot, int32_t start, int outcome) {
+static void start_cell(sim *m, int s, int slot, int64_t start, int outcome) {
   sess_rec *q = &m->sess[s];
-  int32_t commit_t = m->clock;
-  if ((int64_t)start + q->dur >= 2147483647LL) { m->err = ORC_E_INPUT; return; }   /* closed loop only */
+  int64_t commit_t = m->clock;
+  if (start + q->dur >= 2147483647LL) { m->err = ORC_E_INPUT; return; }   /* closed loop only */
   int32_t finish = start + q->dur;
   int32_t delay = start - q->t_submit;
   q->exec_slot = slot;

@@ -374,10 +374,10 @@ __device__ __forceinline__ int find_off_host(const Ctx<F> &c) {
 template <uint32_t F>
 __device__ __forceinline__ int boot_host(Ctx<F> &c, Regs &r, int32_t now, uint32_t hs_new) {
   const int h = find_off_host(c);
-  const int32_t ra = now + c.p.boot;
+  const int32_t ra = after(c, now, c.p.boot);
   c.m.ready_at[h] = ra; c.m.hsn[h] = hs_new;
   if (c.flags() & NBOS_F_WARM_POOL) {         // its pre-warmed containers are there once it is up
-    c.m.warm[4 * h + (c.lane & 3)] = ra + c.p.prewarm;
+    c.m.warm[4 * h + (c.lane & 3)] = after(c, ra, c.p.prewarm);
   }
   c.fu = c.fu < ra ? c.fu : ra;               // a new host may have idle GPUs from then on
   c.fc = c.fc < ra ? c.fc : ra;
@@ -709,7 +709,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
     if (kb != 0xFFFFFFFFu) {
       const int lead = (int)(kb & 3u), hl = (int)((kb >> 2) & 1023u);
       // (every lane writes the entry it has read, the lead's row as it is now; lanes 24 up do what 16 to 23 do)
-      const int32_t bound = med3(f, now + dur, k + g < NGPU ? up : NEVER);
+      const int32_t bound = med3(f, wrap_add(now, dur), k + g < NGPU ? up : NEVER);
       row[k] = rr == lead ? bound : f;
       if (now == t_submit) r.c_imm++;
       start_cell(c, r, s, hw, fl, lead, hl, now, now, t_submit, dur, NBOS_D_START);
@@ -766,7 +766,7 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
       // (b) migration, Section 3.2.3: the target binds the GPUs at once. A ready host of this session
       // with g idle GPUs would have won the election, so none of its hosts can show up as a target.
       const int dst = (int)(tkey & 1023u);
-      int32_t start = now + c.p.migr;
+      int32_t start = after(c, now, c.p.migr);
       uint32_t outcome = NBOS_D_MIGRATE;
       if (c.flags() & NBOS_F_WARM_POOL) {
         // Section 3.2.3: the target's pre-warmed container that has been available longest, if any
@@ -777,8 +777,8 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
         const uint32_t first = wave_min(av);
         if ((int32_t)first <= now) {
           const int w = (int)__builtin_ctzll(wballot(av == first));
-          c.m.warm[4 * dst + w] = now + c.p.prewarm;
-          start = now + c.p.warm_migr;
+          c.m.warm[4 * dst + w] = after(c, now, c.p.prewarm);
+          start = after(c, now, c.p.warm_migr);
           outcome = NBOS_D_MIGRATE_WARM;
           c32_add(c.m, c.lane, CS_MIGRWARM, 1u);
         }
@@ -789,20 +789,20 @@ __device__ __forceinline__ int32_t attempt(Ctx<F> &c, Regs &r, uint32_t s, uint3
       wave_sync();
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
       PROF_SUB(PC_A_VICTIM);
-      bind_gpus(c, dst, g, start + dur);
+      bind_gpus(c, dst, g, wrap_add(start, dur));       // (out of range: start_cell ends the replay)
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, outcome);
       PROF_SUB(PC_A_BIND);
     } else {
       // (c) a new host for the cell, Section 3.4.2: reserved and bound before it is up
-      const int32_t start = now + c.p.boot + c.p.migr;
+      const int32_t start = after(c, after(c, now, c.p.boot), c.p.migr);
       subscribe(c, hv, 0u - moved);
       r.min_s = -1;
       wave_sync();
       cap_bound_host_freed(c, hv, (int32_t)(uni(c.m.hsn[hv]) & 0xFFFFu), now);
       const int h = boot_host(c, r, now, moved);
       c32_max(c.m, c.lane, CS_PEAK, (uint32_t)c.n_on);
-      bind_gpus(c, h, g, start + dur);
+      bind_gpus(c, h, g, wrap_add(start, dur));
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, h, now, start, t_submit, dur, NBOS_D_SCALE_CELL);
     }

@@ -289,10 +289,10 @@ template <int NJ, uint32_t F>
 __device__ __forceinline__ int boot_host(Ctx<NJ, F> &c, Regs &r, int32_t now, uint32_t hs_new) {
   const uint64_t off = wballot((c.lane < c.p.Hmax) & (c.hr == NEVER));
   int h = (int)__builtin_ctzll(off);                 // the caller has checked that one exists
-  int32_t ra = now + c.p.boot;
+  int32_t ra = after(c, now, c.p.boot);
   if (c.lane == h) { c.hr = ra; c.hs = hs_new; }
   if (c.flags() & NBOS_F_WARM_POOL) {         // its pre-warmed containers are there once it is up
-    c.m.warm[4 * h + (c.lane & 3)] = ra + c.p.prewarm;
+    c.m.warm[4 * h + (c.lane & 3)] = after(c, ra, c.p.prewarm);
   }
   c.fu = c.fu < ra ? c.fu : ra;               // a new host may have idle GPUs from then on
   c32_add(c.m, c.lane, CS_NON, 1u);
@@ -544,7 +544,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
   if (kb != 0xFFFFFFFFu) {
     const int hl = (int)(kb & 63u);
     const int lead = (uint32_t)hl == h0 ? 0 : ((uint32_t)hl == h1 ? 1 : 2);
-    bind_gpus(c, hl, g, now, now + dur);
+    bind_gpus(c, hl, g, now, wrap_add(now, dur));       // (out of range: start_cell ends the replay)
     if (now == t_submit) r.c_imm++;
     start_cell(c, r, s, hw, fl, lead, hl, now, now, t_submit, dur, NBOS_D_START);
     return;
@@ -594,7 +594,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
         const uint32_t first = wave_min(av);
         if ((int32_t)first <= now) {
           const int w = (int)__builtin_ctzll(wballot(av == first));
-          c.m.warm[4 * dst + w] = now + c.p.prewarm;
+          c.m.warm[4 * dst + w] = after(c, now, c.p.prewarm);
           c32_add(c.m, c.lane, CS_MIGRWARM, 1u);
           warm = true;
         }
@@ -603,22 +603,22 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
       if (c.lane == dst) c.hs += moved;
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       if (warm) {
-        const int32_t start = now + c.p.warm_migr;
-        bind_gpus(c, dst, g, now, start + dur);
+        const int32_t start = after(c, now, c.p.warm_migr);
+        bind_gpus(c, dst, g, now, wrap_add(start, dur));
         start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, NBOS_D_MIGRATE_WARM);
       } else {
-        const int32_t start = now + c.p.migr;
-        bind_gpus(c, dst, g, now, start + dur);
+        const int32_t start = after(c, now, c.p.migr);
+        bind_gpus(c, dst, g, now, wrap_add(start, dur));
         start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, NBOS_D_MIGRATE);
       }
     } else {
       // (c) a new host for the cell, Section 3.4.2: reserved and bound before it is up
-      const int32_t start = now + c.p.boot + c.p.migr;
+      const int32_t start = after(c, after(c, now, c.p.boot), c.p.migr);
       if (c.lane == hv) c.hs -= moved;
       const int h = boot_host(c, r, now, moved);
       wave_sync();
       c32_max(c.m, c.lane, CS_PEAK, uni(c.m.c32[CS_NON]));
-      bind_gpus(c, h, g, now, start + dur);
+      bind_gpus(c, h, g, now, wrap_add(start, dur));
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, h, now, start, t_submit, dur, NBOS_D_SCALE_CELL);
     }

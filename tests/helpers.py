@@ -28,3 +28,27 @@ def digest_of(codes):
     for c in codes:
         d = (d * 0x100000001B3 + int(c)) & 0xFFFFFFFFFFFFFFFF
     return d
+
+
+def late_in_a_closed_loop(how, left, first_dur=1):
+    """A closed loop near the end of the int32 time range: (config, events, GPUs) with two sessions (0 and 4) whose
+    cells come days late, each after four day-long ones that follow one another at once, when three other sessions hold
+    all GPUs of the hosts of both. Session 0's last cell, of ``first_dur`` ms, is submitted ``left`` ms before the last
+    time there is, session 4's 5 s later. ``how``: 'migrate' (to the one idle host), 'grow' (onto a new host) or 'warm'
+    (to the idle host, which has one pre-warmed container)."""
+    from paper_2503_20591_amd import tracegen as tg
+    day, end, now = 86_400_000, 2**31 - 1, 2**31 - 1 - left
+    cfg = dict(tg.base_config(hosts_initial=3 if how == "grow" else 4, hosts_max=4,
+                              flags=tg.F_CLOSED_LOOP | {"migrate": tg.F_MIGRATE, "grow": tg.F_SCALE_OUT,
+                                                        "warm": tg.F_MIGRATE | tg.F_WARM_POOL}[how]),
+               migration_delay_ms={"migrate": 600_000, "grow": 1_000, "warm": 2_000}[how], boot_delay_ms=600_000 if how == "grow" else 0,
+               retry_interval_ms=1000, max_retries=2, warm_pool_per_host=1, warm_migration_delay_ms=1_000,
+               prewarm_delay_ms=600_000 if how == "warm" else 0)
+    latest = end - 1 - (day + 2 * 1000 + 600_000 + 2_000)          # a trace's last event
+    ev = [[0, 0, s, 0] for s in range(5)]
+    for s, at, dur in ((0, now, first_dur), (4, now + 5_000, 1)):
+        ev += [[10 + i, 1, s, day] for i in range(4)]              # at 10 + i days: three days late at the end
+        ev += [[at - 3 * day + 3, 1, s, dur]]
+    for s in (1, 2, 3):                                            # a day, and on to the last second but one
+        ev += [[latest - 10, 1, s, day], [latest - 10, 1, s, end - 2 - (latest - 10 + day)]]
+    return cfg, sorted(ev), [8] * 5

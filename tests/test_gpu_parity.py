@@ -9,7 +9,7 @@ import os
 import numpy as np
 import pytest
 
-from helpers import GOLDEN, code_of, digest_of, events_to_arrays, load_golden
+from helpers import GOLDEN, code_of, digest_of, events_to_arrays, late_in_a_closed_loop, load_golden
 from paper_2503_20591_amd import tracegen as tg
 
 pytestmark = pytest.mark.gpu
@@ -480,6 +480,24 @@ def test_closed_loop_time_range(rp, oracle, in_lds):
     st, logs = gpu_run(rp, b, log=True, in_lds=in_lds)
     assert_same(rp, oracle, b, st, logs, check=True)
     assert st["t_end_ms"][0] == 2**31 - 2
+
+
+@pytest.mark.parametrize("in_lds", [False, True], ids=["regs", "lds"])
+@pytest.mark.parametrize("how,left,dur,fine", [("migrate", 605_000, 4_999, True), ("migrate", 605_000, 5_000, False),
+                                               ("migrate", 600_000, 1, False), ("migrate", 10_000, 1, False),
+                                               ("grow", 606_000, 4_999, True), ("grow", 601_000, 1, False),
+                                               ("grow", 10_000, 1, False), ("warm", 100_000, 1, True)])
+def test_closed_loop_start_near_the_end_of_time(rp, oracle, how, left, dur, fine, in_lds):
+    # delays that lead out of the int32 range: the replay is invalid (its cell cannot start), or the pool's container
+    # is not there any more
+    cfg, ev, gp = late_in_a_closed_loop(how, left, dur)
+    b = _tiny(cfg, ev, gp, [100000])
+    st, logs = gpu_run(rp, b, log=True, in_lds=in_lds)
+    if fine:
+        assert_same(rp, oracle, b, st, logs, check=True)
+        assert st["migrations"][0] == (2 if how == "warm" else 1)
+    else:
+        assert (st["status"] == rp.E_RANGE).all()
 
 
 def test_closed_loop_rejects_periodic_scaling_and_batch(rp):

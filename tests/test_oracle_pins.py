@@ -10,7 +10,7 @@ import os
 import numpy as np
 import pytest
 
-from helpers import code_of, digest_of, events_to_arrays, load_golden, GOLDEN
+from helpers import code_of, digest_of, events_to_arrays, late_in_a_closed_loop, load_golden, GOLDEN
 from paper_2503_20591_amd import tracegen as tg
 
 S, CELL, END = 0, 1, 2
@@ -859,3 +859,25 @@ def test_rejects_bad_input(oracle):
     assert rc(dict(BASE, gpus_per_host=9), [], []) == -1
     assert rc(dict(BASE, hosts_max=2), [], []) == -1
     assert rc(BASE, [], [], cap=0) == -1
+
+
+@pytest.mark.parametrize("how", ["migrate", "grow"])
+def test_closed_loop_start_beyond_the_time_range(oracle, how):
+    # the container start (600 s, or 601 s with the boot of a new host) ends in time, or not: then the replay is invalid,
+    # also where "now + delay" alone leaves the range
+    delay = 600_000 if how == "migrate" else 601_000
+    cfg, ev, gp = late_in_a_closed_loop(how, delay + 5_000, 4_999)
+    r = run(oracle, cfg, ev, gp, 100000)
+    assert r["t_end_ms"] == 2**31 - 2 and r["migrations"] == 1 and r["max_delay_ms"] == delay
+    for left, dur in ((delay + 5_000, 5_000), (delay + 1, 1), (delay, 1), (500_000, 1), (10_000, 1)):
+        cfg, ev, gp = late_in_a_closed_loop(how, left, dur)
+        with pytest.raises(ValueError) as e:
+            run(oracle, cfg, ev, gp, 100000)
+        assert e.value.args[1] == -2
+
+
+def test_closed_loop_container_beyond_the_time_range(oracle):
+    # the idle host's one pre-warmed container is used; its replacement would be there after the end of time
+    cfg, ev, gp = late_in_a_closed_loop("warm", 100_000)
+    r = run(oracle, cfg, ev, gp, 100000)
+    assert r["migrations"] == 2 and r["migrations_warm"] == 1 and r["max_delay_ms"] == 2_000
