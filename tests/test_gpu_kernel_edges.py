@@ -32,22 +32,58 @@ def test_batch_kernel_at_its_chunk_edges(rp, oracle, hosts, G, grow):  # noqa: F
     assert st["cells_queued"].max() > 0
 
 
+def on_a_grid(seed, hosts, sessions, step_ms, flags, caps):
+    """Every time of the trace is a multiple of ``step_ms``: the coarser, the more timers are due at one instant."""
+    on_grid = lambda v: np.maximum(v // step_ms, 1) * step_ms  # noqa: E731
+    tr = tg.make_trace(seed, sessions, sessions * 6, ramp_ms=300_000, gpus=lambda r, n: tg.gpus_uniform(r, n),
+                       gap=lambda r, s: on_grid(tg.exp_ms(r, 40.0, s)), dur=lambda r, s: on_grid(tg.lognormal_ms(r, 200.0, 1.0, s)),
+                       with_end=True)
+    tr = (tr[0] // step_ms * step_ms, *tr[1:])
+    return tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, flags=flags), [tr], [0] * len(caps), list(caps), "refill")
+
+
+def cell_timers_at_once(b, log):
+    """The most cells that timers of one instant have started or given up, by the decision log (a closed loop's cells all
+    come by timer, an open loop's if they do not arrive at that instant). All of these timers were pending before it."""
+    time, sess, what = log >> np.uint64(32), (log >> np.uint64(16)) & np.uint64(0xFFFF), (log >> np.uint64(12)) & np.uint64(15)
+    by_timer = np.isin(what, [4, 5, 6, 7, 12])
+    if not b.config["flags"] & tg.F_CLOSED_LOOP:
+        cell = b.ev_sk >> 24 == tg.EV_CELL
+        arrivals = b.ev_time[cell].astype(np.uint64) << np.uint64(16) | b.ev_sk[cell].astype(np.uint64) & np.uint64(0xFFFF)
+        by_timer &= ~np.isin(time << np.uint64(16) | sess, arrivals)
+    return int(np.unique(time[by_timer], return_counts=True)[1].max(initial=0))
+
+
 @pytest.mark.parametrize("closed", [False, True], ids=["open", "closed"])
 @pytest.mark.parametrize("hosts,sessions,step_ms", [(256, 1024, 1), (256, 1025, 1), (256, 1028, 1000), (257, 2049, 60_000),
                                                     (320, 4099, 1), (300, 3000, 600_000), (65, 1300, 1000)])
 def test_refill_of_the_sorted_timers(rp, oracle, hosts, sessions, step_ms, closed):  # noqa: F811
     # many more timers than the 64 sorted ones, alone in their millisecond or hundreds at one instant; the helper
     # waves take part in the scan from 256 hosts and more than 1,024 sessions on
-    on_grid = lambda v: np.maximum(v // step_ms, 1) * step_ms  # noqa: E731
-    tr = tg.make_trace(5, sessions, sessions * 6, ramp_ms=300_000, gpus=lambda r, n: tg.gpus_uniform(r, n),
-                       gap=lambda r, s: on_grid(tg.exp_ms(r, 40.0, s)), dur=lambda r, s: on_grid(tg.lognormal_ms(r, 200.0, 1.0, s)),
-                       with_end=True)
-    tr = (tr[0] // step_ms * step_ms, *tr[1:])
-    flags = tg.F_MIGRATE | (tg.F_CLOSED_LOOP if closed else 0)
-    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, flags=flags), [tr], [0, 0], [1500, 4000], "refill")
+    b = on_a_grid(5, hosts, sessions, step_ms, tg.F_MIGRATE | (tg.F_CLOSED_LOOP if closed else 0), [1500, 4000])
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
     assert closed or st["cells_queued"].max() > 64
+    # on the coarse grids more than 64 timers of one instant wait outside the 64 sorted ones
+    assert step_ms < 60_000 or max(cell_timers_at_once(b, log) for log in logs) > 128
+
+
+@pytest.mark.parametrize("hosts,sessions,step_ms,flags", [(64, 1200, 10_000, 0), (64, 1200, 10_000, tg.F_SCALE_IN), (8, 500, 10_000, tg.F_MIGRATE),
+                                                          (33, 700, 10_000, tg.F_MIGRATE), (64, 1200, 10_000, tg.F_MIGRATE),
+                                                          (33, 700, 600_000, tg.F_MIGRATE), (8, 300, 10_000, tg.F_MIGRATE | tg.F_SCALE_OUT),
+                                                          (64, 1200, 10_000, tg.F_MIGRATE | tg.F_SCALE_OUT)])
+def test_refill_of_one_instant_in_the_register_kernel(rp, oracle, hosts, sessions, step_ms, flags):  # noqa: F811
+    # retries fall on the grid of the trace (10 s apart): more than 64 timers of one instant wait in the session records,
+    # the earliest is taken alone, and timers pushed for that instant before it fires (an END deferred to a cell's finish,
+    # the retry of a session with a lower number) come before it or wait behind it. Each case on the 10 s grid was
+    # answered in another order while all such timers were left to wait.
+    b = on_a_grid(5, hosts, sessions, step_ms, flags, [4000, 20_000, 100_000])
+    if flags & tg.F_SCALE_OUT:
+        b.config["hosts_max"] = min(64, hosts + 6)
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert st["cells_queued"].max() > 64
+    assert step_ms < 60_000 or max(cell_timers_at_once(b, log) for log in logs) > 128
 
 
 @pytest.mark.parametrize("flags", [0, tg.F_MIGRATE, tg.F_MIGRATE | tg.F_SCALE_OUT, tg.F_MIGRATE | tg.F_STICKY_EXECUTOR],
