@@ -11,7 +11,9 @@ PROFILE_LIB = os.path.join(PKG, "libnbos_pathprofile.so")      # diagnostic buil
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-               # LDS counters are bumped by one lane on purpose; keep them single ds_add instructions
+               # all lanes take part in every LDS atomic (one instruction, no branch): without this the optimiser wraps the
+               # sums that several lanes bring to one counter in reductions over the wave (measured without it: 64 hosts
+               # 68.0 -> 74.7 ms, 30 hosts 28.0 -> 31.3, 24 hosts 47.3 -> 54.5, 300 short replays 0.84 -> 0.95)
                "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
                # a replay is one long dependent chain run by a lone wave: schedule for instruction-level
                # parallelism, not for occupancy (measured: c4 239 -> 230 ms, c3 101 -> 98.8 ms, c2 37.4 -> 36.9 ms)

@@ -205,7 +205,7 @@ struct nbos_replay {
   char kernel_name[96];    // as a profiler prints it, without the argument list
   nbos_stats *d_stats;
   nbos_bill *d_bill;
-  int32_t *d_ovf;          // open-loop replay kernels: durations of queued cells, [n_replays][n_cap]
+  int32_t *d_ovf;          // open-loop replay kernels: durations of queued cells, [n_replays][n_cap + 1]
   int32_t *d_order;        // the replay each workgroup of the launch runs
   int32_t *d_chain;        // closed loop only: the chain records of all events, then the cursors
   uint64_t *d_log;

@@ -46,7 +46,7 @@ def run_policies(batch: tg.TraceBatch, batch_start_delay_ms: int = 15_000,
     as_batch = _with_config(batch, flags=tg.F_BATCH_MODE | (batch.config["flags"] & tg.F_SCALE_OUT),
                                  batch_start_delay_ms=batch_start_delay_ms)
     # A study's replays leave most of the chip idle and last as long as their longest one, so the two policies run
-    # side by side, each on a stream of its own (20 replays of 60,000 cells each: 51.5 ms one after the other, 30.2 ms
+    # side by side, each on a stream of its own (20 replays of 60,000 cells each: 51.5 ms one after the other, 29.8 ms
     # side by side). Streams share four hardware queues, and one of the two would wait on the other's: two new streams
     # in a row have different ones but for one call in sixteen (31.4 ms on average), a new one and the current one but for
     # one in four (34.8). Both handles exist before either runs (making one waits for the device), and both are closed,
