@@ -12,8 +12,8 @@ namespace {
 // Where does a replay spend its time? The wave that runs the replay reads the cycle counter at the marks
 // below and adds the clocks since the previous mark to the category of the path just left (and a count);
 // the sums of every replay go to a device array that nbos_path_profile_read copies out. The marks cost
-// time of their own (two counter reads and two LDS atomics each), so a profiled launch runs about a tenth
-// longer; the shares are what it is for. In the product build every mark is empty.
+// time of their own (two counter reads and two LDS atomics each), so a profiled launch runs a fifth to
+// two fifths longer; the shares are what it is for. In the product build every mark is empty.
 #ifdef NBOS_PATH_PROFILE
 enum { PC_TILE, PC_ROUND, PC_ELECT, PC_MIGR, PC_FAIL, PC_START, PC_END, PC_TIMER_OTHER, PC_TICK, PC_RETRY_ELECT,
        PC_RETRY_MIGR, PC_RETRY_FAIL, PC_QUIET_RETRIES, PC_DROP, PC_LOOP_HORIZON, PC_LOOP_ROUND, PC_LOOP_TIMER,

@@ -30,7 +30,7 @@
 // the end after the last one.
 //
 // Bound by the latency of the serial chain of jobs (one wave per replay): about 200 instructions and six LDS
-// accesses per job on 512 hosts, 622 ns (256 replays of 250,000 jobs: 156 ms). The version before, whose jobs
+// accesses per job on 512 hosts, 608 ns (256 replays of 250,000 jobs: 152 ms). The version before, whose jobs
 // scanned the rows of every chunk that could take them, took 543 ms. Control flow is uniform throughout: a store
 // that one lane would do is done by all lanes (same value, same address), as an exec-masked region costs 40
 // clocks and makes the compiler rebuild the branches around it.

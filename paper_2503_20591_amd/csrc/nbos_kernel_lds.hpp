@@ -206,7 +206,7 @@ __device__ __forceinline__ uint32_t helper_result(const Ctx<F> &c, int w, int i)
 // times per lane are in flight while the current ones are looked at; a time inside the window is rare (one or two
 // in a block), so only the words that have one are staged. Bound by the latency of the scan, once per about 40 timers:
 // with one wave and all four words of a block staged, a refill over 8,000 sessions took 26,000 clocks, 30 % of the
-// closed loops on 512 to 768 hosts (256 replays of 250,000 cells: 181.5 ms; now 129.0).
+// closed loops on 512 to 768 hosts (256 replays of 250,000 cells: 181.5 ms, and 129.0 with this).
 template <uint32_t F>
 __device__ __forceinline__ int refill_part(const Ctx<F> &c, int32_t T, int first, int stride, int32_t &staged, int32_t &left) {
   const int4 *due4 = (const int4 *)c.m.due;
