@@ -88,6 +88,8 @@ MUTANTS = [
     ("warm pool: refilled at once", "d->warm[w] = m->clock + m->p->prewarm_delay_ms;", ""),
     ("warm pool: an added host is warm from the start", "m->hosts[h].warm[i] = m->hosts[h].ready_at + m->p->prewarm_delay_ms;", "m->hosts[h].warm[i] = 0;"),
     ("warm pool: container available exactly now is not taken", "if (d->warm[w] <= m->clock) {", "if (d->warm[w] < m->clock) {"),
+    ("closed loop: a start beyond the time range wraps", "int64_t start, int outcome) {", "int32_t start, int outcome) {"),
+    ("warm pool: a container beyond the time range wraps", "  int64_t warm[4];", "  int32_t warm[4];"),
     ("warm pool: warm start pays the cold delay", "m->clock + m->p->warm_migration_delay_ms, ORC_D_MIGRATE_WARM", "m->clock + m->p->migration_delay_ms, ORC_D_MIGRATE_WARM"),
     ("warm pool: only one container per host", "for (int i = 1; i < m->p->warm_pool_per_host; i++)", "for (int i = 1; i < 1; i++)"),
     ("closed loop: think measured from the previous event's start", "anchor[s] = kind == ORC_EV_CELL ? ev_time[i] + ev_dur[i] : ev_time[i];", "anchor[s] = ev_time[i];"),
@@ -158,6 +160,8 @@ def run_pins(lib_path):
     checks += [lambda s=s: pins.test_closed_loop_without_waiting_is_the_open_loop(o, s) for s in range(3)]
     checks += [lambda s=s: pins.test_closed_loop_schedule_from_the_log(o, s) for s in range(5)]
     checks += [lambda s=s: pins.test_closed_loop_never_meets_a_busy_session(o, s) for s in range(4)]
+    checks += [lambda h=h: pins.test_closed_loop_start_beyond_the_time_range(o, h) for h in ("migrate", "grow")]
+    checks.append(lambda: pins.test_closed_loop_container_beyond_the_time_range(o))
     checks += [lambda s=s: pins.test_warm_pool_that_refills_at_once_is_a_shorter_delay(o, s) for s in range(3)]
     checks += [lambda: pins.test_batch_single_server_is_the_textbook_fifo_queue(o), lambda: pins.test_batch_without_contention(o)]
     checks += [lambda s=s: pins.test_batch_order_and_capacity_random(o, s) for s in range(6)]
