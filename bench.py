@@ -23,7 +23,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, published
-GPU_BOX_CPU_SHARE = 16    # host threads one GPU's share of the box allows
+CPU_THREADS_PER_GPU = 16  # host threads that go with one GPU of the machine
 
 
 COMPUTE_UNITS = 256       # MI355X
@@ -107,8 +107,8 @@ def cpu_baseline(batch, budget_s: float, threads: int):
             "sample": f"{n} of {batch.n_replays} replays of {batch.name}, evenly spaced, "
                       f"{threads} thread(s), {dt:.1f} s",
             "host_cpus": os.cpu_count(), "cpu_model": cpu_model(),
-            "threads_note": f"{threads} = min(hardware threads of the host, {GPU_BOX_CPU_SHARE}: the share of the "
-                            f"box that goes with one GPU)",
+            "threads_note": f"{threads} = min(hardware threads of the host, {CPU_THREADS_PER_GPU}: the share of the "
+                            f"machine that goes with one GPU)",
             "one_core": {"value": v1, "unit": unit, "cores": 1,
                          "sample": f"first {n1} of {batch.n_replays} replays of {batch.name}, 1 thread, {dt1:.1f} s; "
                                    f"the whole batch would take {dt1 / n1 * batch.n_replays:.1f} s at this rate"}}
@@ -157,7 +157,7 @@ def main():
     replay.load()
     assert torch.cuda.is_available(), "bench.py needs a GPU"
 
-    threads = args.cpu_threads or min(GPU_BOX_CPU_SHARE, os.cpu_count() or 1)
+    threads = args.cpu_threads or min(CPU_THREADS_PER_GPU, os.cpu_count() or 1)
     t0 = time.perf_counter()
     batch = tracegen.workload(args.workload, n_replays=args.replays, workers=threads)
     t_gen = time.perf_counter() - t0

@@ -77,7 +77,7 @@ def test_create_rejects_bad_config(lib, bad):
 
 def test_create_accepts_the_base_config_as_far_as_the_host_checks_go(lib):
     # the same call with nothing wrong gets past the parameter checks: it fails only for want of a
-    # device (here), or succeeds (on a GPU machine)
+    # device (here), or succeeds (where there is a GPU)
     c = replay.make_config(_cfg(), 0, 1)
     ins = replay.NbosInputs()
     h = C.c_void_p()
