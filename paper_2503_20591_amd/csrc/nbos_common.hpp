@@ -72,7 +72,7 @@ struct KParams {
   int32_t batch_delay;     // Batch baseline: container start per job
   int32_t warm_n, warm_migr, prewarm;   // pre-warmed containers per host, warm migration delay, pre-warm time
   int32_t n_cap;           // LDS capacity: sessions
-  int32_t batch;           // event-parallel rounds on (LDS kernel)
+  int32_t batch;           // event-parallel rounds on (LDS kernel); Batch kernel: its list of completions is there
   // closed loop only. cl_chain: per event of the traces {the next event of its session (index within
   // the trace, -1: none), the think time before that event}; the second word is -1 for an event no
   // chain holds. cl_cursor: per replay and session the event that is due next or under way.
@@ -104,6 +104,11 @@ __device__ __forceinline__ void refuse_replay(const KParams &p, int rep, int lan
 __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ int32_t lane_get(int32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
+// v with lane l mod 64 holding x (v_writelane_b32; clang has no builtin for it)
+extern "C" __device__ __attribute__((const)) int nbos_writelane(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t lane_set(uint32_t v, uint32_t l, uint32_t x) {
+  return (uint32_t)nbos_writelane((int)x, (int)l, (int)v);
+}
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
@@ -324,6 +329,45 @@ __device__ __forceinline__ uint64_t decision_code(int32_t now, uint32_t outcome,
                                                   uint32_t host) {
   return (uint64_t)(host | (slot << 10) | (outcome << 12) | (s << 16)) | ((uint64_t)(uint32_t)now << 32);
 }
+// Sum of a 64-bit value over the wave, wave-uniform (four DPP steps make the sum of every row of 16 lanes, the four
+// rows are added on the scalar unit)
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+  return ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t lane_get64(uint64_t v, int l) {
+  return ((uint64_t)(uint32_t)lane_get((int)(uint32_t)(v >> 32), l) << 32) | (uint32_t)lane_get((int)(uint32_t)v, l);
+}
+__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
+  v += dpp64<0xB1>(v);
+  v += dpp64<0x4E>(v);
+  v += dpp64<0x141>(v);
+  v += dpp64<0x140>(v);
+  return lane_get64(v, 0) + lane_get64(v, 16) + lane_get64(v, 32) + lane_get64(v, 48);
+}
+
+// The digest of many decisions at once: the codes of the lanes of `mask`, in the order of the lanes, are
+// digest * P^n + sum over i of code_i * P^(n-1-i), every lane its own term. (On the scalar unit a decision is a 64-bit
+// multiplication and an addition, a dozen instructions of the serial chain; here the multiplications of up to 64 are one.)
+// power: per lane P^(63 - lane), see digest_powers.
+__device__ __forceinline__ uint64_t digest_powers(int lane) {
+  uint64_t power = 1, square = DIGEST_PRIME;
+#pragma unroll
+  for (int b = 0; b < 6; b++, square *= square) power *= ((63 - lane) >> b) & 1 ? square : 1ull;
+  return power;
+}
+__device__ __forceinline__ uint64_t fold_decisions(uint64_t digest, uint64_t power, uint64_t mask, uint32_t code_lo, uint32_t code_hi) {
+  const int n = __builtin_popcountll(mask);
+  if (n == 0) return digest;
+  // the factor P^(n-1-i) is held by lane i + 64 - n
+  const int at = ((lane_rank(mask) + WAVE - n) & (WAVE - 1)) << 2;
+  const uint32_t pl = (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)(uint32_t)power);
+  const uint32_t ph = (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)(uint32_t)(power >> 32));
+  const uint32_t lo = in_mask(mask) ? code_lo : 0u, hi = in_mask(mask) ? code_hi : 0u;
+  const uint64_t sum = wave_sum64((((uint64_t)hi << 32) | lo) * (((uint64_t)ph << 32) | pl));
+  return digest * (lane_get64(power, WAVE - n) * DIGEST_PRIME) + sum;
+}
+
 template <class C, class R>
 __device__ __forceinline__ void decide(C &c, R &r, int32_t now, uint32_t outcome, uint32_t s, uint32_t slot,
                                        uint32_t host) {

@@ -2,247 +2,382 @@
 // own, first come first served, a container per job. One workgroup (one wave64) per replay, any cluster
 // size up to NBOS_MAX_HOSTS.
 //
-// fin[h][8] in LDS: the "busy until" times of host h's GPUs, one row of 32 bytes per host, sorted ascending; slots
-// beyond G hold NEVER. A GPU is held at time t iff fin > t; the host has g idle GPUs from fin[g-1] on. A host
-// that is off holds NEVER everywhere, one that is being provisioned its ready time in all G slots: it has
-// no idle GPU before it is ready, and needs no other mark.
-// In registers, lane l and chunk j (j < NCH) for host h = 64 j + l:
-//   key[j]  (slots with fin > T) << 10 | h at the time T of the last look; slots beyond G count too (the
-//           same number on every host)
-//   nx[j]   the earliest fin beyond that T: key[j] is good until then
-// A job takes the ready host with the fewest held GPUs (ties: lowest index), i.e. the smallest key, and
-// fits there or nowhere: its GPUs are idle iff (key >> 10) + g <= 8. So one minimum over the keys answers
-// both questions, and a look at time T first brings those keys up to date whose nx has passed (the hosts of
-// a completion or two per job). Allocating the g GPUs that have been free longest on a sorted row is one
-// median per slot, lane = slot: new[k] = median(old[k], finish, old[k + g]).
-// Sessions in LDS, 8 bytes each: time (busy until, or submit time while the job waits in the queue), and
-// duration | (g - 1) << 27 | waiting. fifo: ring of waiting jobs (16-bit session ids), at most one per session.
+// Hosts: a bitmap per number of held GPUs ("level"; slots beyond G count as held, hosts that are off or being provisioned
+// as full), 64 hosts to a word, level 8 left out: lane 8 l + w holds the word of hosts 64 w .. 64 w + 63 on level l,
+// for each set of 512 hosts (NS of them) a pair of registers. A job takes the ready host with the fewest held GPUs (ties:
+// lowest index): the first bit of the first lane that has one, found by two bit scans, and it fits there or nowhere.
+// A job or a completion flips one bit in each of two lanes.
+// Completions: the earliest ones, in the order of their times, in registers (qt, qk: entry i in lane i, qe of them,
+// at most 63): all running jobs that finish up to win_t. With more than MID_CAP sessions (p.batch) those that
+// finish up to mid_t are in a list in LDS as well (mid_t[], mid_k[], in no order), the others are found in the session
+// records only: a refill of the registers looks through a few hundred of the list, once per about 40 jobs, and the
+// list is made anew from all records once per few hundred.
+// Hosts being provisioned come up in the order of their index (all take the same time): next_up, ready[].
+// Sessions in LDS: time[] and meta[] of the latest job: finish, host | (g - 1) << 27.
 //
-// The CPU reference runs completions and "host ready" as timers and looks at the queue after each
-// instant. Here nothing is queued as a timer. The job at the head of the queue first meets the scheduler
-// at T0 = max(its submit time, the time the previous head got its GPUs). If some ready host has g idle
-// GPUs at T0 it starts there. Otherwise nothing is allocated until it starts (it blocks the queue), so
-// the busy-until times do not change while it waits and the instant it starts is known in closed form:
-// E = min over hosts of f[g-1], which is the time of a completion or of a host turning ready, i.e. an
-// instant at which the reference serves the queue. A GPU with f <= E is free at E exactly when the
-// reference has applied every completion of that instant. The queue is advanced up to the time of each
-// arriving event before the event is looked at (timers due at or before an arrival run before it), and to
-// the end after the last one.
+// The CPU reference keeps a queue, runs completions and "host ready" as timers and looks at the queue after each
+// instant. First come, first served means that jobs start in the order in which they arrive, so a job can be followed to
+// its start before the next arrival is looked at: it first meets the scheduler at T0 = max(its arrival, the start of the
+// job before it), with everything applied that happens to the hosts up to T0. It starts there if a host has the GPUs
+// idle; else nothing starts until it does, it asks for one more host (once), and starts at the first instant
+// after which a host has them. An arrival is dropped if its session's previous job finishes later than that, and
+// that job's start is known by then. There is no queue.
 //
-// Bound by the latency of the serial chain of jobs (one wave per replay): about 200 instructions and six LDS
-// accesses per job on 512 hosts, 608 ns (256 replays of 250,000 jobs: 152 ms). The version before, whose jobs
-// scanned the rows of every chunk that could take them, took 543 ms. Control flow is uniform throughout: a store
-// that one lane would do is done by all lanes (same value, same address), as an exec-masked region costs 40
-// clocks and makes the compiler rebuild the branches around it.
+// Bound by the latency of the serial chain of jobs (one wave per replay). On a lone wave an instruction takes 5 clocks, a
+// scalar one that reads what the vector side has just produced 20 more, a branch 12 to 25: hence bit scans where
+// a minimum over the keys of all hosts was taken (and the rows of the hosts with a completion read again to refresh
+// them); a job leaves its start and host in its lane, and records, sums, waits and digest are made from those for 64 jobs
+// at a time. 512 hosts, 250,000 jobs, 256 replays: 152.4 ms with a key per host, a minimum over the keys and the queue, 88.2
+// with this; of it 60 % the loop of jobs that start at once (570 clocks per job and completion), 18 % refills.
+// Control flow is uniform throughout: a store that one lane would do is done by all lanes.
 #pragma once
 #include "nbos_common.hpp"
 
 namespace {
 namespace batchk {
 
-constexpr int32_t WAITING = 1 << 30;
 constexpr int G_SHIFT = 27;
-constexpr int32_t DUR_MASK = (1 << G_SHIFT) - 1;      // a duration is at most NBOS_MAX_DUR_MS < 2^27
+constexpr uint32_t HOST_MASK = 1023u;
+constexpr int Q_CAP = WAVE - 1;                       // completions in registers: lane 63 holds NEVER
+constexpr uint32_t SLOW = 1u << 31;                   // (of an arrival) an earlier arrival of its session is in the tile
+constexpr int32_t ALL = NEVER - 1;                    // win_t when no running job is left out
+constexpr int MID_CAP = 512;                          // jobs in the list in LDS
 
 struct Lds {
-  int32_t *fin;
   uint32_t *hist;               // 32 bins, and behind them a word per lane for the lanes that an LDS atomic is not for
-  int2 *sess;
-  uint16_t *fifo;
+  int32_t *stage_t;             // [WAVE + 4] completions on their way into the registers; one place for lanes with none
+  uint32_t *stage_k;
+  int32_t *time;
+  uint32_t *meta;
+  int32_t *mid_t;               // [MID_CAP + 4] finish and meta word of the jobs in the list
+  uint32_t *mid_k;
+  int32_t *ready;               // [hosts] when a host that was added comes up
 };
 
-template <int NCH>
+template <int NS>
 struct Ctx {
   const KParams &p;
   Lds m;
   int lane;
-  int own_slot;                 // -1 in lane 0, elsewhere the lane's own word behind the histogram
-  int ring;                     // ring capacity
-  uint64_t *dlog;
-  uint32_t key[NCH];
-  int32_t nx[NCH];
-  uint32_t vsid;                // session of this lane's event in the current tile (~0 if none)
-  int32_t w_s, w_t, w_d;        // jobs read ahead from the queue, one per lane: session, its record
+  int n_sess;
+  int mid_sink;                 // a word of the list in LDS that nobody reads
+  uint32_t lo[NS], hi[NS];      // the levels, see above
+  int32_t qt;                   // completions: finish,
+  uint32_t qk;                  // and the session's meta word
+  // the tile of events: arrival, container start + duration, session | (g - 1) << 16 | SLOW; and of the jobs that
+  // have started: when, where
+  int32_t vt, vfd;
+  uint32_t vjob;
+  int32_t vstart;
+  uint32_t vhost;
+  uint64_t power;               // see digest_powers
 };
 
-// (status is only ever set by a select: a conditional store to it next to one to head_E is merged into one store
-// through a chosen pointer, which puts both into memory and every value that depends on them into vector registers)
 struct State {
-  uint32_t n_dec, c_total, c_started, c_imm, c_busy;
-  int64_t sum_dur, g_exec, sum_g, sum_wait, prov;
+  uint32_t c_total, c_started, c_imm, c_busy, n_dec;
+  int32_t qe, q_t;              // completions: how many, the next one's time (NEVER: none listed)
+  uint32_t q_k;                 // ... and meta word
+  int32_t win_t, win;           // all that finish up to win_t are listed; the window the next refill takes
+  int32_t mid_t, mid_n;         // the list in LDS: all that finish up to mid_t >= win_t (with few sessions: win_t, and all of them)
+  int32_t mid_win;
+  int32_t next_up, up_t;        // the next host to come up and when (NEVER: none is being provisioned)
+  int32_t n_on;
+  int32_t now;                  // when the latest job started; the hosts have been advanced at least to there
+  // a job that has started, finishes within the lists' windows and finds no room there (p_f < 0: none)
+  int32_t p_f;
+  uint32_t p_k;
+  uint64_t todo;                // arrivals of the tile that are still to come,
+  uint64_t unsaved;             // ... and those that were when the records were last written
+  uint64_t started, folded;     // jobs of the tile whose records are written; whose decisions are in the digest
   uint64_t digest;
-  uint64_t dirty;               // lanes of the current tile whose prefetched record is stale
-  int32_t q_head, q_n;          // ring: index of the head, jobs waiting (the head included)
-  int32_t w_at, w_n;            // jobs read ahead: the next one, how many
-  int32_t h_s, h_t, h_dur, h_g; // the head of the queue
-  int32_t head_T;               // when the head looks for a host next: as it becomes the head, or once a host can
-                                // give it its GPUs (NEVER: the queue is empty)
-  int32_t last_T;               // when the last job got its GPUs
-  int32_t n_on, max_wait;
-  int32_t lazy_max, t_end;
+  int64_t prov;
+  int32_t latest_up, t_end;
   int32_t status;               // NBOS_OK, or NBOS_E_RANGE once a time leaves the int32 range
 };
 
-template <class C>
-__device__ __forceinline__ void decide(C &c, State &r, int32_t now, uint32_t outcome, uint32_t s, uint32_t host) {
-  const uint64_t code = decision_code(now, outcome, s, 0u, host);
+// the host (set, word, bit) that the lanes of `flip` stand for moves between the levels of those lanes
+template <int NS>
+__device__ __forceinline__ void flip_host(Ctx<NS> &c, uint64_t flip, uint32_t h) {
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    const uint64_t here = NS == 1 || (int)(h >> 9) == s ? flip : 0ull;
+    const uint64_t bit = (uint64_t)(in_mask(here) ? 1u : 0u) << (h & 63u);
+    c.lo[s] ^= (uint32_t)bit;
+    c.hi[s] ^= (uint32_t)(bit >> 32);
+  }
+}
+
+// the g GPUs that a job held on host h are idle again (a host that comes up: all G); returns the host's lane from now on
+template <int NS>
+__device__ __forceinline__ int give_back(Ctx<NS> &c, uint32_t h, int g) {
+  const uint32_t w = (h >> 6) & 7u;
+  uint32_t lo = c.lo[0], hi = c.hi[0];
+  if constexpr (NS == 2) { lo = h >> 9 ? c.lo[1] : lo; hi = h >> 9 ? c.hi[1] : hi; }
+  const uint32_t there = (uint32_t)((((uint64_t)hi << 32) | lo) >> (h & 63u)) & 1u;
+  const uint64_t from = wballot(there != 0u) & (0x0101010101010101ull << w);      // no lane: the host was full
+  const uint64_t full = from == 0 ? 1ull << w : 0ull;          // (g = 8 is a full host: then `from` is 0)
+  const uint64_t to = (from >> (8 * (g & 7))) | (full << ((64 - 8 * g) & 63));
+  flip_host(c, from | to, h);
+  return (int)__builtin_ctzll(to);
+}
+
+// nothing happens to the hosts before this time
+__device__ __forceinline__ int32_t due_time(const State &r) { return min(min(r.q_t, r.up_t), r.win_t + 1); }
+
+// Which of the n times at `times` lie in [from, from + win]? They and their keys come to lie side by side in stage_t and
+// stage_k (the first 64); returned are how many there are, and the earliest time beyond (as a distance from `from`; 2^31
+// or more: none). Times before `from` wrap to large distances. Both arrays are read four at a time.
+template <int NS>
+__device__ __forceinline__ int scan_window(const Ctx<NS> &c, const int32_t *times, const uint32_t *keys, int n, int32_t from, uint32_t win, uint32_t &left) {
+  const int4 *time4 = (const int4 *)times, *key4 = (const int4 *)keys;
+  int cnt = 0;
+  uint32_t mn = 0xFFFFFFFFu;
+  for (int q0 = 0; 4 * q0 < n; q0 += WAVE) {
+    const int q = q0 + c.lane, at = min(q, (n - 1) >> 2);
+    const int4 d = time4[at], e = key4[at];
+    const int32_t t[4] = {d.x, d.y, d.z, d.w}, k[4] = {e.x, e.y, e.z, e.w};
+    uint64_t b[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const uint32_t x = (uint32_t)t[j] - (uint32_t)from;
+      const bool in = 4 * q + j < n, hit = in & (x <= win);
+      b[j] = wballot(hit);
+      mn = in & !hit ? umin(mn, x) : mn;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int to = min(cnt + lane_rank(b[j]), WAVE), place = in_mask(b[j]) ? to : WAVE;
+      c.m.stage_t[place] = t[j];
+      c.m.stage_k[place] = (uint32_t)k[j];
+      cnt += __builtin_popcountll(b[j]);
+    }
+  }
+  left = wave_min(mn);
+  return cnt;
+}
+
+// The list in LDS anew: the running jobs that finish within a window from `from` on, at most MID_CAP (the window adapts
+// to find 192 to 384); more at one instant: none, and the registers are refilled from the records.
+template <int NS>
+__device__ __forceinline__ void list_jobs(Ctx<NS> &c, State &r, int32_t from) {
+  const int4 *time4 = (const int4 *)c.m.time, *key4 = (const int4 *)c.m.meta;
+  const int quads = (c.n_sess + 3) >> 2;
+  uint32_t win = (uint32_t)r.mid_win;
+  int cnt;
+  uint32_t left;
+  for (;;) {
+    win = umin(win, (uint32_t)(ALL - from));
+    cnt = 0;
+    uint32_t mn = 0xFFFFFFFFu;
+    int4 next = time4[min(c.lane, quads - 1)], next_k = key4[min(c.lane, quads - 1)];
+    for (int q0 = 0; q0 < quads; q0 += WAVE) {
+      const int q = q0 + c.lane;
+      const int4 d = next, e = next_k;
+      next = time4[min(q + WAVE, quads - 1)]; next_k = key4[min(q + WAVE, quads - 1)];
+      const bool in = q < quads;                       // (the places beyond the last session hold time 0, which is before `from`)
+      const int32_t t[4] = {d.x, d.y, d.z, d.w}, k[4] = {e.x, e.y, e.z, e.w};
+      uint64_t b[4];
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const uint32_t x = (uint32_t)t[j] - (uint32_t)from;
+        b[j] = wballot(in & (x <= win));
+        mn = in & (x > win) ? umin(mn, x) : mn;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int to = min(cnt + lane_rank(b[j]), MID_CAP), place = in_mask(b[j]) ? to : MID_CAP;
+        c.m.mid_t[place] = t[j];
+        c.m.mid_k[place] = (uint32_t)k[j];
+        cnt += __builtin_popcountll(b[j]);
+      }
+    }
+    left = wave_min(mn);
+    if (cnt == 0 && left < 0x80000000u) { from += (int32_t)left; continue; }
+    if (cnt <= MID_CAP) break;
+    if (win == 0) break;
+    win = (uint32_t)((uint64_t)win * 300u / (uint32_t)cnt);
+  }
+  wave_sync();
+  r.mid_n = cnt <= MID_CAP ? cnt : 0;
+  r.mid_t = cnt > MID_CAP ? from - 1 : left < 0x80000000u ? from + (int32_t)win : ALL;
+  r.mid_win = cnt < MID_CAP * 3 / 8 ? (int32_t)umin(win + (win + 1) / 2 + 1, 1u << 26) : cnt > MID_CAP * 3 / 4 ? (int32_t)(win - win / 4) : (int32_t)win;
+}
+
+// The list in the registers is empty and time goes on beyond win_t, at most to t: the completions of the next window come in.
+// More than fit into the registers at one instant: they are all applied at once if they are due at t, or left until they are.
+template <int NS>
+__device__ __forceinline__ void refill(Ctx<NS> &c, State &r, int32_t t) {
+  wave_sync();
+  const bool few = c.p.batch == 0;
+  int32_t from = r.win_t + 1;
+  uint32_t win = (uint32_t)r.win, left, most;
+  int cnt;
+  r.qe = 0; r.q_t = NEVER;
+  c.qt = NEVER;
+  for (;;) {
+    const int32_t *times = c.m.time;
+    const uint32_t *keys = c.m.meta;
+    int n = c.n_sess;
+    most = (uint32_t)(ALL - from);            // (from <= ALL: a finish is below NEVER)
+    if (!few) {
+      if (r.mid_t < from) list_jobs(c, r, from);
+      if (r.mid_t >= from) { times = c.m.mid_t; keys = c.m.mid_k; n = r.mid_n; most = (uint32_t)(r.mid_t - from); }
+    }
+    win = umin(win, most);
+    cnt = scan_window(c, times, keys, n, from, win, left);
+    if (cnt == 0) {
+      from += left < 0x80000000u ? (int32_t)left : (int32_t)most + 1;      // nothing (listed) up to there
+      if (from > ALL) { r.win_t = ALL; r.mid_t = few ? ALL : r.mid_t; return; }
+      continue;
+    }
+    if (cnt <= Q_CAP) break;
+    if (win == 0) {
+      const bool now = t >= from;
+      r.win_t = now ? from : from - 1;
+      r.mid_t = max(r.mid_t, r.win_t);
+      if (!now) return;
+      for (int s0 = 0; s0 < c.n_sess; s0 += WAVE) {
+        const int s = min(s0 + c.lane, c.n_sess - 1);
+        const uint32_t k = c.m.meta[s];
+        for (uint64_t w = wballot((s0 + c.lane < c.n_sess) & (c.m.time[s] == from)); w != 0; w &= w - 1) {
+          const uint32_t one = (uint32_t)lane_get((int)k, (int)__builtin_ctzll(w));
+          give_back(c, one & HOST_MASK, (int)((one >> G_SHIFT) & 7u) + 1);
+        }
+      }
+      return;
+    }
+    win = (uint32_t)((uint64_t)win * 40u / (uint32_t)cnt);
+  }
+  r.win_t = from + (int32_t)win;
+  r.mid_t = max(r.mid_t, r.win_t);
+  // (a window cut short by the end of the list says nothing about the next one)
+  if (cnt > 7 * WAVE / 8) r.win = (int32_t)(win - win / 4);
+  else if (cnt < WAVE / 2 && (int32_t)win == r.win) r.win = (int32_t)umin(win + (win + 1) / 2 + 1, 1u << 26);
+  else if (win < most) r.win = (int32_t)win;
+  wave_sync();
+  const bool take = c.lane < cnt;
+  const int32_t f = c.m.stage_t[c.lane], t_own = take ? f : NEVER;
+  const uint32_t k = c.m.stage_k[c.lane];
+  const int rank = timer_ranks(c.lane, cnt, t_own, (uint32_t)c.lane);
+  const int dst = (take ? rank : c.lane) << 2;
+  c.qt = __builtin_amdgcn_ds_permute(dst, t_own);
+  c.qk = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)k);
+  r.qe = cnt;
+  r.q_t = lane_get(c.qt, 0); r.q_k = (uint32_t)lane_get((int)c.qk, 0);
+}
+
+// a job that finishes at f goes into the list in the registers (there is room)
+template <int NS>
+__device__ __forceinline__ void insert_completion(Ctx<NS> &c, State &r, int32_t f, uint32_t k) {
+  const int pos = __builtin_popcountll(wballot(c.qt <= f));
+  const int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x138, 0xF, 0xF, false);          // wave_shr:1
+  const uint32_t sk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x138, 0xF, 0xF, false);
+  const bool up = c.lane > pos, here = c.lane == pos;
+  c.qt = here ? f : up ? st : c.qt;
+  c.qk = here ? k : up ? sk : c.qk;
+  r.qe++;
+  r.q_t = lane_get(c.qt, 0); r.q_k = (uint32_t)lane_get((int)c.qk, 0);
+}
+
+// The job that has started finishes at p_f <= mid_t, and there was no room where that belongs: the list in LDS is given
+// up, or (if the registers are still full) the latest instant in the registers, and that list with it.
+template <int NS>
+__device__ __forceinline__ void make_room(Ctx<NS> &c, State &r) {
+  const int32_t f = r.p_f;
+  r.p_f = -1;
+  if (f <= r.win_t) {
+    if (r.qe == Q_CAP) {
+      const int32_t last = lane_get(c.qt, Q_CAP - 1);
+      r.qe = __builtin_popcountll(wballot(c.qt < last));
+      c.qt = c.lane < r.qe ? c.qt : NEVER;
+      r.q_t = lane_get(c.qt, 0);
+      r.win_t = last - 1;
+      r.mid_t = r.win_t;
+    }
+    if (f <= r.win_t) insert_completion(c, r, f, r.p_k);
+  } else {
+    r.mid_t = r.win_t;
+  }
+}
+
+// the next completion leaves the list
+template <int NS>
+__device__ __forceinline__ void pop_completion(Ctx<NS> &c, State &r) {
+  c.qt = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);                // wave_shl:1
+  c.qk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x130, 0xF, 0xF, false);
+  r.qe--;
+  r.q_t = lane_get(c.qt, 0); r.q_k = (uint32_t)lane_get((int)c.qk, 0);
+}
+
+// The ready host with the fewest held GPUs, lowest index first: its lane (8 level + word; 64: all are full).
+// The choice of the set comes back in `set`.
+template <int NS>
+__device__ __forceinline__ int best_lane(const Ctx<NS> &c, int &set) {
+  const uint64_t a = wballot((c.lo[0] | c.hi[0]) != 0u);
+  int L = a != 0 ? (int)__builtin_ctzll(a) : WAVE;
+  set = 0;
+  if constexpr (NS == 2) {
+    const uint64_t b = wballot((c.lo[1] | c.hi[1]) != 0u);
+    const int L1 = b != 0 ? (int)__builtin_ctzll(b) : WAVE;
+    set = (L1 >> 3) < (L >> 3) ? 1 : 0;
+    L = set ? L1 : L;
+  }
+  return L;
+}
+__device__ __forceinline__ bool fits(int L, int g) { return (L >> 3) + g <= NGPU; }
+
+// The records of the tile's jobs that have started since this was last done (before anyone looks at the records: a refill,
+// a second arrival of a session in the tile, the next tile).
+template <int NS>
+__device__ __forceinline__ void save_records(Ctx<NS> &c, State &r) {
+  const uint64_t jobs = r.unsaved & ~r.todo;
+  wave_sync();
+  const bool mine = in_mask(jobs);
+  const int s = (int)(c.vjob & 0xFFFFu);
+  *(mine ? &c.m.time[s] : c.m.stage_t + WAVE) = c.vstart + c.vfd;
+  *(mine ? &c.m.meta[s] : c.m.stage_k + WAVE) = c.vhost | (((c.vjob >> 16) & 7u) << G_SHIFT);
+  r.started |= jobs;
+  r.unsaved = r.todo;
+}
+
+// The decisions of the tile's jobs in `jobs` go into the digest (they are the latest ones), and into the log.
+template <int NS>
+__device__ __forceinline__ void fold_jobs(Ctx<NS> &c, State &r, uint64_t *dlog, uint64_t jobs) {
+  const uint32_t lo = c.vhost | ((uint32_t)NBOS_D_BATCH_START << 12) | (c.vjob << 16);
+  r.digest = fold_decisions(r.digest, c.power, jobs, lo, (uint32_t)c.vstart);
+  if (__builtin_expect(dlog != nullptr, 0)) {
+    int64_t at = (int64_t)r.n_dec;
+    for (uint64_t w = jobs; w != 0; w &= w - 1, at++) {
+      const int j = (int)__builtin_ctzll(w);
+      const uint64_t code = ((uint64_t)(uint32_t)lane_get(c.vstart, j) << 32) | (uint32_t)lane_get((int)lo, j);
+      if (at < c.p.dlog_stride) dlog[at] = code;
+    }
+  }
+  r.n_dec += (uint32_t)__builtin_popcountll(jobs);
+  r.folded |= jobs;
+}
+
+// the job of session s finds no host at time T: it asks for one more host
+template <int NS>
+__device__ __forceinline__ void ask_for_host(Ctx<NS> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
+  if (!(c.p.flags & NBOS_F_SCALE_OUT) || r.n_on >= c.p.Hmax) return;
+  const int64_t up = (int64_t)T + c.p.boot;
+  r.status = up >= 0x7FFFFFFFLL ? (int32_t)NBOS_E_RANGE : r.status;
+  const int h = r.n_on++;                              // hosts are added in order and never go
+  r.prov -= (int64_t)c.p.G * T;
+  c.m.ready[h] = (int32_t)up;
+  r.up_t = r.next_up == h ? (int32_t)up : r.up_t;
+  r.latest_up = max(r.latest_up, (int32_t)up);
+  fold_jobs(c, r, dlog, (r.started | (r.unsaved & ~r.todo)) & ~r.folded);
+  const uint64_t code = decision_code(T, NBOS_D_BATCH_HOST, s, 0u, (uint32_t)h);
   r.digest = r.digest * DIGEST_PRIME + code;
-  if (__builtin_expect(c.dlog != nullptr, 0)) {
-    if ((int64_t)r.n_dec < c.p.dlog_stride) c.dlog[r.n_dec] = code;
+  if (__builtin_expect(dlog != nullptr, 0)) {
+    if ((int64_t)r.n_dec < c.p.dlog_stride) dlog[r.n_dec] = code;
   }
   r.n_dec++;
 }
 
-// smallest key at time T: the host that takes the next job, if that fits (see fits)
-template <int NCH>
-__device__ __forceinline__ uint32_t best_host(Ctx<NCH> &c, int32_t T) {
-  int32_t soonest = c.nx[0];
-#pragma unroll
-  for (int j = 1; j < NCH; j++) soonest = min(soonest, c.nx[j]);
-  if (wballot(soonest <= T) != 0) {
-    wave_sync();
-#pragma unroll
-    for (int j = 0; j < NCH; j++) {
-      if (__builtin_expect(wballot(c.nx[j] <= T) != 0, 0)) {      // (the chunk's other keys come out as they were)
-        const int4 *row = (const int4 *)(c.m.fin + NGPU * (j * WAVE + c.lane));
-        const int4 a = row[0], b = row[1];
-        const int32_t f[NGPU] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        uint32_t held = 0;
-        int32_t next = NEVER;
-#pragma unroll
-        for (int k = NGPU - 1; k >= 0; k--) {
-          held += f[k] > T ? 1u : 0u;
-          next = f[k] > T ? f[k] : next;
-        }
-        c.key[j] = (held << 10) | (uint32_t)(j * WAVE + c.lane);
-        c.nx[j] = next;
-      }
-    }
-  }
-  uint32_t best = c.key[0];
-#pragma unroll
-  for (int j = 1; j < NCH; j++) best = umin(best, c.key[j]);
-  return wave_min(best);
-}
-__device__ __forceinline__ bool fits(uint32_t key, int g) { return (int)(key >> 10) + g <= NGPU; }
-
-// earliest time at which some host has g idle GPUs if nothing new is allocated
-template <int NCH>
-__device__ __forceinline__ int32_t earliest_free(const Ctx<NCH> &c, int g) {
-  wave_sync();
-  int32_t y = NEVER;
-#pragma unroll
-  for (int j = 0; j < NCH; j++) y = min(y, c.m.fin[NGPU * (j * WAVE + c.lane) + g - 1]);
-  return (int32_t)wave_min((uint32_t)y);
-}
-
-// The key and the next change of the host in chunk jh, lane `mine`: found by halving the chunks (a few uniform
-// branches; touching the registers of all chunks takes five vector instructions for each).
-template <int LO, int HI, int NCH>
-__device__ __forceinline__ void note_allocation(Ctx<NCH> &c, int jh, bool mine, uint32_t key, int32_t finish) {
-  if constexpr (HI - LO == 1) {
-    c.key[LO] = mine ? key : c.key[LO];
-    c.nx[LO] = mine ? min(c.nx[LO], finish) : c.nx[LO];
-  } else {
-    constexpr int MID = (LO + HI) / 2;
-    if (jh < MID) note_allocation<LO, MID>(c, jh, mine, key, finish);
-    else note_allocation<MID, HI>(c, jh, mine, key, finish);
-  }
-}
-
-// the job of session s gets g GPUs of the host with this key at time T
-template <int NCH>
-__device__ __forceinline__ void start_job(Ctx<NCH> &c, State &r, uint32_t s, int32_t T, int32_t t_submit, int32_t dur, int g, uint32_t key) {
-  const int h = (int)(key & 1023u);
-  // a long queue can push a job beyond the int32 time range: the replay ends as invalid (the sum stays below 2^32)
-  const uint32_t fin = (uint32_t)T + (uint32_t)c.p.batch_delay + (uint32_t)dur;
-  r.status = fin >= 0x7FFFFFFFu ? (int32_t)NBOS_E_RANGE : r.status;
-  const int32_t finish = (int32_t)fin;
-  // the g GPUs of the row that have been free longest are held until `finish` (see the file header)
-  wave_sync();
-  int32_t *row = c.m.fin + NGPU * h;
-  const int k = c.lane & 7;
-  const int32_t own = row[k];
-  int32_t up = row[(k + g) & 7];
-  up = k + g < NGPU ? up : NEVER;
-  note_allocation<0, NCH>(c, h >> 6, c.lane == (h & 63), key + ((uint32_t)g << 10), finish);
-  r.dirty |= wballot(c.vsid == s);
-  r.c_started++;
-  r.sum_dur += dur;
-  r.g_exec += (int64_t)g * dur;
-  r.sum_g += g;
-  if (T == t_submit) {
-    r.c_imm++;                                    // its delay is the container start: histogram and sum follow at the end
-  } else {
-    const int32_t wait = T - t_submit, delay = wait + c.p.batch_delay;
-    r.sum_wait += wait;
-    r.max_wait = r.max_wait > wait ? r.max_wait : wait;
-    const int b = min(32 - __builtin_clz((uint32_t)delay), 31);      // (delay > 0)
-    atomicAdd(&c.m.hist[c.own_slot < 0 ? b : c.own_slot], 1u);
-  }
-  r.lazy_max = r.lazy_max > finish ? r.lazy_max : finish;
-  r.last_T = T;
-  decide(c, r, T, NBOS_D_BATCH_START, s, (uint32_t)h);
-  row[k] = med3(own, finish, up);                 // (every eighth lane the same)
-  c.m.sess[s] = make_int2(finish, (g - 1) << G_SHIFT);
-}
-
-// The head finds no host at time T: it asks for one more host, and its start time is worked out (a host has the
-// GPUs idle then: it does not come here a second time).
-template <int NCH>
-__device__ __forceinline__ void head_waits(Ctx<NCH> &c, State &r, int32_t T) {
-  int32_t first_free = earliest_free(c, r.h_g);
-  if ((c.p.flags & NBOS_F_SCALE_OUT) && r.n_on < c.p.Hmax) {
-    const int64_t up = (int64_t)T + c.p.boot;
-    r.status = up >= 0x7FFFFFFFLL ? (int32_t)NBOS_E_RANGE : r.status;
-    const int32_t ra = (int32_t)up;
-    const int h = r.n_on++;                       // hosts are added in order and never go
-    r.prov -= (int64_t)c.p.G * T;
-    c.m.fin[NGPU * h + (c.lane & 7)] = (c.lane & 7) < c.p.G ? ra : NEVER;      // all its GPUs are idle once it is up
-#pragma unroll
-    for (int j = 0; j < NCH; j++) c.nx[j] = h - c.lane == j * WAVE ? ra : c.nx[j];
-    r.lazy_max = r.lazy_max > ra ? r.lazy_max : ra;
-    decide(c, r, T, NBOS_D_BATCH_HOST, (uint32_t)r.h_s, (uint32_t)h);
-    first_free = first_free < ra ? first_free : ra;
-  }
-  r.status = first_free < T ? (int32_t)NBOS_E_RANGE : r.status;      // (cannot be; the loop might not end)
-  r.head_T = first_free;
-}
-
-// the next waiting job becomes the head; jobs are read ahead from the ring, up to 64 at a time
-template <int NCH>
-__device__ __forceinline__ void next_head(Ctx<NCH> &c, State &r) {
-  if (r.w_at == r.w_n) {
-    wave_sync();
-    r.w_n = r.q_n < WAVE ? r.q_n : WAVE;
-    r.w_at = 0;
-    int at = r.q_head + min(c.lane, r.w_n - 1);
-    at = at >= c.ring ? at - c.ring : at;
-    c.w_s = c.m.fifo[at];
-    const int2 rec = c.m.sess[c.w_s];
-    c.w_t = rec.x; c.w_d = rec.y;
-  }
-  const int32_t d = lane_get(c.w_d, r.w_at);
-  r.h_s = lane_get(c.w_s, r.w_at);
-  r.h_t = lane_get(c.w_t, r.w_at);
-  r.h_dur = d & DUR_MASK;
-  r.h_g = ((d >> G_SHIFT) & 7) + 1;
-  r.w_at++;
-  r.head_T = max(r.h_t, r.last_T);
-}
-
-// an arrival that cannot start yet waits at the end of the queue
-template <int NCH>
-__device__ __forceinline__ void join_queue(Ctx<NCH> &c, State &r, uint32_t s, int32_t t, int32_t dur, int g) {
-  int tail = r.q_head + r.q_n;
-  tail = tail >= c.ring ? tail - c.ring : tail;
-  c.m.fifo[tail] = (uint16_t)s;
-  c.m.sess[s] = make_int2(t, dur | ((g - 1) << G_SHIFT) | WAITING);
-  r.dirty |= wballot(c.vsid == s);
-  r.q_n++;
-}
-
-template <int NCH>
+template <int NS>
 __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int rep = launch_slot_replay(p);
@@ -253,126 +388,232 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   const int64_t ev_lo = p.ev_offset[trace], ev_hi = p.ev_offset[trace + 1];
   const int s_lo = p.sess_offset[trace];
   const int n_sess = p.sess_offset[trace + 1] - s_lo;
+  uint64_t *const dlog = p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr;
 
   Lds m;
   unsigned char *q = lds_raw;
-  m.fin = (int32_t *)q;             q += (size_t)NCH * WAVE * NGPU * 4;
+  const bool few = p.batch == 0;
+  const size_t n4 = (size_t)((p.n_cap + 3) / 4 * 4);   // (read four at a time)
   m.hist = (uint32_t *)q;           q += (32 + WAVE) * 4;
-  m.sess = (int2 *)q;               q += (size_t)p.n_cap * 8;
-  m.fifo = (uint16_t *)q;
+  m.stage_t = (int32_t *)q;         q += (WAVE + 4) * 4;
+  m.stage_k = (uint32_t *)q;        q += (WAVE + 4) * 4;
+  m.time = (int32_t *)q;            q += n4 * 4;
+  m.meta = (uint32_t *)q;           q += n4 * 4;
+  m.mid_t = (int32_t *)q;           q += (few ? 4 : MID_CAP + 4) * 4;              // (and a word where nothing is kept)
+  m.mid_k = (uint32_t *)q;          q += (few ? 4 : MID_CAP + 4) * 4;
+  m.ready = (int32_t *)q;
 
-  for (int i = lane; i < NCH * WAVE * NGPU; i += WAVE) m.fin[i] = (i >> 3) < p.H0 && (i & 7) < p.G ? 0 : NEVER;
   if (lane < 32) m.hist[lane] = 0;
-  for (int s = lane; s < n_sess; s += WAVE) m.sess[s] = make_int2(0, ((int)p.sess_gpus[s_lo + s] - 1) << G_SHIFT);
+  for (int s = lane; s < (int)n4; s += WAVE) { m.time[s] = 0; m.meta[s] = 0; }
+  wave_sync();
+  for (int s = lane; s < n_sess; s += WAVE) m.meta[s] = ((uint32_t)p.sess_gpus[s_lo + s] - 1u) << G_SHIFT;
   __syncthreads();
 
-  Ctx<NCH> c{p, m, lane, lane == 0 ? -1 : 32 + lane, p.n_cap + 1, p.dlog ? p.dlog + (int64_t)rep * p.dlog_stride : nullptr};
+  Ctx<NS> c{p, m, lane, n_sess, few ? 0 : MID_CAP};
 #pragma unroll
-  for (int j = 0; j < NCH; j++) {
-    const int h = j * WAVE + lane;
-    c.key[j] = ((h < p.H0 ? (uint32_t)(NGPU - p.G) : (uint32_t)NGPU) << 10) | (uint32_t)h;
-    c.nx[j] = NEVER;
+  for (int s = 0; s < NS; s++) {
+    // the hosts that are there from the start are on the level of the slots that are not
+    const int n = min(max(p.H0 - 512 * s - 64 * (lane & 7), 0), 64);
+    const uint64_t bits = n == 64 ? ~0ull : (1ull << n) - 1ull;
+    const bool here = (lane >> 3) == NGPU - p.G;
+    c.lo[s] = here ? (uint32_t)bits : 0u;
+    c.hi[s] = here ? (uint32_t)(bits >> 32) : 0u;
   }
-  c.w_s = 0; c.w_t = 0; c.w_d = 0;
+  c.qt = NEVER; c.qk = 0;
+  c.vt = 0; c.vfd = 0; c.vjob = 0; c.vstart = 0; c.vhost = 0;
+  c.power = digest_powers(lane);
   State r;
   memset(&r, 0, sizeof r);
+  r.q_t = NEVER; r.up_t = NEVER;
+  r.win_t = ALL; r.win = 1024;
+  r.mid_t = ALL; r.mid_win = 1 << 17;
+  r.p_f = -1;
+  r.next_up = p.H0; r.n_on = p.H0;
   r.digest = 0xCBF29CE484222325ULL;
-  r.head_T = NEVER;
-  r.n_on = p.H0;
+  // per lane: sums over jobs, their latest finish, the longest wait
+  uint64_t sum_dur = 0, g_exec = 0, sum_wait = 0;
+  uint32_t sum_g = 0;
+  int32_t latest = 0, max_wait = 0;
 
-  // the events: one per lane per tile, next tile in flight; after the last one the queue is served to its end
-  int64_t base = ev_lo;
-  int32_t vt = 0, vd = 0, vs = 0, nt = 0, nd = 0, ns = 0;
-  if (base < ev_hi) {
-    const int64_t at = min(base + lane, ev_hi - 1);
+  // the events: one per lane per tile, next tile in flight
+  int32_t nt = 0, nd = 0, ns = 0;
+  if (ev_lo < ev_hi) {
+    const int64_t at = min(ev_lo + lane, ev_hi - 1);
     nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
   }
-  bool final = false;
-  while (!final) {
-    uint64_t todo = 0;
-    int2 rec = make_int2(0, 0);             // prefetched session record of this lane's event
-    if (base < ev_hi) {
-      vt = nt; vd = nd; vs = ns;
-      const int64_t cur = base;
-      base += WAVE;
-      if (base < ev_hi) {
-        const int64_t at = min(base + lane, ev_hi - 1);
-        nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
-      }
-      const bool valid = cur + lane < ev_hi;
-      const bool is_cell = valid && ((uint32_t)vs >> 24) == NBOS_EV_CELL;
-      const uint32_t sid = (uint32_t)vs & 0xFFFFFFu;
-      c.vsid = is_cell ? sid : 0xFFFFFFFFu;
-      wave_sync();
-      rec = m.sess[sid];                    // (every event of a trace has a session)
-      // a cell whose session's job has started and outlasts it is dropped, whatever happens until then
-      const bool drop = is_cell && !(rec.y & WAITING) && rec.x > vt;
-      r.dirty = 0;
-      r.c_total += (uint32_t)__builtin_popcountll(wballot(is_cell));
-      r.c_busy += (uint32_t)__builtin_popcountll(wballot(drop));
-      todo = wballot(is_cell && !drop);
-      if (ev_hi - cur <= WAVE) {
-        const int32_t tl = lane_get(vt, (int)(ev_hi - cur - 1));
-        r.t_end = r.t_end > tl ? r.t_end : tl;
-      }
-    } else {
-      final = true;
+  for (int64_t cur = ev_lo; cur < ev_hi; cur += WAVE) {
+    c.vt = nt;
+    const int32_t vd = nd, vs = ns;
+    if (cur + WAVE < ev_hi) {
+      const int64_t at = min(cur + WAVE + lane, ev_hi - 1);
+      nt = p.ev_time[at]; nd = p.ev_dur[at]; ns = p.ev_sk[at];
     }
-    // one iteration per look at a job: the head of the queue if it meets the scheduler at or before the
-    // next arrival (what is due at or before an arrival comes first), else the arrival
-    while (r.status == NBOS_OK) {
-      int i = 0;
-      int32_t t = NEVER;
-      if (todo != 0) { i = (int)__builtin_ctzll(todo); t = lane_get(vt, i); }
-      else if (!final || r.q_n == 0) break;
-      uint32_t s;
-      int32_t T, t_submit, dur;
-      int g;
-      if (r.head_T <= t) {
-        T = r.head_T; s = (uint32_t)r.h_s; t_submit = r.h_t; dur = r.h_dur; g = r.h_g;
-      } else {
-        todo &= todo - 1;
-        s = (uint32_t)lane_get(vs, i) & 0xFFFFFFu;
-        int32_t tm = lane_get(rec.x, i), gq = lane_get(rec.y, i);
-        if (__builtin_expect(((r.dirty >> i) & 1u) != 0, 0)) {
-          wave_sync();
-          const int2 now = m.sess[s];
-          tm = uni(now.x); gq = uni(now.y);
+    const bool is_cell = (cur + lane < ev_hi) & (((uint32_t)vs >> 24) == NBOS_EV_CELL);
+    const uint32_t sid = (uint32_t)vs & 0xFFFFu;      // (every event of a trace has a session, below 2^16)
+    wave_sync();
+    const int32_t rt = m.time[sid];
+    const uint32_t rm = m.meta[sid];
+    // a cell whose session's previous job has started and outlasts it is dropped
+    const bool drop = is_cell & (rt > c.vt);
+    // lanes whose session has an earlier lane in the tile look again at their turn: every lane's mark goes to its session's
+    // record, in bits that are 0 there, and the lowest lane's is the largest
+    atomicMax(is_cell & !drop ? &m.meta[sid] : m.stage_k + WAVE, rm | ((uint32_t)(WAVE - lane) << 16));
+    wave_sync();
+    const uint32_t first = m.meta[sid];
+    wave_sync();
+    m.meta[sid] = rm;
+    c.vfd = (int32_t)((uint32_t)p.batch_delay + (uint32_t)vd);
+    c.vjob = sid | (((rm >> G_SHIFT) & 7u) << 16) | (((first >> 16) & 127u) != (uint32_t)(WAVE - lane) ? SLOW : 0u);
+    r.c_total += (uint32_t)__builtin_popcountll(wballot(is_cell));
+    r.c_busy += (uint32_t)__builtin_popcountll(wballot(drop));
+    r.todo = wballot(is_cell & !drop);
+    r.unsaved = r.todo;
+    r.started = 0; r.folded = 0;
+    while (r.todo != 0) {
+      if (__builtin_expect(r.p_f >= 0, 0)) make_room(c, r);
+      // ---- jobs that start when they first meet the scheduler, the listed completions due before each applied on the
+      // way: a loop with nothing else in it and one way out. `bad` is negative when it ends: no job of the tile is left (lane
+      // 63's time is looked at then: no later than any job to come), the last one finds no room in the lists, or what does not fit.
+      int32_t other_t = min(r.up_t, r.win_t + 1) - 1;
+      int i, L, set, g;
+      int32_t T, f, bad;
+      uint32_t job;
+      auto look_at_next = [&]() {
+        i = (int)__builtin_ctzll(r.todo | (1ull << 63));
+        job = (uint32_t)lane_get((int)c.vjob, i);
+        T = max(lane_get(c.vt, i), r.now);
+        f = (int32_t)((uint32_t)T + (uint32_t)lane_get(c.vfd, i));      // (below 2^32)
+        while (r.q_t <= T) {
+          const uint32_t k = r.q_k;
+          pop_completion(c, r);
+          give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1);
         }
-        if (__builtin_expect(tm > t || (gq & WAITING), 0)) { r.c_busy++; continue; }   // its previous job has not finished
-        T = t; t_submit = t; dur = lane_get(vd, i);
-        g = ((gq >> G_SHIFT) & 7) + 1;
-        if (r.q_n > 0) { join_queue(c, r, s, t, dur, g); continue; }
+        L = best_lane(c, set);
+        g = (int)((job >> 16) & 7u) + 1;
+        // (a long queue can push a job beyond the int32 time range: f + 1 is negative then)
+        bad = (r.todo == 0 ? -1 : 0) | (int32_t)job | (NGPU - (L >> 3) - g) | (other_t - T) | (int32_t)((uint32_t)f + 1u);
+      };
+      look_at_next();
+      while (__builtin_expect(bad >= 0, 1)) {
+        uint32_t wl = (uint32_t)lane_get((int)c.lo[0], L), wh = (uint32_t)lane_get((int)c.hi[0], L);
+        if constexpr (NS == 2) {
+          const uint32_t vl = (uint32_t)lane_get((int)c.lo[1], L), vh = (uint32_t)lane_get((int)c.hi[1], L);
+          wl = set ? vl : wl; wh = set ? vh : wh;
+        }
+        const uint32_t h = (uint32_t)__builtin_ctzll(((uint64_t)wh << 32) | wl) | ((uint32_t)(L & 7) << 6) | ((uint32_t)set << 9);
+        // from lane L to lane L + 8 g, which is not there for a host that is full now (8 g in two steps: a shift is by 63 at most)
+        const uint64_t from = 1ull << L;
+        flip_host(c, from | ((from << (4 * g)) << (4 * g)), h);
+        c.vstart = (int32_t)lane_set((uint32_t)c.vstart, (uint32_t)i, (uint32_t)T);
+        c.vhost = lane_set(c.vhost, (uint32_t)i, h);
+        r.now = T;
+        r.todo &= r.todo - 1;
+        if (f <= r.mid_t) {
+          const uint32_t k = h | ((uint32_t)(g - 1) << G_SHIFT);
+          const bool near = f <= r.win_t;
+          if (near & (r.qe < Q_CAP)) {
+            insert_completion(c, r, f, k);
+          } else {
+            const bool mid = !near & (r.mid_n < MID_CAP);
+            const int at = mid ? r.mid_n : c.mid_sink;
+            c.m.mid_t[at] = f;
+            c.m.mid_k[at] = k;
+            r.mid_n += mid ? 1 : 0;
+            r.p_f = mid ? -1 : f;
+            r.p_k = k;
+            other_t = mid ? other_t : -1;
+          }
+        }
+        look_at_next();
       }
-      const uint32_t key = best_host(c, T);
-      if (__builtin_expect(fits(key, g), 1)) {
-        start_job(c, r, s, T, t_submit, dur, g, key);
-        if (r.q_n > 0) {                          // it was the head
-          r.q_head = r.q_head + 1 == c.ring ? 0 : r.q_head + 1;
-          r.q_n--;
-          r.head_T = NEVER;
-          if (r.q_n > 0) next_head(c, r);
-        }
-      } else {
-        if (r.q_n == 0) {
-          join_queue(c, r, s, t, dur, g);
-          r.h_s = (int32_t)s; r.h_t = t; r.h_dur = dur; r.h_g = g;
-          r.w_at = 0; r.w_n = 0;
-        }
-        head_waits(c, r, T);
+      if ((r.todo == 0) | (r.p_f >= 0)) continue;
+      // ---- one job that does not start like that ----
+      save_records(c, r);
+      const uint32_t s = job & 0xFFFFu;
+      if (__builtin_expect((job & SLOW) != 0u, 0)) {
+        wave_sync();
+        const bool dropped = uni(m.time[s]) > lane_get(c.vt, i);       // its previous job has not finished
+        r.c_busy += dropped ? 1u : 0u;
+        r.todo = dropped ? r.todo & (r.todo - 1) : r.todo;
+        r.unsaved = r.todo;
+        c.vjob = in_mask(1ull << i) ? c.vjob & ~SLOW : c.vjob;
+        continue;
       }
+      bool asked = false;
+      for (;;) {
+        // what happens to the hosts up to T
+        while (due_time(r) <= T) {
+          if (r.win_t < min(r.q_t, r.up_t)) { refill(c, r, min(T, r.up_t)); continue; }
+          const bool listed = r.q_t <= r.up_t;
+          const uint32_t k = listed ? r.q_k : (uint32_t)r.next_up | ((uint32_t)(p.G - 1) << G_SHIFT);
+          r.next_up += listed ? 0 : 1;
+          if (__builtin_expect(listed, 1)) {
+            pop_completion(c, r);
+          } else {
+            wave_sync();
+            r.up_t = r.next_up < r.n_on ? uni(m.ready[r.next_up]) : NEVER;
+          }
+          give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1);
+        }
+        if (fits(best_lane(c, set), g)) break;             // it starts at T, in the loop above
+        if (!asked) ask_for_host(c, r, dlog, s, T);         // (it starts before this path is left)
+        asked = true;
+        // the listed completions, instant by instant, for as long as none leaves a host with the GPUs idle
+        other_t = min(r.up_t - 1, r.win_t);
+        bool found = false;
+        while (!found & (r.q_t <= other_t)) {
+          T = r.q_t;
+          do {
+            const uint32_t k = r.q_k;
+            pop_completion(c, r);
+            found = found | fits(give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1), g);
+          } while (r.q_t == T);
+        }
+        if (found) break;
+        T = due_time(r);                                   // (at the end of a window nothing need happen: no harm)
+        r.status = T == NEVER ? (int32_t)NBOS_E_RANGE : r.status;      // (cannot be: a job fits once the others are over)
+        if (r.status != NBOS_OK) break;
+      }
+      // (a start beyond the time range ends the replay)
+      r.status = (uint32_t)T + (uint32_t)lane_get(c.vfd, i) >= 0x7FFFFFFFu ? (int32_t)NBOS_E_RANGE : r.status;
+      if (r.status != NBOS_OK) break;
+      r.now = T;
     }
     if (r.status != NBOS_OK) break;
+    save_records(c, r);
+    // the tile's jobs: digest, sums, waits (those that start at once are all in the histogram's bin of the container start)
+    fold_jobs(c, r, dlog, r.started & ~r.folded);
+    r.c_started += (uint32_t)__builtin_popcountll(r.started);
+    const bool mine = in_mask(r.started);
+    const uint32_t one = mine ? 1u : 0u, g = ((c.vjob >> 16) & 7u) + 1u;
+    const uint32_t d = one * (uint32_t)vd, wait = one * (uint32_t)(c.vstart - c.vt);
+    r.c_imm += (uint32_t)__builtin_popcountll(wballot(mine & (wait == 0u)));
+    sum_dur += d;
+    g_exec += g * d;                               // (8 * NBOS_MAX_DUR_MS is below 2^32)
+    sum_g += one * g;
+    sum_wait += wait;
+    max_wait = max(max_wait, (int32_t)wait);
+    latest = max(latest, mine ? c.vstart + c.vfd : 0);
+    const int b = min(32 - __builtin_clz(wait + (uint32_t)p.batch_delay), 31);      // (of a wait of 0: not looked at)
+    atomicAdd(&m.hist[wait != 0u ? b : 32 + lane], 1u);
+  }
+  if (ev_lo < ev_hi) {
+    const int32_t tl = p.ev_time[ev_hi - 1];
+    r.t_end = r.t_end > tl ? r.t_end : tl;
   }
 
   __syncthreads();
-  const int32_t t_end = r.t_end > r.lazy_max ? r.t_end : r.lazy_max;
+  const int64_t sum_dur_all = (int64_t)wave_sum64(sum_dur), g_exec_all = (int64_t)wave_sum64(g_exec), sum_g_all = (int64_t)wave_sum64(sum_g),
+                sum_wait_all = (int64_t)wave_sum64(sum_wait);
+  const int32_t longest = (int32_t)~wave_min(~(uint32_t)max_wait);
+  const int32_t over = max((int32_t)~wave_min(~(uint32_t)latest), r.latest_up);
+  const int32_t t_end = r.t_end > over ? r.t_end : over;
   nbos_stats *out = p.stats + rep;
   // the jobs that started at once: all in the bin of the container start
   const int b0 = p.batch_delay == 0 ? 0 : 32 - __builtin_clz((uint32_t)p.batch_delay);
   if (lane < 32) out->delay_hist[lane] = m.hist[lane] + (lane == b0 ? r.c_imm : 0u);
   if (lane == 0) {
-    const int64_t sum_delay = r.sum_wait + (int64_t)r.c_started * p.batch_delay;
+    const int64_t sum_delay = sum_wait_all + (int64_t)r.c_started * p.batch_delay;
     out->status = r.status; out->n_decisions = r.n_dec;
     out->sessions_placed = 0; out->sessions_rejected = 0;
     out->cells_total = r.c_total; out->cells_immediate = r.c_imm; out->cells_started = r.c_started;
@@ -381,9 +622,9 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     out->executor_reused = 0; out->migrations = 0;
     out->scale_out_hosts = (uint32_t)(r.n_on - p.H0); out->scale_in_hosts = 0; out->peak_hosts = (uint32_t)r.n_on;
     out->migrations_warm = 0;
-    out->max_delay_ms = r.c_started > 0 ? r.max_wait + p.batch_delay : 0; out->t_end_ms = t_end;
-    out->sum_delay_ms = sum_delay; out->sum_tct_ms = r.sum_dur + sum_delay;
-    out->gpu_ms_executed = r.g_exec; out->gpu_ms_committed = r.g_exec + r.sum_g * p.batch_delay;
+    out->max_delay_ms = r.c_started > 0 ? longest + p.batch_delay : 0; out->t_end_ms = t_end;
+    out->sum_delay_ms = sum_delay; out->sum_tct_ms = sum_dur_all + sum_delay;
+    out->gpu_ms_executed = g_exec_all; out->gpu_ms_committed = g_exec_all + sum_g_all * p.batch_delay;
     out->gpu_ms_provisioned = r.prov + (int64_t)r.n_on * p.G * t_end;
     out->reservation_gpu_ms = 0; out->sub_gpu_ms = 0; out->replica_ms = 0;
     out->digest = r.digest;

@@ -319,6 +319,7 @@ struct Shape {
   int HP = 0;               // hosts_max rounded up to whole waves
   int n_cap = 1;            // session capacity of a replay's LDS
   bool in_regs = false;     // the register kernel runs
+  bool listed = false;      // Batch kernel: there is room for its list of completions in LDS, and use for it
 };
 
 // the offsets of the traces, copied to the host
@@ -365,16 +366,9 @@ template <uint32_t F> void set_reg_closed_kernel(nbos_replay *h, int nj) {
   set_kernel(h, reg_closed_kernel_for<F>(nj), "regk::nbos_replay_reg_closed_kernel<%d, %uu>", nj > 8 ? 8 : nj, F);
 }
 
-// the Batch baseline's kernel for clusters of up to 64, 128, 256, 512, 768 or 1,024 hosts (the keys of all its
-// hosts are unrolled over registers: a kernel for more hosts than there are looks at the others for nothing);
-// returns the chunks of 64 hosts it is compiled for
-template <int NCH> int set_batch_kernel_of(nbos_replay *h) {
-  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NCH>, "batchk::nbos_replay_batch_kernel<%d>", NCH, 0u);
-  return NCH;
-}
-int set_batch_kernel(nbos_replay *h, int chunks) {
-  return chunks <= 1 ? set_batch_kernel_of<1>(h) : chunks <= 2 ? set_batch_kernel_of<2>(h) : chunks <= 4 ? set_batch_kernel_of<4>(h)
-         : chunks <= 8 ? set_batch_kernel_of<8>(h) : chunks <= 12 ? set_batch_kernel_of<12>(h) : set_batch_kernel_of<16>(h);
+// the Batch baseline's kernel: a set of registers per 512 hosts
+template <int NS> void set_batch_kernel(nbos_replay *h) {
+  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NS>, "batchk::nbos_replay_batch_kernel<%d>", NS, 0u);
 }
 
 // LDS of a replay with its hosts in registers: counters, 8 bytes per session, the pre-warmed pool
@@ -445,10 +439,18 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
   const size_t n_cap = (size_t)sh->n_cap;
   const bool force_generic = (cfg->flags & NBOS_F_GENERIC_KERNEL) != 0;
   if (batch_mode) {
-    // a row of 32 bytes per host, a record of 8 bytes and a place in the queue per session
-    const int chunks = set_batch_kernel(h, HP / WAVE);
-    h->lds_bytes = (size_t)chunks * WAVE * 32 + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2;
-    if (h->lds_bytes > (size_t)maxlds) return NBOS_E_LIMIT;
+    // a record of 8 bytes per session, and where hosts are added the time each comes up. What is accepted stays what it
+    // was when there was a queue as well (2 bytes per session) and a row of 32 bytes per host, for up to 64, 128, 256, 512,
+    // 768 or 1,024 hosts.
+    const int chunks = HP / WAVE;
+    const size_t rows = (size_t)(chunks <= 2 ? chunks : chunks <= 4 ? 4 : chunks <= 8 ? 8 : chunks <= 12 ? 12 : 16) * WAVE * 32;
+    if (rows + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2 > (size_t)maxlds) return NBOS_E_LIMIT;
+    const size_t least = 128 + WAVE * 4 + (WAVE + 4) * 8 + (n_cap + 3) / 4 * 32 + 4 * 8 +
+                         ((cfg->flags & NBOS_F_SCALE_OUT) ? (size_t)HP * 4 : 0);
+    sh->listed = n_cap > (size_t)batchk::MID_CAP && least + batchk::MID_CAP * 8 <= (size_t)maxlds;
+    h->lds_bytes = least + (sh->listed ? batchk::MID_CAP * 8 : 0);
+    if (chunks <= 8) set_batch_kernel<1>(h);
+    else set_batch_kernel<2>(h);
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
     // hosts in registers; 8 bytes per session
     h->lds_bytes = reg_lds_bytes(n_cap, warm_pool);
@@ -609,6 +611,7 @@ void fill_params(nbos_replay *h, const Shape &sh) {
   // without, 119 ms with). NBOS_F_ROUNDS_OFF / _ON force the choice (comparison runs, tests).
   const bool closed_loop = (cfg->flags & NBOS_F_CLOSED_LOOP) != 0;
   k.batch = (cfg->flags & NBOS_F_ROUNDS_OFF) ? 0 : (cfg->flags & NBOS_F_ROUNDS_ON) ? 1 : (closed_loop && cfg->hosts_max <= WAVE) ? 0 : 1;
+  if (cfg->flags & NBOS_F_BATCH_MODE) k.batch = sh.listed ? 1 : 0;
   k.cl_chain = (const int2 *)h->d_chain;
   k.cl_cursor = h->d_chain ? h->d_chain + 2 * (size_t)sh.total_ev : nullptr;
 }

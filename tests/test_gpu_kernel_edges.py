@@ -21,7 +21,7 @@ def crowded(seed, hosts, G, sessions_per_host, cells_per_session, gap_s=5.0, dur
 @pytest.mark.parametrize("hosts,G", [(1, 8), (2, 1), (63, 8), (64, 3), (65, 8), (128, 2), (129, 1), (256, 4), (257, 3), (512, 2),
                                      (513, 1), (768, 2), (769, 3), (1024, 1), (1024, 2)])
 def test_batch_kernel_at_its_chunk_edges(rp, oracle, hosts, G, grow):  # noqa: F811
-    # one kernel for up to 64, 128, 256, 512, 768, 1,024 hosts; rows of fewer than 8 GPUs are padded
+    # 64 hosts to a word, 512 to a set of registers; of 8 slots per host those beyond G are held for ever
     b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, gpus_per_host=G),
                 [crowded(7, hosts, G, 3, 3), crowded(8, hosts, G, 2, 2)], [0, 1, 0], [1000, 1000, 1000], f"edge{hosts}")
     as_batch(b, delay=15_000, scale_out=grow)
@@ -40,6 +40,21 @@ def on_a_grid(seed, hosts, sessions, step_ms, flags, caps):
                        with_end=True)
     tr = (tr[0] // step_ms * step_ms, *tr[1:])
     return tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, flags=flags), [tr], [0] * len(caps), list(caps), "refill")
+
+
+@pytest.mark.parametrize("grow", [False, True], ids=["fixed", "grow"])
+@pytest.mark.parametrize("hosts,sessions,step_ms,delay", [(40, 60, 1, 0), (40, 512, 1, 15_000), (64, 513, 1, 0), (100, 2000, 1, 15_000),
+                                                          (100, 400, 600_000, 0), (100, 3000, 600_000, 0), (600, 3000, 60_000, 15_000),
+                                                          (600, 6000, 1_200_000, 0), (520, 5000, 1000, 0), (3, 700, 100_000, 15_000)])
+def test_batch_completions_in_order(rp, oracle, hosts, sessions, step_ms, delay, grow):  # noqa: F811
+    # the list of completions in registers (63) and the one in LDS (512 jobs, only with more sessions than that): refilled,
+    # pushed into, overrun, and hundreds of jobs (1,200 and more on the coarsest grid) that end at one instant
+    b = as_batch(on_a_grid(9, hosts, sessions, step_ms, 0, [1000]), delay=delay, scale_out=grow)
+    if grow:
+        b.config.update(hosts_initial=max(1, hosts // 2), hosts_max=hosts, boot_delay_ms=20_000)
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs)
+    assert st["cells_started"].min() > 0
 
 
 def cell_timers_at_once(b, log):
