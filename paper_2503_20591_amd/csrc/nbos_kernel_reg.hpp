@@ -19,8 +19,8 @@
 // Events: coalesced dword loads, one event per lane, next tile in flight while the current tile
 //         is consumed from registers (v_readlane). At tile start every lane prefetches the record of
 //         its event's session from LDS; events of sessions in a final state (rejected / ended) are
-//         counted in bulk and skipped. A record written during the tile marks the matching lanes
-//         dirty, and only those are read again from LDS.
+//         counted in bulk and skipped. A cell that starts at once brings the lanes of its session up to date, any
+//         other change of a record marks them stale, and only those are read again from LDS.
 // Timers: RETRY of a queued cell (Section 3.2.3) and the END of a session that was busy when its END
 //         arrived are the only timers that change decisions. The 64 earliest live sorted in
 //         registers (insert = ballot + DPP wave shift, pop = DPP wave shift); later ones stay with
@@ -58,15 +58,12 @@ struct Lds {
 struct Regs {
   uint32_t n_dec, c_total, c_imm, c_started, c_busy, c_unplaced, reused, h0;
   int64_t sum_dur, g_exec;
-  uint64_t digest;
   int32_t lazy_max, t_end;
   int32_t q_n, q_head_t;                 // sorted register queue: size, time of lane 0
   int32_t o_n, o_min_t;                  // timers outside the registers: how many, the earliest
   uint32_t o_min_k;
   int32_t status;
-  uint64_t dirty;                        // lanes of the current tile whose prefetched record is stale
   uint64_t at_once;                      // lanes of the current tile whose cells started at once, not in the sums yet
-  uint64_t slow_lanes;                   // lanes of the current tile whose prefetched record showed no idle placed session
   // closed loop: the event being handled, its duration and kind (packed as in Ctx::qx), its session's next
   // event and the think time before that; the time window the next refill takes
   int32_t cl_e, cl_x, cl_nx, cl_nth, cl_win;
@@ -87,7 +84,11 @@ struct Ctx {
   uint32_t hs;               // S | nrep << 16 of host = lane
   int32_t qt, qd;            // sorted timers, entry i in lane i
   uint32_t qk;
-  uint32_t vsid;             // session id of this lane's event in the current tile (~0 if none)
+  // this lane's event in the current tile, if it is a cell of a placed session that is not ending and whose record nobody
+  // has changed since but by starting cells at once: the session and its busy-until time (else ~0 and NEVER)
+  uint32_t vsid;
+  int32_t vtm;
+  uint64_t digest;           // the same in all lanes, see decide_code
   int32_t fu;                // lane g-1 (g = 1..8): no host can have g idle GPUs before this time
   // closed loop: the replay's cursors, the events of the trace; and with every sorted timer what firing
   // it needs: qd = the event's index, qx = its duration | kind << 28 | CLX_LOADED (0: not loaded yet),
@@ -102,16 +103,48 @@ struct Ctx {
   __device__ __forceinline__ uint32_t flags() const { return instance_flags<F>(p); }
 };
 
-// write a session record; lanes of the current tile that prefetched it go stale
+// A decision's code goes into the digest (and into the log). The digest is kept in vector registers, the same in all lanes:
+// the scalar unit, which is what many small replays are bound by (0.86 instructions a clock with 64 of them on a
+// compute unit), would take nine instructions for the 64-bit product, the vector side takes four. 24 hosts, 16,384 replays:
+// 45.0 ms with the scalar product, 42.5 with this; 300 short replays 0.766 -> 0.744. (Codes kept in lanes and folded 64 at a
+// time: 43.5, but 30 hosts 27.2 -> 31.3 and 64 hosts 64.6 -> 71.7, as every path then carries two more registers.)
 template <int NJ, uint32_t F>
-__device__ __forceinline__ void sess_write(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint32_t hw, int32_t tm, uint32_t fl) {
-  c.m.sess[s] = make_int2((int)((hw & ~RK_FLAGS) | (fl & RK_FLAGS)), tm);
-  r.dirty |= wballot(c.vsid == s);
+__device__ __forceinline__ void decide_code(Ctx<NJ, F> &c, Regs &r, int32_t now, uint32_t code_lo) {
+  const uint64_t code = ((uint64_t)(uint32_t)now << 32) | code_lo, d = c.digest;
+  static_assert(DIGEST_PRIME == (1ull << 40) + 0x1B3u, "the product below");
+  uint64_t low = (uint64_t)(uint32_t)d * 0x1B3u + code;
+  uint32_t high = (uint32_t)(low >> 32) + (uint32_t)(d >> 32) * 0x1B3u + ((uint32_t)d << 8);
+  uint32_t keep = (uint32_t)low;
+  asm volatile("" : "+v"(keep), "+v"(high));             // (uniform, but kept off the scalar unit)
+  c.digest = ((uint64_t)high << 32) | keep;
+  if (__builtin_expect(c.dlog != nullptr, 0)) {
+    if ((int64_t)r.n_dec < c.p.dlog_stride) c.dlog[r.n_dec] = code;
+  }
+  r.n_dec++;
 }
 template <int NJ, uint32_t F>
-__device__ __forceinline__ void sess_write_flag(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint32_t fl) {
+__device__ __forceinline__ void decide(Ctx<NJ, F> &c, Regs &r, int32_t now, uint32_t outcome, uint32_t s, uint32_t slot, uint32_t host) {
+  decide_code(c, r, now, host | (slot << 10) | (outcome << 12) | (s << 16));
+}
+
+// a session record has been written: lanes of the current tile that hold it go stale
+template <int NJ, uint32_t F>
+__device__ __forceinline__ void mark_stale(Ctx<NJ, F> &c, uint32_t s) {
+  if constexpr (!Ctx<NJ, F>::closed) {
+    const bool stale = c.vsid == s;
+    c.vtm = stale ? NEVER : c.vtm;
+    c.vsid = stale ? 0xFFFFFFFFu : c.vsid;
+  }
+}
+template <int NJ, uint32_t F>
+__device__ __forceinline__ void sess_write(Ctx<NJ, F> &c, uint32_t s, uint32_t hw, int32_t tm, uint32_t fl) {
+  c.m.sess[s] = make_int2((int)((hw & ~RK_FLAGS) | (fl & RK_FLAGS)), tm);
+  mark_stale(c, s);
+}
+template <int NJ, uint32_t F>
+__device__ __forceinline__ void sess_write_flag(Ctx<NJ, F> &c, uint32_t s, uint32_t fl) {
   c.m.sess[s].x = (int)fl;
-  r.dirty |= wballot(c.vsid == s);
+  mark_stale(c, s);
 }
 
 // ---- timers beyond the 64 sorted ones stay with their session -------------------------------------
@@ -133,7 +166,7 @@ __device__ __forceinline__ void ovf_push(Ctx<NJ, F> &c, Regs &r, int32_t t, uint
     c.m.sess[s].x |= (int)RK_OVF;
     c.ovf_dur[s] = d;
   }
-  r.dirty |= wballot(c.vsid == s);
+  mark_stale(c, s);
   if (r.o_n == 0 || t < r.o_min_t || (t == r.o_min_t && k < r.o_min_k)) { r.o_min_t = t; r.o_min_k = k; }
   r.o_n++;
 }
@@ -235,9 +268,8 @@ __device__ __forceinline__ void refill(Ctx<NJ, F> &c, Regs &r) {
     nx = ch.x; nth = ch.y;
   } else {
     e = c.ovf_dur[s];                            // qd carries the queued cell's duration (of a deferred end: not looked at)
-    // the records taken have lost their mark: lanes of the tile that prefetched one read it again. Such a
-    // session was queued or ending when the tile was loaded (or its lanes are stale already)
-    r.dirty |= r.slow_lanes;
+    // (the records taken have lost their mark: lanes of the tile with one of those sessions are stale, as it was queued or
+    // ending when the tile was loaded or has become so since)
   }
   const int rank = timer_ranks(c.lane, cnt, t, key);
   const int dst = take ? rank : c.lane;          // a permutation: the timers taken in order, the rest where they are
@@ -268,6 +300,35 @@ __device__ __forceinline__ int committed(const Ctx<NJ, F> &c, int32_t now) {
     bits = grp == j ? mine : bits;
   }
   return __builtin_popcount(bits & 0xFFu);
+}
+
+// The same on top of `more`, with the words of the busy GPUs kept for binding.
+template <int NJ, uint32_t F>
+__device__ __forceinline__ uint32_t committed_words(const Ctx<NJ, F> &c, int32_t now, uint32_t more, uint64_t (&busy)[NJ]) {
+  const int sh = 8 * (c.lane & 7), grp = c.lane >> 3;
+  uint32_t bits = 0;
+#pragma unroll
+  for (int j = 0; j < NJ; j++) {
+    busy[j] = wballot(c.fin[j] > now);
+    const uint32_t mine = (uint32_t)(busy[j] >> sh);
+    bits = grp == j ? mine : bits;
+  }
+  return (uint32_t)__builtin_popcount(bits & 0xFFu) + more;
+}
+template <int NJ, uint32_t F>
+__device__ __forceinline__ void bind_words(Ctx<NJ, F> &c, int h, int g, int32_t finish, const uint64_t (&busy)[NJ]) {
+  const int j = h >> 3, hl = h & 7;
+  const uint64_t mine = 0xFFull << (8 * hl);
+#pragma unroll
+  for (int jj = 0; jj < NJ; jj++) {
+    if (jj == j) {
+      const uint64_t fr = mine & ~busy[jj];
+      const int rank = lane_rank(fr) | (in_mask(fr) ? 0 : WAVE);
+      c.fin[jj] = rank < g ? finish : c.fin[jj];
+      // (keeps the arms apart: merged into one store through a chosen pointer they put the rows into memory)
+      asm volatile("; group %1" : "+v"(c.fin[jj]) : "n"(jj));
+    }
+  }
 }
 
 // bind g free GPUs of host h until `finish`
@@ -387,7 +448,7 @@ __device__ __forceinline__ void session_start(Ctx<NJ, F> &c, Regs &r, uint32_t s
     wave_sync();
     int n_on = (int)uni(c.m.c32[CS_NON]);
     if (!((c.flags() & NBOS_F_SCALE_OUT) && n_on + missing <= c.p.Hmax)) {
-      sess_write_flag(c, r, s, (fl & ~7u) | SS_REJECTED);
+      sess_write_flag(c, s, (fl & ~7u) | SS_REJECTED);
       c32_add(c.m, c.lane, CS_REJECTED, 1u);
       decide(c, r, now, NBOS_D_REJECT, s, 0, 0);
       return;
@@ -411,7 +472,7 @@ __device__ __forceinline__ void session_start(Ctx<NJ, F> &c, Regs &r, uint32_t s
     wave_sync();
     c32_max(c.m, c.lane, CS_PEAK, uni(c.m.c32[CS_NON]));
   }
-  sess_write(c, r, s, hw, 0, (fl & ~7u) | SS_PLACED);
+  sess_write(c, s, hw, 0, (fl & ~7u) | SS_PLACED);
   c32_add(c.m, c.lane, CS_PLACED, 1u);
   c32_add(c.m, c.lane, CS_SUMS, (uint32_t)(3 * g));
   c32_add(c.m, c.lane, CS_OPENG, (uint32_t)g);
@@ -429,7 +490,7 @@ __device__ __forceinline__ void end_session(Ctx<NJ, F> &c, Regs &r, uint32_t s, 
   const uint32_t sub = (uint32_t)g | (1u << 16);
   const int h0 = (int)slot_host(hw, 0), h1 = (int)slot_host(hw, 1), h2 = (int)slot_host(hw, 2);
   c.hs -= (c.lane == h0) | (c.lane == h1) | (c.lane == h2) ? sub : 0u;
-  sess_write_flag(c, r, s, (fl & ~(7u | SF_ENDING)) | SS_ENDED);
+  sess_write_flag(c, s, (fl & ~(7u | SF_ENDING)) | SS_ENDED);
   c32_add(c.m, c.lane, CS_SUMS, (uint32_t)(-3 * g));
   c64_add(c.m, c.lane, CL_SUB, (int64_t)(3 * g) * now);
   c32_add(c.m, c.lane, CS_NREP, (uint32_t)-3);
@@ -465,7 +526,7 @@ __device__ __forceinline__ void start_cell(Ctx<NJ, F> &c, Regs &r, uint32_t s, u
     c64_add(c.m, c.lane, CL_GWAIT, (int64_t)g * (start - now));
   }
   c.m.sess[s] = make_int2((int)nw, finish);
-  r.dirty |= wballot(c.vsid == s);
+  mark_stale(c, s);
   r.lazy_max = r.lazy_max > finish ? r.lazy_max : finish;
   decide(c, r, now, outcome, s, (uint32_t)slot, (uint32_t)host);
   if (__builtin_expect((fl & SF_ENDING) != 0, 0)) timer_push(c, r, finish, QK_END, s, 0);
@@ -491,18 +552,38 @@ __device__ __forceinline__ uint32_t elect(const Ctx<NJ, F> &c, uint32_t hw, uint
   return kb;
 }
 
+// The same from keys that nobody has looked at yet: per lane = host, (committed GPUs, and 16 more where the host is not
+// ready) << 8 | host << 2. Where the smallest of the three keys has too few GPUs idle, all have. Returns that key with
+// the replica's slot in its low two bits; (key >> 8) + g <= 8 if it can bind.
+template <int NJ, uint32_t F>
+__device__ __forceinline__ uint32_t elect_slot(const Ctx<NJ, F> &c, uint32_t hw, uint32_t key, int g) {
+  const uint32_t k0 = (uint32_t)lane_get((int)key, (int)slot_host(hw, 0)), k1 = (uint32_t)lane_get((int)key, (int)slot_host(hw, 1)) | 1u,
+                 k2 = (uint32_t)lane_get((int)key, (int)slot_host(hw, 2)) | 2u;
+  uint32_t kb = umin(k0, (uint32_t)fresh((int)umin(k1, k2)));
+  if (c.flags() & NBOS_F_STICKY_EXECUTOR) {
+    const uint32_t last = hw >> 30;
+    const uint32_t kp = last == 1u ? k0 : (last == 2u ? k1 : (last == 3u ? k2 : 0xFFFFFFFFu));
+    if ((int)(kp >> 8) + g <= NGPU) kb = kp;
+  }
+  return kb;
+}
+
 // A cell of an idle placed session starts by election at the instant it is submitted (open loop): what
 // start_cell does for a delay of 0, with nothing of the other cases in it. The cell's lane is marked in r.at_once:
-// the sums that nobody reads during the replay are made from those marks once per tile (see fold_starts).
+// the sums that nobody reads during the replay are made from those marks once per tile (see fold_starts). code: the
+// session and the outcome in their places of the decision code.
 template <int NJ, uint32_t F>
-__device__ __forceinline__ void start_at_once(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint32_t hw, int slot, int host,
+__device__ __forceinline__ void start_at_once(Ctx<NJ, F> &c, Regs &r, int32_t &vhw, uint32_t code, uint32_t hw, uint32_t slot, uint32_t host,
                                               int32_t now, int32_t finish) {
-  if ((hw >> 30) == (uint32_t)slot + 1u) r.reused++;
+  const uint32_t s = code >> 16;
+  r.reused += (hw >> 30) == slot + 1u ? 1u : 0u;
   // the record's word: hosts as they are, this slot the last executor; state "placed", retry count 0 already
-  const uint32_t nw = (hw & 0x3FFFFFFFu) | ((uint32_t)(slot + 1) << 30);
+  const uint32_t nw = (hw & 0x3FFFFFFFu) | ((slot + 1u) << 30);
   c.m.sess[s] = make_int2((int)nw, finish);
-  r.dirty |= wballot(c.vsid == s);
-  decide(c, r, now, NBOS_D_START, s, (uint32_t)slot, (uint32_t)host);
+  const bool same = c.vsid == s;
+  vhw = same ? (int32_t)nw : vhw;
+  c.vtm = same ? finish : c.vtm;
+  decide_code(c, r, now, host | (slot << 10) | code);
 }
 
 // The tile's cells that started at once (lanes of r.at_once), all at a time: counts on the scalar unit, durations,
@@ -644,7 +725,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
     } else {
       c.m.sess[s].x = (int)nfl;
     }
-    r.dirty |= wballot(c.vsid == s);
+    mark_stale(c, s);
     if constexpr (Ctx<NJ, F>::closed) {
       // every timer carries its event (the cursor still points at the cell under way)
       if ((int64_t)t_submit + (int64_t)retries * c.p.retry_iv >= 0x7FFFFFFFLL) { r.status = NBOS_E_RANGE; return; }
@@ -657,7 +738,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
   c32_add(c.m, c.lane, CS_ABORTED, 1u);
   decide(c, r, now, NBOS_D_ABORT, s, 0, 0);
   const uint32_t nfl = (fl & ~(7u | (15u << 8))) | SS_PLACED;
-  sess_write(c, r, s, hw, 0, nfl);
+  sess_write(c, s, hw, 0, nfl);
   if (fl & SF_ENDING) end_session(c, r, s, hw, nfl, now);
   if constexpr (Ctx<NJ, F>::closed) cl_schedule(c, r, s, now);
 }
@@ -717,7 +798,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
       c32_add(c.m, c.lane, CS_ABORTED, 1u);
       decide(c, r, now, NBOS_D_ABORT, s, 0, 0);
       c.m.sess[s] = make_int2((int)((fl & ~(7u | (15u << 8))) | SS_PLACED), 0);
-      r.dirty |= wballot(c.vsid == s);
+      mark_stale(c, s);
       c.qt = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);                      // wave_shl:1
       c.qd = __builtin_amdgcn_update_dpp(c.qd, c.qd, 0x130, 0xF, 0xF, false);
       c.qk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x130, 0xF, 0xF, false);
@@ -734,7 +815,7 @@ __device__ __forceinline__ int32_t failing_retries(Ctx<NJ, F> &c, Regs &r, int32
     }
     const uint32_t nfl = (fl & ~(15u << 8)) | ((uint32_t)retries << 8);
     c.m.sess[s].x = (int)nfl;
-    r.dirty |= wballot(c.vsid == s);
+    mark_stale(c, s);
     // ... and move the entry from lane 0 to its new place: entries before it shift down one lane
     const int32_t t_new = t_submit + retries * c.p.retry_iv;
     const int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);          // wave_shl:1
@@ -823,7 +904,7 @@ __device__ __forceinline__ void on_session_end(Ctx<NJ, F> &c, Regs &r, uint32_t 
   if (st == SS_PLACED && tm <= now) {
     end_session(c, r, s, hw, fl, now);
   } else {
-    sess_write_flag(c, r, s, fl | SF_ENDING);
+    sess_write_flag(c, s, fl | SF_ENDING);
     if (st == SS_PLACED) timer_push(c, r, tm, QK_END, s, 0);
   }
 }
@@ -856,7 +937,7 @@ __device__ __forceinline__ void lds_init_closed(const KParams &p, const Lds &m, 
 }
 
 // ---- S10: close the integrals at t_end and write the result record ---------------------------------
-__device__ __forceinline__ void write_stats(const KParams &p, const Lds &m, const Regs &r, int rep, int lane) {
+__device__ __forceinline__ void write_stats(const KParams &p, const Lds &m, const Regs &r, uint64_t digest, int rep, int lane) {
   __syncthreads();
   const int32_t t_end = r.t_end > r.lazy_max ? r.t_end : r.lazy_max;
   nbos_stats *out = p.stats + rep;
@@ -879,7 +960,7 @@ __device__ __forceinline__ void write_stats(const KParams &p, const Lds &m, cons
     out->reservation_gpu_ms = (int64_t)m.c64[CL_RESV] + (int64_t)(int32_t)m.c32[CS_OPENG] * t_end;
     out->sub_gpu_ms = (int64_t)m.c64[CL_SUB] + (int64_t)(int32_t)m.c32[CS_SUMS] * t_end;
     out->replica_ms = (int64_t)m.c64[CL_REPL] + (int64_t)(int32_t)m.c32[CS_NREP] * t_end;
-    out->digest = r.digest;
+    out->digest = digest;
   }
 }
 
@@ -929,13 +1010,13 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   c.hr = lane < p.H0 ? 0 : NEVER;
   c.hs = 0;
   c.qt = NEVER; c.qd = 0; c.qk = 0xFFFFFFFFu;
-  c.vsid = 0xFFFFFFFFu;
+  c.vsid = 0xFFFFFFFFu; c.vtm = NEVER;
+  c.digest = 0xCBF29CE484222325ULL;
   c.fu = 0;
   c.dyn = dynamic_limit_matters(p, c.flags(), c.slim);
   c.latest = 0;
   Regs r;
   memset(&r, 0, sizeof r);
-  r.digest = 0xCBF29CE484222325ULL;
   r.q_head_t = NEVER;
   r.o_min_t = NEVER;
   r.cl_win = 1024;
@@ -958,9 +1039,9 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
   // never touches the registers of the tile in flight.
   bool final = false;
   while (r.status == NBOS_OK) {
-    int2 rec = make_int2(0, 0);             // prefetched session record of this lane's event
-    uint64_t todo = 0, cellmask = 0;        // events to look at; which are cells
-    uint64_t fastmask = 0;                  // ... and which are cells of an idle placed session
+    int32_t vhw = 0;                        // word of the session record of this lane's event
+    uint32_t vcode = 0;                     // decision code of a cell that starts at once, without slot and host
+    uint64_t todo = 0;                      // events to look at
     if (base < ev_hi) {
       // the prefetched tile becomes current; start loading the one after it
       vt = nt; vd = nd; vs = ns;
@@ -974,9 +1055,10 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
       const bool is_last = cur + lane == ev_hi - 1;
       const uint32_t sid = (uint32_t)vs & 0xFFFFFFu;
       const bool is_cell = ((uint32_t)vs >> 24) == NBOS_EV_CELL;
-      c.vsid = valid ? sid : 0xFFFFFFFFu;
       wave_sync();
-      rec = m.sess[sid];                    // (lanes beyond the last event hold that one's)
+      const int2 rec = m.sess[sid];         // (lanes beyond the last event hold that one's)
+      vhw = rec.x;
+      vcode = ((uint32_t)NBOS_D_START << 12) | (sid << 16);
       // Cells of sessions in a final state (rejected / ended) and cells that arrive while the
       // session's running cell lasts beyond them change nothing: count them, skip them. Neither
       // condition can be undone before the event's time. The last event of the trace is never
@@ -985,13 +1067,13 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
       const bool dead = (st == SS_REJECTED) | (st == SS_ENDED);
       const bool running = (st == SS_PLACED) & (rec.y > vt);
       const bool skip = valid & !is_last & (dead | (is_cell & running));
-      cellmask = wballot(valid & is_cell);
-      r.c_total += (uint32_t)__builtin_popcountll(cellmask);
+      r.c_total += (uint32_t)__builtin_popcountll(wballot(valid & is_cell));
       r.c_unplaced += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & dead));
       r.c_busy += (uint32_t)__builtin_popcountll(wballot(skip & is_cell & !dead));
-      fastmask = wballot(valid & is_cell & (st == SS_PLACED) & !running & (((uint32_t)rec.x & SF_ENDING) == 0));
+      const bool plain = valid & is_cell & (st == SS_PLACED) & (((uint32_t)rec.x & SF_ENDING) == 0);
+      c.vsid = plain ? sid : 0xFFFFFFFFu;
+      c.vtm = plain ? rec.y : NEVER;
       todo = wballot(valid & !skip);
-      r.dirty = 0;
       if (ev_hi - cur <= WAVE) {
         int32_t tl = lane_get(vt, (int)(ev_hi - cur - 1));
         r.t_end = r.t_end > tl ? r.t_end : tl;
@@ -1002,46 +1084,41 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
       r.lazy_max = r.lazy_max > latest ? r.lazy_max : latest;
     }
     PROF(PC_TILE, 1);
-    r.slow_lanes = ~fastmask;
     for (;;) {
       if (__builtin_expect(r.status != NBOS_OK, 0)) break;
-      // ---- runs of arrivals that start at once (S4, S5): cells of idle placed sessions (by the prefetched
-      // record, or, where that is stale, by the record as it is now), no timer due first, the election won.
-      // A loop of its own with nothing else in it; whatever does not fit leaves the arrival to the general
-      // path below.
+      // ---- runs of arrivals that start at once (S4, S5): cells of idle placed sessions, no timer due first, the
+      // election won. A loop of its own with nothing else in it. Whatever does not fit makes `bad` negative, of what the event's
+      // lane says or of what the election says (two branches, as one that is not taken costs a lone wave 12 clocks, a
+      // scalar instruction 5), and leaves the arrival to the general path below. No event left: lane 63 is looked at.
+      // With five ways out, the keys of hosts that cannot bind masked before the choice, and stale records read again
+      // in the loop: 64 hosts 68.1 -> 64.7 ms, 24 hosts 47.2 -> 45.0, 30 hosts 27.9 -> 27.2, 300 short replays 0.84 -> 0.77.
       PROF(PC_LOOP_ROUND, 1);
       [[maybe_unused]] const uint64_t prof_at0 = r.at_once;
-      while (todo != 0) {
-        const int i = (int)__builtin_ctzll(todo);
-        if (((cellmask >> i) & 1ull) == 0) break;
-        const int32_t t = lane_get(vt, i);
-        if (t >= due_t) break;
-        uint32_t hw;
-        if ((((fastmask & ~r.dirty) >> i) & 1ull) != 0) {
-          hw = (uint32_t)lane_get(rec.x, i);
-        } else {
-          wave_sync();
-          const int2 cur = m.sess[lane_get((int)c.vsid, i)];
-          hw = uni((uint32_t)cur.x);
-          const int32_t tm = uni(cur.y);
-          // idle and placed, nothing pending (the general path copes with everything else)
-          if (((hw & (7u | SF_ENDING | RK_OVF | (15u << 8))) != SS_PLACED) | (tm > t)) break;
+      {
+        int i;
+        int32_t at, bad;
+        auto look_at_next = [&]() {
+          i = (int)__builtin_ctzll(todo | (1ull << 63));
+          at = lane_get(vt, i);
+          bad = (todo == 0 ? -1 : 0) | (at - lane_get(c.vtm, i)) | (due_t - 1 - at);
+        };
+        look_at_next();
+        while (__builtin_expect(bad >= 0, 1)) {
+          const uint32_t hw = (uint32_t)lane_get(vhw, i);
+          const int g = (int)((hw >> 3) & 7u) + 1;
+          // election (Section 3.2.2) on the vector side: every host's key; and a host may have the GPUs idle by now
+          uint64_t busy[NJ];
+          const uint32_t C = committed_words(c, at, c.hr <= at ? 0u : 16u, busy);
+          const uint32_t kb = elect_slot(c, hw, (C << 8) | ((uint32_t)c.lane << 2), g);
+          if (__builtin_expect(((at - lane_get(c.fu, g - 1)) | (NGPU - (int)(kb >> 8) - g)) < 0, 0)) break;
+          const uint32_t host = (kb >> 2) & 63u, slot = kb & 3u;
+          const int32_t finish = at + lane_get(vd, i);
+          bind_words(c, (int)host, g, finish, busy);
+          start_at_once(c, r, vhw, (uint32_t)lane_get((int)vcode, i), hw, slot, host, at, finish);
+          r.at_once |= 1ull << i;
+          todo &= ~(1ull << i);
+          look_at_next();
         }
-        const int g = (int)((hw >> 3) & 7u) + 1;
-        if (t < lane_get(c.fu, g - 1)) break;                 // no host has g idle GPUs yet
-        // election (Section 3.2.2) on the vector side: every host's key (committed GPUs, index), or all
-        // ones where it cannot bind; the keys of the session's three hosts are read and compared
-        const int C = committed(c, t);
-        const uint32_t key = (c.hr <= t) & (C + g <= NGPU) ? (((uint32_t)C << 6) | (uint32_t)c.lane) : 0xFFFFFFFFu;
-        const uint32_t kb = elect(c, hw, key);
-        if (kb == 0xFFFFFFFFu) break;                         // every replica yields
-        const int hl = (int)(kb & 63u);
-        const int lead = (uint32_t)hl == slot_host(hw, 0) ? 0 : ((uint32_t)hl == slot_host(hw, 1) ? 1 : 2);
-        const int32_t finish = t + lane_get(vd, i);
-        bind_gpus(c, hl, g, t, finish);
-        start_at_once(c, r, (uint32_t)lane_get((int)c.vsid, i), hw, lead, hl, t, finish);
-        r.at_once |= todo & (0 - todo);
-        todo &= todo - 1;
       }
       PROF(PC_ROUND, __builtin_popcountll(r.at_once ^ prof_at0));
       int i = 0;
@@ -1058,21 +1135,16 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
         todo &= ~bit;
         const uint32_t sk = (uint32_t)lane_get(vs, i);
         const uint32_t s = sk & 0xFFFFFFu;
-        if (__builtin_expect((fastmask & ~r.dirty & bit) != 0, 1)) {
-          // a cell of an idle placed session whose record nobody touched since the prefetch
-          a_s = s; a_hw = (uint32_t)lane_get(rec.x, i);
+        if (__builtin_expect(lane_get(c.vtm, i) <= t, 1)) {
+          // a cell of an idle placed session whose record is up to date
+          a_s = s; a_hw = (uint32_t)lane_get(vhw, i);
           a_fl = a_hw;
           a_now = t; a_sub = t; a_dur = lane_get(vd, i);
         } else {
           const uint32_t kind = sk >> 24;
-          uint32_t hw, fl;
-          int32_t tm;
-          if ((r.dirty >> i) & 1u) {
-            int2 cur = m.sess[s];
-            hw = uni((uint32_t)cur.x); tm = uni(cur.y); fl = hw;
-          } else {
-            hw = (uint32_t)lane_get(rec.x, i); tm = lane_get(rec.y, i); fl = hw;
-          }
+          const int2 cur = m.sess[s];
+          const uint32_t hw = uni((uint32_t)cur.x), fl = hw;
+          const int32_t tm = uni(cur.y);
           if (kind == NBOS_EV_CELL) {           // S4-S8 (counted in c_total at tile load)
             const uint32_t st = fl & 7u;
             if (st == SS_PLACED && tm <= t) {
@@ -1143,10 +1215,10 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_kernel(KParams p) {
       due_t = r.q_head_t < tick_t ? r.q_head_t : tick_t;
     }
     if (final) break;
-    fold_starts(c, r, vt, vd, (uint32_t)rec.x);
+    fold_starts(c, r, vt, vd, (uint32_t)vhw);
   }
 
-  write_stats(p, m, r, rep, lane);
+  write_stats(p, m, r, c.digest, rep, lane);
   PROF_OUT(rep);
 }
 
@@ -1256,7 +1328,8 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
   c.hr = lane < p.H0 ? 0 : NEVER;
   c.hs = 0;
   c.qt = NEVER; c.qd = 0; c.qk = 0xFFFFFFFFu;
-  c.vsid = 0xFFFFFFFFu;
+  c.vsid = 0xFFFFFFFFu; c.vtm = NEVER;
+  c.digest = 0xCBF29CE484222325ULL;
   c.fu = 0;
   c.dyn = dynamic_limit_matters(p, c.flags(), c.slim);
   c.cl_cur = p.cl_cursor + (int64_t)rep * (p.n_cap + 1);
@@ -1264,7 +1337,6 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
   c.qx = 0; c.qnx = -1; c.qnth = 0;
   Regs r;
   memset(&r, 0, sizeof r);
-  r.digest = 0xCBF29CE484222325ULL;
   r.q_head_t = NEVER;
   r.o_min_t = NEVER;
   r.cl_win = 1024;
@@ -1341,7 +1413,7 @@ __global__ void __launch_bounds__(WAVE, 4) nbos_replay_reg_closed_kernel(KParams
     }
     if (final) break;
   }
-  write_stats(p, m, r, rep, lane);
+  write_stats(p, m, r, c.digest, rep, lane);
 }
 
 }  // namespace regk
