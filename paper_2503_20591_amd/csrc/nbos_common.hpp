@@ -150,6 +150,9 @@ __device__ __forceinline__ void wave_sync() {
 __host__ __device__ __forceinline__ int32_t wrap_add(int32_t a, int32_t b) { return (int32_t)((uint32_t)a + (uint32_t)b); }
 // a closed loop's next event: think time after the finish of the cell that started at t
 __host__ __device__ __forceinline__ int32_t next_event_time(int32_t t, int32_t dur, int32_t think) { return wrap_add(wrap_add(t, dur), think); }
+// a job of the Batch baseline that holds its GPUs from start on (a lane without one: an earlier job's start, and of a START
+// or END event a duration that nobody has checked)
+__host__ __device__ __forceinline__ int32_t job_finish(int32_t start, int32_t held) { return wrap_add(start, held); }
 // the n-th retry of a cell
 __host__ __device__ __forceinline__ int32_t retry_time(int32_t t_submit, int32_t n, int32_t interval) {
   return wrap_add(t_submit, (int32_t)((uint32_t)n * (uint32_t)interval));

@@ -334,7 +334,7 @@ __device__ __forceinline__ void save_records(Ctx<NS> &c, State &r) {
   wave_sync();
   const bool mine = in_mask(jobs);
   const int s = (int)(c.vjob & 0xFFFFu);
-  *(mine ? &c.m.time[s] : c.m.stage_t + WAVE) = c.vstart + c.vfd;
+  *(mine ? &c.m.time[s] : c.m.stage_t + WAVE) = job_finish(c.vstart, c.vfd);
   *(mine ? &c.m.meta[s] : c.m.stage_k + WAVE) = c.vhost | (((c.vjob >> 16) & 7u) << G_SHIFT);
   r.started |= jobs;
   r.unsaved = r.todo;
@@ -593,7 +593,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     sum_g += one * g;
     sum_wait += wait;
     max_wait = max(max_wait, (int32_t)wait);
-    latest = max(latest, mine ? c.vstart + c.vfd : 0);
+    latest = max(latest, mine ? job_finish(c.vstart, c.vfd) : 0);
     const int b = min(32 - __builtin_clz(wait + (uint32_t)p.batch_delay), 31);      // (of a wait of 0: not looked at)
     atomicAdd(&m.hist[wait != 0u ? b : 32 + lane], 1u);
   }
