@@ -158,14 +158,19 @@ __host__ __device__ __forceinline__ int32_t retry_time(int32_t t_submit, int32_t
   return wrap_add(t_submit, (int32_t)((uint32_t)n * (uint32_t)interval));
 }
 
+// t + by (neither below 0), at most the end of the range
+__host__ __device__ __forceinline__ int32_t add_in_range(int32_t t, int32_t by) {
+  const uint32_t sum = (uint32_t)t + (uint32_t)by;
+  return (int32_t)(sum < (uint32_t)NEVER ? sum : (uint32_t)NEVER);
+}
+
 // `by` after t. An open loop's times are checked against the range when the replay is created; the lag of a closed
 // loop is not bounded in advance, and a time beyond the range stays at its end (a cell's start there ends the replay,
 // a pre-warmed container is never available again).
 template <class C>
 __host__ __device__ __forceinline__ int32_t after(const C &, int32_t t, int32_t by) {
   if constexpr (!C::closed) return t + by;
-  const uint32_t sum = (uint32_t)t + (uint32_t)by;
-  return (int32_t)(sum < (uint32_t)NEVER ? sum : (uint32_t)NEVER);
+  return add_in_range(t, by);
 }
 
 // c ? a : b without a branch, whatever a and b take to work out (the compiler likes to move that into an arm)

@@ -361,13 +361,13 @@ __device__ __forceinline__ void fold_jobs(Ctx<NS> &c, State &r, uint64_t *dlog, 
 template <int NS>
 __device__ __forceinline__ void ask_for_host(Ctx<NS> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
   if (!(c.p.flags & NBOS_F_SCALE_OUT) || r.n_on >= c.p.Hmax) return;
-  const int64_t up = (int64_t)T + c.p.boot;
-  r.status = up >= 0x7FFFFFFFLL ? (int32_t)NBOS_E_RANGE : r.status;
+  const int32_t up = add_in_range(T, c.p.boot);          // (a host that comes up at the end of the range ends the replay)
+  r.status = up == NEVER ? (int32_t)NBOS_E_RANGE : r.status;
   const int h = r.n_on++;                              // hosts are added in order and never go
   r.prov -= (int64_t)c.p.G * T;
-  c.m.ready[h] = (int32_t)up;
-  r.up_t = r.next_up == h ? (int32_t)up : r.up_t;
-  r.latest_up = max(r.latest_up, (int32_t)up);
+  c.m.ready[h] = up;
+  r.up_t = r.next_up == h ? up : r.up_t;
+  r.latest_up = max(r.latest_up, up);
   fold_jobs(c, r, dlog, (r.started | (r.unsaved & ~r.todo)) & ~r.folded);
   const uint64_t code = decision_code(T, NBOS_D_BATCH_HOST, s, 0u, (uint32_t)h);
   r.digest = r.digest * DIGEST_PRIME + code;

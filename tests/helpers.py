@@ -52,3 +52,20 @@ def late_in_a_closed_loop(how, left, first_dur=1):
     for s in (1, 2, 3):                                            # a day, and on to the last second but one
         ev += [[latest - 10, 1, s, day], [latest - 10, 1, s, end - 2 - (latest - 10 + day)]]
     return cfg, sorted(ev), [8] * 5
+
+
+def late_batch_host(up, lead=0):
+    """A Batch queue whose last request for a host, made when none is being provisioned, asks for one that comes up at ``up``:
+    (config, events, GPUs). All jobs need a whole host, hosts take 12 h to come up. The jobs arrive 48 h before ``up``; two days
+    of waiting bring the fourth request to 12 h before ``up``, and the job that makes it runs a minute later on a host that
+    is over by then. ``lead``: short jobs of another session at the trace's start."""
+    from paper_2503_20591_amd import tracegen as tg
+    hour, minute = 3_600_000, 60_000
+    cfg = dict(tg.base_config(hosts_initial=1, hosts_max=5, flags=tg.F_BATCH_MODE | tg.F_SCALE_OUT), boot_delay_ms=12 * hour,
+               batch_start_delay_ms=0)
+    # hosts asked for at 0, 12, 24, 36 h; jobs start at 0 (host 0), 12 (1), 24 (0 again, and 2), 36 (1 again, and 3), 36 h 1 min
+    durations = [24 * hour, 24 * hour, 23 * hour, 12 * hour + minute, 11 * hour, 11 * hour, 1]
+    arrive = up - 48 * hour
+    ev = [[2 * i, 1, 7, 1] for i in range(lead)]
+    ev += [[arrive, 1, s, d] for s, d in enumerate(durations)]
+    return cfg, ev, [8] * 8

@@ -9,7 +9,7 @@ import os
 import numpy as np
 import pytest
 
-from helpers import GOLDEN, code_of, digest_of, events_to_arrays, late_in_a_closed_loop, load_golden
+from helpers import GOLDEN, code_of, digest_of, events_to_arrays, late_batch_host, late_in_a_closed_loop, load_golden
 from paper_2503_20591_amd import tracegen as tg
 
 pytestmark = pytest.mark.gpu
@@ -335,6 +335,40 @@ def test_batch_mode_time_range(rp, oracle):
     b = tg._pack(cfg, [(t, d, sk, np.full(n, 8, np.uint8))], [0], [1000], "no-overflow")
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
+
+
+@pytest.mark.parametrize("lead", [0, 150])
+def test_batch_mode_time_range_of_added_hosts(rp, oracle, lead):
+    # a host asked for while none is being provisioned, in the first tile of events or a later one: it comes up at the
+    # last time there is, or beyond that, and the replay is invalid on both sides
+    cfg, ev, gp = late_batch_host(2**31 - 2, lead)
+    b = _tiny(cfg, ev, gp, [1000, 1000])
+    st, logs = gpu_run(rp, b, log=True)
+    assert_same(rp, oracle, b, st, logs, check=True)
+    assert (st["t_end_ms"] == 2**31 - 2).all() and (st["scale_out_hosts"] == 4).all()
+    for up in (2**31 - 1, 2**31, 2**31 + 1):
+        b = _tiny(*late_batch_host(up, lead), [1000, 1000])
+        with pytest.raises(ValueError) as e:
+            oracle.replay_batch(b)
+        assert e.value.args[1] == -2
+        st, _ = gpu_run(rp, b, log=True)
+        assert (st["status"] == rp.E_RANGE).all()
+
+
+def test_batch_mode_time_range_past_the_first_tile(rp, oracle):
+    # the job that ends at the last time there is, or beyond it, comes after more than 64 events
+    for last, fine in ((2**31 - 2 - 24 * 86_400_000 - 1_000, True), (2**31 - 1 - 24 * 86_400_000 - 1_000, False)):
+        ev = [[2 * i, 1, 31, 1] for i in range(150)]
+        ev += [[1_000 + (i > 0), 1, i, 86_400_000 if i < 24 else last] for i in range(25)]
+        b = _tiny(tg.base_config(hosts_initial=1, hosts_max=1, flags=tg.F_BATCH_MODE), ev, [8] * 32, [1000])
+        st, logs = gpu_run(rp, b, log=True)
+        if fine:
+            assert_same(rp, oracle, b, st, logs, check=True)
+            assert (st["t_end_ms"] == 2**31 - 2).all()
+        else:
+            with pytest.raises(ValueError):
+                oracle.replay_batch(b)
+            assert (st["status"] == rp.E_RANGE).all()
 
 
 def test_batch_mode_rejects_other_policy_flags(rp):

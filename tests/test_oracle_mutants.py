@@ -83,6 +83,7 @@ MUTANTS = [
     ("batch: every queued job asks for a server", "j->asked = 1;", "", "nbos_oracle_batch.c"),
     ("batch: timers due at an arrival run after it", "m.heap[0].time <= t && !m.err) run_instant(&m);", "m.heap[0].time < t && !m.err) run_instant(&m);", "nbos_oracle_batch.c"),
     ("batch: queue looked at between two timers of one instant", "    }\n  }\n  dispatch(m);\n}", "    }\n    dispatch(m);\n  }\n  dispatch(m);\n}", "nbos_oracle_batch.c"),
+    ("batch: a server that comes up beyond the time range is accepted", "if ((int64_t)m->clock + m->p->boot_delay_ms >= 2147483647LL)", "if (0)", "nbos_oracle_batch.c"),
     ("warm pool: takes the newest container", "if (d->warm[i] < d->warm[w]) w = i;", "if (d->warm[i] > d->warm[w]) w = i;"),
     ("warm pool: never refilled", "d->warm[w] = m->clock + m->p->prewarm_delay_ms;", "d->warm[w] = 2147483647;"),
     ("warm pool: refilled at once", "d->warm[w] = m->clock + m->p->prewarm_delay_ms;", ""),
@@ -163,7 +164,8 @@ def run_pins(lib_path):
     checks += [lambda h=h: pins.test_closed_loop_start_beyond_the_time_range(o, h) for h in ("migrate", "grow")]
     checks.append(lambda: pins.test_closed_loop_container_beyond_the_time_range(o))
     checks += [lambda s=s: pins.test_warm_pool_that_refills_at_once_is_a_shorter_delay(o, s) for s in range(3)]
-    checks += [lambda: pins.test_batch_single_server_is_the_textbook_fifo_queue(o), lambda: pins.test_batch_without_contention(o)]
+    checks += [lambda: pins.test_batch_single_server_is_the_textbook_fifo_queue(o), lambda: pins.test_batch_without_contention(o),
+               lambda: pins.test_batch_host_beyond_the_time_range(o)]
     checks += [lambda s=s: pins.test_batch_order_and_capacity_random(o, s) for s in range(6)]
     checks += [lambda: pins.test_billing_printed_example(o), lambda: pins.test_billing_is_linear_and_exact_on_large_results(o),
                lambda: pins.test_billing_without_replicas_has_no_standby_charge(o)]

@@ -10,7 +10,7 @@ import os
 import numpy as np
 import pytest
 
-from helpers import code_of, digest_of, events_to_arrays, late_in_a_closed_loop, load_golden, GOLDEN
+from helpers import code_of, digest_of, events_to_arrays, late_batch_host, late_in_a_closed_loop, load_golden, GOLDEN
 from paper_2503_20591_amd import tracegen as tg
 
 S, CELL, END = 0, 1, 2
@@ -592,6 +592,20 @@ def test_batch_single_server_is_the_textbook_fifo_queue(oracle):
                [(b, i, 0, oracle.D_BATCH_START) for i, b in enumerate(begins)]
         assert r["cells_immediate"] == sum(1 for i in range(n) if begins[i] == int(t[i]))
         assert r["gpu_ms_committed"] == 8 * (n * Dc + int(d.sum())) and r["gpu_ms_executed"] == 8 * int(d.sum())
+
+
+def test_batch_host_beyond_the_time_range(oracle):
+    # the last host asked for comes up at the last time there is, or the replay is invalid
+    cfg, ev, gp = late_batch_host(2**31 - 2)
+    r = run(oracle, cfg, ev, gp, 1000, want_log=True)
+    asked = [d["time"] for d in map(oracle.decode, r["log"]) if d["outcome"] == oracle.D_BATCH_HOST]
+    assert [2**31 - 2 - t for t in asked] == [h * 3_600_000 for h in (48, 36, 24, 12)]
+    assert r["t_end_ms"] == 2**31 - 2 and r["cells_started"] == 7 and r["max_delay_ms"] == 36 * 3_600_000 + 60_000
+    for up in (2**31 - 1, 2**31, 2**31 + 1):
+        cfg, ev, gp = late_batch_host(up)
+        with pytest.raises(ValueError) as e:
+            run(oracle, cfg, ev, gp, 1000)
+        assert e.value.args[1] == -2
 
 
 def test_batch_without_contention(oracle):
