@@ -6,7 +6,11 @@
 // as full), 64 hosts to a word, level 8 left out: lane 8 l + w holds the word of hosts 64 w .. 64 w + 63 on level l,
 // for each set of 512 hosts (NS of them) a pair of registers. A job takes the ready host with the fewest held GPUs (ties:
 // lowest index): the first bit of the first lane that has one, found by two bit scans, and it fits there or nowhere.
-// A job or a completion flips one bit in each of two lanes.
+// A job or a completion flips one bit in each of two lanes. On up to 64 hosts (NW = 1) lane l holds the one word of
+// level l, and level 8 is there as well: every host is in exactly one lane, so that a completion's two lanes are a ballot
+// and that ballot shifted by g. Many replays of a small cluster share a compute unit and are bound by its scalar unit,
+// not by latency: 46 scalar instructions per job and completion in place of 67 take 4,096 replays of 16, 30 and 64 hosts
+// with 3,000 cells from 2.86, 2.56 and 3.44 ms to 2.34, 2.08 and 2.81 (with a key per host 2.35, 2.31 and 3.35).
 // Completions: the earliest ones, in the order of their times, in registers (qt, qk: entry i in lane i, qe of them,
 // at most 63): all running jobs that finish up to win_t. With more than MID_CAP sessions (p.batch) those that
 // finish up to mid_t are in a list in LDS as well (mid_t[], mid_k[], in no order), the others are found in the session
@@ -54,8 +58,12 @@ struct Lds {
   int32_t *ready;               // [hosts] when a host that was added comes up
 };
 
-template <int NS>
+// NW: words of 64 hosts per level (1, 8, or 16 in two sets of 8)
+template <int NW>
 struct Ctx {
+  static constexpr int NS = NW > 8 ? 2 : 1;
+  static constexpr int PER = NW > 8 ? 8 : NW;         // lanes per level
+  static constexpr bool ALL_LEVELS = 9 * PER <= WAVE;  // full hosts have lanes, too
   const KParams &p;
   Lds m;
   int lane;
@@ -96,11 +104,11 @@ struct State {
 };
 
 // the host (set, word, bit) that the lanes of `flip` stand for moves between the levels of those lanes
-template <int NS>
-__device__ __forceinline__ void flip_host(Ctx<NS> &c, uint64_t flip, uint32_t h) {
+template <int NW>
+__device__ __forceinline__ void flip_host(Ctx<NW> &c, uint64_t flip, uint32_t h) {
 #pragma unroll
-  for (int s = 0; s < NS; s++) {
-    const uint64_t here = NS == 1 || (int)(h >> 9) == s ? flip : 0ull;
+  for (int s = 0; s < c.NS; s++) {
+    const uint64_t here = c.NS == 1 || (int)(h >> 9) == s ? flip : 0ull;
     const uint64_t bit = (uint64_t)(in_mask(here) ? 1u : 0u) << (h & 63u);
     c.lo[s] ^= (uint32_t)bit;
     c.hi[s] ^= (uint32_t)(bit >> 32);
@@ -108,12 +116,17 @@ __device__ __forceinline__ void flip_host(Ctx<NS> &c, uint64_t flip, uint32_t h)
 }
 
 // the g GPUs that a job held on host h are idle again (a host that comes up: all G); returns the host's lane from now on
-template <int NS>
-__device__ __forceinline__ int give_back(Ctx<NS> &c, uint32_t h, int g) {
-  const uint32_t w = (h >> 6) & 7u;
+template <int NW>
+__device__ __forceinline__ int give_back(Ctx<NW> &c, uint32_t h, int g) {
   uint32_t lo = c.lo[0], hi = c.hi[0];
-  if constexpr (NS == 2) { lo = h >> 9 ? c.lo[1] : lo; hi = h >> 9 ? c.hi[1] : hi; }
+  if constexpr (Ctx<NW>::NS == 2) { lo = h >> 9 ? c.lo[1] : lo; hi = h >> 9 ? c.hi[1] : hi; }
   const uint32_t there = (uint32_t)((((uint64_t)hi << 32) | lo) >> (h & 63u)) & 1u;
+  if constexpr (Ctx<NW>::ALL_LEVELS) {
+    const uint32_t from = (uint32_t)wballot(there != 0u), to = from >> g;
+    flip_host(c, from | to, h);
+    return __builtin_ctz(to);
+  }
+  const uint32_t w = (h >> 6) & 7u;
   const uint64_t from = wballot(there != 0u) & (0x0101010101010101ull << w);      // no lane: the host was full
   const uint64_t full = from == 0 ? 1ull << w : 0ull;          // (g = 8 is a full host: then `from` is 0)
   const uint64_t to = (from >> (8 * (g & 7))) | (full << ((64 - 8 * g) & 63));
@@ -127,8 +140,8 @@ __device__ __forceinline__ int32_t due_time(const State &r) { return min(min(r.q
 // Which of the n times at `times` lie in [from, from + win]? They and their keys come to lie side by side in stage_t and
 // stage_k (the first 64); returned are how many there are, and the earliest time beyond (as a distance from `from`; 2^31
 // or more: none). Times before `from` wrap to large distances. Both arrays are read four at a time.
-template <int NS>
-__device__ __forceinline__ int scan_window(const Ctx<NS> &c, const int32_t *times, const uint32_t *keys, int n, int32_t from, uint32_t win, uint32_t &left) {
+template <int NW>
+__device__ __forceinline__ int scan_window(const Ctx<NW> &c, const int32_t *times, const uint32_t *keys, int n, int32_t from, uint32_t win, uint32_t &left) {
   const int4 *time4 = (const int4 *)times, *key4 = (const int4 *)keys;
   int cnt = 0;
   uint32_t mn = 0xFFFFFFFFu;
@@ -158,8 +171,8 @@ __device__ __forceinline__ int scan_window(const Ctx<NS> &c, const int32_t *time
 
 // The list in LDS anew: the running jobs that finish within a window from `from` on, at most MID_CAP (the window adapts
 // to find 192 to 384); more at one instant: none, and the registers are refilled from the records.
-template <int NS>
-__device__ __forceinline__ void list_jobs(Ctx<NS> &c, State &r, int32_t from) {
+template <int NW>
+__device__ __forceinline__ void list_jobs(Ctx<NW> &c, State &r, int32_t from) {
   const int4 *time4 = (const int4 *)c.m.time, *key4 = (const int4 *)c.m.meta;
   const int quads = (c.n_sess + 3) >> 2;
   uint32_t win = (uint32_t)r.mid_win;
@@ -205,8 +218,8 @@ __device__ __forceinline__ void list_jobs(Ctx<NS> &c, State &r, int32_t from) {
 
 // The list in the registers is empty and time goes on beyond win_t, at most to t: the completions of the next window come in.
 // More than fit into the registers at one instant: they are all applied at once if they are due at t, or left until they are.
-template <int NS>
-__device__ __forceinline__ void refill(Ctx<NS> &c, State &r, int32_t t) {
+template <int NW>
+__device__ __forceinline__ void refill(Ctx<NW> &c, State &r, int32_t t) {
   wave_sync();
   const bool few = c.p.batch == 0;
   int32_t from = r.win_t + 1;
@@ -267,8 +280,8 @@ __device__ __forceinline__ void refill(Ctx<NS> &c, State &r, int32_t t) {
 }
 
 // a job that finishes at f goes into the list in the registers (there is room)
-template <int NS>
-__device__ __forceinline__ void insert_completion(Ctx<NS> &c, State &r, int32_t f, uint32_t k) {
+template <int NW>
+__device__ __forceinline__ void insert_completion(Ctx<NW> &c, State &r, int32_t f, uint32_t k) {
   const int pos = __builtin_popcountll(wballot(c.qt <= f));
   const int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x138, 0xF, 0xF, false);          // wave_shr:1
   const uint32_t sk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x138, 0xF, 0xF, false);
@@ -281,8 +294,8 @@ __device__ __forceinline__ void insert_completion(Ctx<NS> &c, State &r, int32_t 
 
 // The job that has started finishes at p_f <= mid_t, and there was no room where that belongs: the list in LDS is given
 // up, or (if the registers are still full) the latest instant in the registers, and that list with it.
-template <int NS>
-__device__ __forceinline__ void make_room(Ctx<NS> &c, State &r) {
+template <int NW>
+__device__ __forceinline__ void make_room(Ctx<NW> &c, State &r) {
   const int32_t f = r.p_f;
   r.p_f = -1;
   if (f <= r.win_t) {
@@ -301,22 +314,23 @@ __device__ __forceinline__ void make_room(Ctx<NS> &c, State &r) {
 }
 
 // the next completion leaves the list
-template <int NS>
-__device__ __forceinline__ void pop_completion(Ctx<NS> &c, State &r) {
+template <int NW>
+__device__ __forceinline__ void pop_completion(Ctx<NW> &c, State &r) {
   c.qt = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);                // wave_shl:1
   c.qk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x130, 0xF, 0xF, false);
   r.qe--;
   r.q_t = lane_get(c.qt, 0); r.q_k = (uint32_t)lane_get((int)c.qk, 0);
 }
 
-// The ready host with the fewest held GPUs, lowest index first: its lane (8 level + word; 64: all are full).
+// The ready host with the fewest held GPUs, lowest index first: its lane (8 level + word; beyond level 7: all are full).
 // The choice of the set comes back in `set`.
-template <int NS>
-__device__ __forceinline__ int best_lane(const Ctx<NS> &c, int &set) {
+template <int NW>
+__device__ __forceinline__ int best_lane(const Ctx<NW> &c, int &set) {
   const uint64_t a = wballot((c.lo[0] | c.hi[0]) != 0u);
-  int L = a != 0 ? (int)__builtin_ctzll(a) : WAVE;
   set = 0;
-  if constexpr (NS == 2) {
+  if constexpr (Ctx<NW>::ALL_LEVELS) return (int)__builtin_ctzll(a);     // (a host is in some lane)
+  int L = a != 0 ? (int)__builtin_ctzll(a) : WAVE;
+  if constexpr (Ctx<NW>::NS == 2) {
     const uint64_t b = wballot((c.lo[1] | c.hi[1]) != 0u);
     const int L1 = b != 0 ? (int)__builtin_ctzll(b) : WAVE;
     set = (L1 >> 3) < (L >> 3) ? 1 : 0;
@@ -324,12 +338,13 @@ __device__ __forceinline__ int best_lane(const Ctx<NS> &c, int &set) {
   }
   return L;
 }
-__device__ __forceinline__ bool fits(int L, int g) { return (L >> 3) + g <= NGPU; }
+template <int NW>
+__device__ __forceinline__ bool fits(const Ctx<NW> &, int L, int g) { return L / Ctx<NW>::PER + g <= NGPU; }
 
 // The records of the tile's jobs that have started since this was last done (before anyone looks at the records: a refill,
 // a second arrival of a session in the tile, the next tile).
-template <int NS>
-__device__ __forceinline__ void save_records(Ctx<NS> &c, State &r) {
+template <int NW>
+__device__ __forceinline__ void save_records(Ctx<NW> &c, State &r) {
   const uint64_t jobs = r.unsaved & ~r.todo;
   wave_sync();
   const bool mine = in_mask(jobs);
@@ -341,8 +356,8 @@ __device__ __forceinline__ void save_records(Ctx<NS> &c, State &r) {
 }
 
 // The decisions of the tile's jobs in `jobs` go into the digest (they are the latest ones), and into the log.
-template <int NS>
-__device__ __forceinline__ void fold_jobs(Ctx<NS> &c, State &r, uint64_t *dlog, uint64_t jobs) {
+template <int NW>
+__device__ __forceinline__ void fold_jobs(Ctx<NW> &c, State &r, uint64_t *dlog, uint64_t jobs) {
   const uint32_t lo = c.vhost | ((uint32_t)NBOS_D_BATCH_START << 12) | (c.vjob << 16);
   r.digest = fold_decisions(r.digest, c.power, jobs, lo, (uint32_t)c.vstart);
   if (__builtin_expect(dlog != nullptr, 0)) {
@@ -358,8 +373,8 @@ __device__ __forceinline__ void fold_jobs(Ctx<NS> &c, State &r, uint64_t *dlog, 
 }
 
 // the job of session s finds no host at time T: it asks for one more host
-template <int NS>
-__device__ __forceinline__ void ask_for_host(Ctx<NS> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
+template <int NW>
+__device__ __forceinline__ void ask_for_host(Ctx<NW> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
   if (!(c.p.flags & NBOS_F_SCALE_OUT) || r.n_on >= c.p.Hmax) return;
   const int32_t up = add_in_range(T, c.p.boot);          // (a host that comes up at the end of the range ends the replay)
   r.status = up == NEVER ? (int32_t)NBOS_E_RANGE : r.status;
@@ -377,7 +392,7 @@ __device__ __forceinline__ void ask_for_host(Ctx<NS> &c, State &r, uint64_t *dlo
   r.n_dec++;
 }
 
-template <int NS>
+template <int NW>
 __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int rep = launch_slot_replay(p);
@@ -409,15 +424,16 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   for (int s = lane; s < n_sess; s += WAVE) m.meta[s] = ((uint32_t)p.sess_gpus[s_lo + s] - 1u) << G_SHIFT;
   __syncthreads();
 
-  Ctx<NS> c{p, m, lane, n_sess, few ? 0 : MID_CAP};
+  Ctx<NW> c{p, m, lane, n_sess, few ? 0 : MID_CAP};
 #pragma unroll
-  for (int s = 0; s < NS; s++) {
-    // the hosts that are there from the start are on the level of the slots that are not
-    const int n = min(max(p.H0 - 512 * s - 64 * (lane & 7), 0), 64);
-    const uint64_t bits = n == 64 ? ~0ull : (1ull << n) - 1ull;
-    const bool here = (lane >> 3) == NGPU - p.G;
-    c.lo[s] = here ? (uint32_t)bits : 0u;
-    c.hi[s] = here ? (uint32_t)(bits >> 32) : 0u;
+  for (int s = 0; s < c.NS; s++) {
+    // the hosts that are there from the start are on the level of the slots that are not; the others count as full
+    const int n = min(max(p.H0 - 512 * s - 64 * (lane % c.PER), 0), 64);
+    const uint64_t on = n == 64 ? ~0ull : (1ull << n) - 1ull;
+    const int level = lane / c.PER;
+    const uint64_t bits = level == NGPU - p.G ? on : c.ALL_LEVELS & (level == NGPU) ? ~on : 0ull;
+    c.lo[s] = (uint32_t)bits;
+    c.hi[s] = (uint32_t)(bits >> 32);
   }
   c.qt = NEVER; c.qk = 0;
   c.vt = 0; c.vfd = 0; c.vjob = 0; c.vstart = 0; c.vhost = 0;
@@ -491,19 +507,24 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
         L = best_lane(c, set);
         g = (int)((job >> 16) & 7u) + 1;
         // (a long queue can push a job beyond the int32 time range: f + 1 is negative then)
-        bad = (r.todo == 0 ? -1 : 0) | (int32_t)job | (NGPU - (L >> 3) - g) | (other_t - T) | (int32_t)((uint32_t)f + 1u);
+        bad = (r.todo == 0 ? -1 : 0) | (int32_t)job | (NGPU - L / c.PER - g) | (other_t - T) | (int32_t)((uint32_t)f + 1u);
       };
       look_at_next();
       while (__builtin_expect(bad >= 0, 1)) {
         uint32_t wl = (uint32_t)lane_get((int)c.lo[0], L), wh = (uint32_t)lane_get((int)c.hi[0], L);
-        if constexpr (NS == 2) {
+        if constexpr (Ctx<NW>::NS == 2) {
           const uint32_t vl = (uint32_t)lane_get((int)c.lo[1], L), vh = (uint32_t)lane_get((int)c.hi[1], L);
           wl = set ? vl : wl; wh = set ? vh : wh;
         }
-        const uint32_t h = (uint32_t)__builtin_ctzll(((uint64_t)wh << 32) | wl) | ((uint32_t)(L & 7) << 6) | ((uint32_t)set << 9);
-        // from lane L to lane L + 8 g, which is not there for a host that is full now (8 g in two steps: a shift is by 63 at most)
-        const uint64_t from = 1ull << L;
-        flip_host(c, from | ((from << (4 * g)) << (4 * g)), h);
+        const uint32_t h = (uint32_t)__builtin_ctzll(((uint64_t)wh << 32) | wl) | ((uint32_t)(L % c.PER) << 6) | ((uint32_t)set << 9);
+        if constexpr (Ctx<NW>::ALL_LEVELS) {
+          const uint32_t from = 1u << L;
+          flip_host(c, from | (from << g), h);
+        } else {
+          // from lane L to lane L + 8 g, which is not there for a host that is full now (8 g in two steps: a shift is by 63 at most)
+          const uint64_t from = 1ull << L;
+          flip_host(c, from | ((from << (4 * g)) << (4 * g)), h);
+        }
         c.vstart = (int32_t)lane_set((uint32_t)c.vstart, (uint32_t)i, (uint32_t)T);
         c.vhost = lane_set(c.vhost, (uint32_t)i, h);
         r.now = T;
@@ -511,7 +532,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
         if (f <= r.mid_t) {
           const uint32_t k = h | ((uint32_t)(g - 1) << G_SHIFT);
           const bool near = f <= r.win_t;
-          if (near & (r.qe < Q_CAP)) {
+          if (((r.win_t - f) | (Q_CAP - 1 - r.qe)) >= 0) {
             insert_completion(c, r, f, k);
           } else {
             const bool mid = !near & (r.mid_n < MID_CAP);
@@ -555,7 +576,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
           }
           give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1);
         }
-        if (fits(best_lane(c, set), g)) break;             // it starts at T, in the loop above
+        if (fits(c, best_lane(c, set), g)) break;             // it starts at T, in the loop above
         if (!asked) ask_for_host(c, r, dlog, s, T);         // (it starts before this path is left)
         asked = true;
         // the listed completions, instant by instant, for as long as none leaves a host with the GPUs idle
@@ -566,7 +587,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
           do {
             const uint32_t k = r.q_k;
             pop_completion(c, r);
-            found = found | fits(give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1), g);
+            found = found | fits(c, give_back(c, k & HOST_MASK, (int)((k >> G_SHIFT) & 7u) + 1), g);
           } while (r.q_t == T);
         }
         if (found) break;

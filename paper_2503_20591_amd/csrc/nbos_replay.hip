@@ -366,9 +366,10 @@ template <uint32_t F> void set_reg_closed_kernel(nbos_replay *h, int nj) {
   set_kernel(h, reg_closed_kernel_for<F>(nj), "regk::nbos_replay_reg_closed_kernel<%d, %uu>", nj > 8 ? 8 : nj, F);
 }
 
-// the Batch baseline's kernel: a set of registers per 512 hosts
-template <int NS> void set_batch_kernel(nbos_replay *h) {
-  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NS>, "batchk::nbos_replay_batch_kernel<%d>", NS, 0u);
+// the Batch baseline's kernel for clusters of up to 64, 512 or 1,024 hosts (256 replays of 20,000 cells: 64 hosts 5.90 ms
+// with the first instance, 65 hosts 6.41 with the second; 512 hosts fill the lanes of one set of registers)
+template <int NW> void set_batch_kernel(nbos_replay *h) {
+  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NW>, "batchk::nbos_replay_batch_kernel<%d>", NW, 0u);
 }
 
 // LDS of a replay with its hosts in registers: counters, 8 bytes per session, the pre-warmed pool
@@ -449,8 +450,9 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
                          ((cfg->flags & NBOS_F_SCALE_OUT) ? (size_t)HP * 4 : 0);
     sh->listed = n_cap > (size_t)batchk::MID_CAP && least + batchk::MID_CAP * 8 <= (size_t)maxlds;
     h->lds_bytes = least + (sh->listed ? batchk::MID_CAP * 8 : 0);
-    if (chunks <= 8) set_batch_kernel<1>(h);
-    else set_batch_kernel<2>(h);
+    if (chunks <= 1) set_batch_kernel<1>(h);
+    else if (chunks <= 8) set_batch_kernel<8>(h);
+    else set_batch_kernel<16>(h);
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
     // hosts in registers; 8 bytes per session
     h->lds_bytes = reg_lds_bytes(n_cap, warm_pool);

@@ -18,10 +18,11 @@ def crowded(seed, hosts, G, sessions_per_host, cells_per_session, gap_s=5.0, dur
 
 
 @pytest.mark.parametrize("grow", [False, True], ids=["fixed", "grow"])
-@pytest.mark.parametrize("hosts,G", [(1, 8), (2, 1), (63, 8), (64, 3), (65, 8), (128, 2), (129, 1), (256, 4), (257, 3), (512, 2),
+@pytest.mark.parametrize("hosts,G", [(1, 8), (2, 1), (63, 8), (64, 3), (64, 8), (65, 8), (128, 2), (129, 1), (256, 4), (257, 3), (512, 2),
                                      (513, 1), (768, 2), (769, 3), (1024, 1), (1024, 2)])
 def test_batch_kernel_at_its_chunk_edges(rp, oracle, hosts, G, grow):  # noqa: F811
-    # 64 hosts to a word, 512 to a set of registers; of 8 slots per host those beyond G are held for ever
+    # 64 hosts to a word, 512 to a set of registers; of 8 slots per host those beyond G are held for ever (on up to 64
+    # hosts the full ones have a lane of their own)
     b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, gpus_per_host=G),
                 [crowded(7, hosts, G, 3, 3), crowded(8, hosts, G, 2, 2)], [0, 1, 0], [1000, 1000, 1000], f"edge{hosts}")
     as_batch(b, delay=15_000, scale_out=grow)
