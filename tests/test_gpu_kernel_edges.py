@@ -3,6 +3,7 @@
 import numpy as np
 import pytest
 
+from helpers import events_to_arrays
 from paper_2503_20591_amd import tracegen as tg
 from test_gpu_parity import as_batch, assert_same, gpu_run, rp  # noqa: F401  (rp: the fixture)
 
@@ -56,6 +57,28 @@ def test_batch_completions_in_order(rp, oracle, hosts, sessions, step_ms, delay,
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
     assert st["cells_started"].min() > 0
+
+
+@pytest.mark.parametrize("hosts", [10, 64, 100, 600])
+@pytest.mark.parametrize("sizes", [(62, 63, 64, 65, 128, 390), (63, 64, 65, 511, 512, 513, 700, 700)], ids=["few", "listed"])
+def test_batch_crowds_of_completions(rp, oracle, hosts, sizes):  # noqa: F811
+    # per size as many jobs that end at one instant (where the hosts take them all at once), a few before and after it, and
+    # arrivals around it: crowds that just fit into the registers and the list, just do not, and two of them 1 ms apart
+    rng, ev = np.random.default_rng(hosts), []
+    for w, size in enumerate(sizes):
+        at = 2_000_000 * w + 1_000_000
+        ends = [at] * size + [at - 3, at - 1, at - 1, at + 1, at + 2] + ([at + 1] * 70 if w % 2 else [])
+        for s, (start, end) in enumerate(zip(sorted(rng.integers(at - 900_000, at - 1000, len(ends))), rng.permutation(ends))):
+            ev.append([int(start), tg.EV_CELL, s, int(end - start)])
+        ev += [[at + int(d), tg.EV_CELL, len(ends) + k, 500 + k] for k, d in enumerate(sorted(rng.integers(-3, 4, 40)))]
+    n = 1 + max(e[2] for e in ev)
+    assert n <= 512 or sizes[-1] > 512
+    t, d, sk = events_to_arrays(ev)
+    gpus = np.where(rng.random(n) < 0.9, 1, 2).astype(np.uint8)
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts), [(t, d, sk, gpus)], [0, 0], [1000, 1000], "crowds")
+    st, logs = gpu_run(rp, as_batch(b, delay=0, scale_out=False), log=True)
+    assert_same(rp, oracle, b, st, logs, check=True)
+    assert hosts < 100 or st["cells_started"].min() == len(ev)
 
 
 def cell_timers_at_once(b, log):
