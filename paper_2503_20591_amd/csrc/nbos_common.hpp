@@ -72,7 +72,7 @@ struct KParams {
   int32_t batch_delay;     // Batch baseline: container start per job
   int32_t warm_n, warm_migr, prewarm;   // pre-warmed containers per host, warm migration delay, pre-warm time
   int32_t n_cap;           // LDS capacity: sessions
-  int32_t batch;           // event-parallel rounds on (LDS kernel); Batch kernel: its list of completions is there
+  int32_t batch;           // event-parallel rounds on (LDS kernel)
   // closed loop only. cl_chain: per event of the traces {the next event of its session (index within
   // the trace, -1: none), the think time before that event}; the second word is -1 for an event no
   // chain holds. cl_cursor: per replay and session the event that is due next or under way.

@@ -12,10 +12,15 @@
 // not by latency: 46 scalar instructions per job and completion in place of 67 take 4,096 replays of 16, 30 and 64 hosts
 // with 3,000 cells from 2.86, 2.56 and 3.44 ms to 2.34, 2.08 and 2.81 (with a key per host 2.35, 2.31 and 3.35).
 // Completions: the earliest ones, in the order of their times, in registers (qt, qk: entry i in lane i, qe of them,
-// at most 63): all running jobs that finish up to win_t. With more than MID_CAP sessions (p.batch) those that
-// finish up to mid_t are in a list in LDS as well (mid_t[], mid_k[], in no order), the others are found in the session
-// records only: a refill of the registers looks through a few hundred of the list, once per about 40 jobs, and the
-// list is made anew from all records once per few hundred.
+// at most 63): all running jobs that finish up to win_t. With more than MID_CAP sessions those that finish up to mid_t are
+// in a list in LDS as well (mid_t[], mid_k[], in no order), the others are found in the session records only: a refill of
+// the registers looks through a few hundred of the list, once per about 40 jobs, and the list is made anew from all
+// records once per few hundred.
+// Two jobs of one session in a tile of 64 events: the second is dropped if the first outlasts its arrival. With at most
+// MID_CAP sessions (FEW) that is common, and a start looks for its session's other lanes then and there (two comparisons,
+// seven scalar instructions); with more it is rare, and such arrivals leave the loop of starts for a look at the record
+// (as all did before: 4,096 replays of 2,000 cells, 3 and 25 sessions on 16 hosts 1.67 and 1.36 ms, now 0.90 and 0.90;
+// 400 sessions on 30 hosts, 256 replays of 20,000 cells, 6.36 and 6.20).
 // Hosts being provisioned come up in the order of their index (all take the same time): next_up, ready[].
 // Sessions in LDS: time[] and meta[] of the latest job: finish, host | (g - 1) << 27.
 //
@@ -58,8 +63,8 @@ struct Lds {
   int32_t *ready;               // [hosts] when a host that was added comes up
 };
 
-// NW: words of 64 hosts per level (1, 8, or 16 in two sets of 8)
-template <int NW>
+// NW: words of 64 hosts per level (1, 8, or 16 in two sets of 8). FEW: at most MID_CAP sessions
+template <int NW, bool FEW>
 struct Ctx {
   static constexpr int NS = NW > 8 ? 2 : 1;
   static constexpr int PER = NW > 8 ? 8 : NW;         // lanes per level
@@ -68,7 +73,6 @@ struct Ctx {
   Lds m;
   int lane;
   int n_sess;
-  int mid_sink;                 // a word of the list in LDS that nobody reads
   uint32_t lo[NS], hi[NS];      // the levels, see above
   int32_t qt;                   // completions: finish,
   uint32_t qk;                  // and the session's meta word
@@ -76,27 +80,28 @@ struct Ctx {
   // have started: when, where
   int32_t vt, vfd;
   uint32_t vjob;
+  uint32_t vsid;                // (FEW) the session
   int32_t vstart;
   uint32_t vhost;
   uint64_t power;               // see digest_powers
 };
 
 struct State {
-  uint32_t c_total, c_started, c_imm, c_busy, n_dec;
+  uint32_t c_total, c_started, c_imm, n_dec;
   int32_t qe, q_t;              // completions: how many, the next one's time (NEVER: none listed)
   uint32_t q_k;                 // ... and meta word
   int32_t win_t, win;           // all that finish up to win_t are listed; the window the next refill takes
-  int32_t mid_t, mid_n;         // the list in LDS: all that finish up to mid_t >= win_t (with few sessions: win_t, and all of them)
+  int32_t mid_t, mid_n;         // the list in LDS: all that finish up to mid_t >= win_t (with few sessions: not looked at)
   int32_t mid_win;
   int32_t next_up, up_t;        // the next host to come up and when (NEVER: none is being provisioned)
   int32_t n_on;
-  int32_t now;                  // when the latest job started; the hosts have been advanced at least to there
+  int32_t now;                  // no job to come meets the scheduler before this: the latest one did, or has started, at this time
   // a job that has started, finishes within the lists' windows and finds no room there (p_f < 0: none)
   int32_t p_f;
   uint32_t p_k;
-  uint64_t todo;                // arrivals of the tile that are still to come,
-  uint64_t unsaved;             // ... and those that were when the records were last written
-  uint64_t started, folded;     // jobs of the tile whose records are written; whose decisions are in the digest
+  uint64_t jobs, todo;          // arrivals of the tile that have not been dropped; those of them that are still to come
+  uint64_t saved;               // jobs of the tile whose records are written (FEW: that are not their session's latest any more)
+  uint64_t folded;              // ... whose decisions are in the digest
   uint64_t digest;
   int64_t prov;
   int32_t latest_up, t_end;
@@ -104,8 +109,8 @@ struct State {
 };
 
 // the host (set, word, bit) that the lanes of `flip` stand for moves between the levels of those lanes
-template <int NW>
-__device__ __forceinline__ void flip_host(Ctx<NW> &c, uint64_t flip, uint32_t h) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void flip_host(Ctx<NW, FEW> &c, uint64_t flip, uint32_t h) {
 #pragma unroll
   for (int s = 0; s < c.NS; s++) {
     const uint64_t here = c.NS == 1 || (int)(h >> 9) == s ? flip : 0ull;
@@ -116,12 +121,12 @@ __device__ __forceinline__ void flip_host(Ctx<NW> &c, uint64_t flip, uint32_t h)
 }
 
 // the g GPUs that a job held on host h are idle again (a host that comes up: all G); returns the host's lane from now on
-template <int NW>
-__device__ __forceinline__ int give_back(Ctx<NW> &c, uint32_t h, int g) {
+template <int NW, bool FEW>
+__device__ __forceinline__ int give_back(Ctx<NW, FEW> &c, uint32_t h, int g) {
   uint32_t lo = c.lo[0], hi = c.hi[0];
-  if constexpr (Ctx<NW>::NS == 2) { lo = h >> 9 ? c.lo[1] : lo; hi = h >> 9 ? c.hi[1] : hi; }
+  if constexpr (Ctx<NW, FEW>::NS == 2) { lo = h >> 9 ? c.lo[1] : lo; hi = h >> 9 ? c.hi[1] : hi; }
   const uint32_t there = (uint32_t)((((uint64_t)hi << 32) | lo) >> (h & 63u)) & 1u;
-  if constexpr (Ctx<NW>::ALL_LEVELS) {
+  if constexpr (Ctx<NW, FEW>::ALL_LEVELS) {
     const uint32_t from = (uint32_t)wballot(there != 0u), to = from >> g;
     flip_host(c, from | to, h);
     return __builtin_ctz(to);
@@ -140,8 +145,8 @@ __device__ __forceinline__ int32_t due_time(const State &r) { return min(min(r.q
 // Which of the n times at `times` lie in [from, from + win]? They and their keys come to lie side by side in stage_t and
 // stage_k (the first 64); returned are how many there are, and the earliest time beyond (as a distance from `from`; 2^31
 // or more: none). Times before `from` wrap to large distances. Both arrays are read four at a time.
-template <int NW>
-__device__ __forceinline__ int scan_window(const Ctx<NW> &c, const int32_t *times, const uint32_t *keys, int n, int32_t from, uint32_t win, uint32_t &left) {
+template <int NW, bool FEW>
+__device__ __forceinline__ int scan_window(const Ctx<NW, FEW> &c, const int32_t *times, const uint32_t *keys, int n, int32_t from, uint32_t win, uint32_t &left) {
   const int4 *time4 = (const int4 *)times, *key4 = (const int4 *)keys;
   int cnt = 0;
   uint32_t mn = 0xFFFFFFFFu;
@@ -183,8 +188,8 @@ __device__ __forceinline__ uint32_t narrower(uint32_t win, int cnt, int aim, int
 
 // The list in LDS anew: the running jobs that finish within a window from `from` on, at most MID_CAP (the window adapts
 // to find 192 to 384); more at one instant: none, and the registers are refilled from the records.
-template <int NW>
-__device__ __forceinline__ void list_jobs(Ctx<NW> &c, State &r, int32_t from) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void list_jobs(Ctx<NW, FEW> &c, State &r, int32_t from) {
   const int4 *time4 = (const int4 *)c.m.time, *key4 = (const int4 *)c.m.meta;
   const int quads = (c.n_sess + 3) >> 2;
   uint32_t win = (uint32_t)r.mid_win;
@@ -236,10 +241,9 @@ __device__ __forceinline__ void list_jobs(Ctx<NW> &c, State &r, int32_t from) {
 
 // The list in the registers is empty and time goes on beyond win_t, at most to t: the completions of the next window come in.
 // More than fit into the registers at one instant: they are all applied at once if they are due at t, or left until they are.
-template <int NW>
-__device__ __forceinline__ void refill(Ctx<NW> &c, State &r, int32_t t) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void refill(Ctx<NW, FEW> &c, State &r, int32_t t) {
   wave_sync();
-  const bool few = c.p.batch == 0;
   int32_t from = r.win_t + 1;
   uint32_t win = (uint32_t)r.win, left, most;
   int cnt, n;
@@ -251,7 +255,7 @@ __device__ __forceinline__ void refill(Ctx<NW> &c, State &r, int32_t t) {
   for (;;) {
     times = c.m.time; keys = c.m.meta; n = c.n_sess;
     most = (uint32_t)(ALL - from);            // (from <= ALL: a finish is below NEVER)
-    if (!few) {
+    if constexpr (!FEW) {
       if (r.mid_t < from) list_jobs(c, r, from);
       if (r.mid_t >= from) { times = c.m.mid_t; keys = c.m.mid_k; n = r.mid_n; most = (uint32_t)(r.mid_t - from); }
     }
@@ -259,7 +263,7 @@ __device__ __forceinline__ void refill(Ctx<NW> &c, State &r, int32_t t) {
     cnt = scan_window(c, times, keys, n, from, win, left);
     if (cnt == 0) {
       from += left < 0x80000000u ? (int32_t)left : (int32_t)most + 1;      // nothing (listed) up to there
-      if (from > ALL) { r.win_t = ALL; r.mid_t = few ? ALL : r.mid_t; return; }
+      if (from > ALL) { r.win_t = ALL; return; }
       win = from == crowd ? 0u : (uint32_t)r.win;
       continue;
     }
@@ -302,8 +306,8 @@ __device__ __forceinline__ void refill(Ctx<NW> &c, State &r, int32_t t) {
 }
 
 // a job that finishes at f goes into the list in the registers (there is room)
-template <int NW>
-__device__ __forceinline__ void insert_completion(Ctx<NW> &c, State &r, int32_t f, uint32_t k) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void insert_completion(Ctx<NW, FEW> &c, State &r, int32_t f, uint32_t k) {
   const int pos = __builtin_popcountll(wballot(c.qt <= f));
   const int32_t st = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x138, 0xF, 0xF, false);          // wave_shr:1
   const uint32_t sk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x138, 0xF, 0xF, false);
@@ -316,8 +320,8 @@ __device__ __forceinline__ void insert_completion(Ctx<NW> &c, State &r, int32_t 
 
 // The job that has started finishes at p_f <= mid_t, and there was no room where that belongs: the list in LDS is given
 // up, or (if the registers are still full) the latest instant in the registers, and that list with it.
-template <int NW>
-__device__ __forceinline__ void make_room(Ctx<NW> &c, State &r) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void make_room(Ctx<NW, FEW> &c, State &r) {
   const int32_t f = r.p_f;
   r.p_f = -1;
   if (f <= r.win_t) {
@@ -336,8 +340,8 @@ __device__ __forceinline__ void make_room(Ctx<NW> &c, State &r) {
 }
 
 // the next completion leaves the list
-template <int NW>
-__device__ __forceinline__ void pop_completion(Ctx<NW> &c, State &r) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void pop_completion(Ctx<NW, FEW> &c, State &r) {
   c.qt = __builtin_amdgcn_update_dpp(c.qt, c.qt, 0x130, 0xF, 0xF, false);                // wave_shl:1
   c.qk = (uint32_t)__builtin_amdgcn_update_dpp((int)c.qk, (int)c.qk, 0x130, 0xF, 0xF, false);
   r.qe--;
@@ -346,13 +350,13 @@ __device__ __forceinline__ void pop_completion(Ctx<NW> &c, State &r) {
 
 // The ready host with the fewest held GPUs, lowest index first: its lane (8 level + word; beyond level 7: all are full).
 // The choice of the set comes back in `set`.
-template <int NW>
-__device__ __forceinline__ int best_lane(const Ctx<NW> &c, int &set) {
+template <int NW, bool FEW>
+__device__ __forceinline__ int best_lane(const Ctx<NW, FEW> &c, int &set) {
   const uint64_t a = wballot((c.lo[0] | c.hi[0]) != 0u);
   set = 0;
-  if constexpr (Ctx<NW>::ALL_LEVELS) return (int)__builtin_ctzll(a);     // (a host is in some lane)
+  if constexpr (Ctx<NW, FEW>::ALL_LEVELS) return (int)__builtin_ctzll(a);     // (a host is in some lane)
   int L = a != 0 ? (int)__builtin_ctzll(a) : WAVE;
-  if constexpr (Ctx<NW>::NS == 2) {
+  if constexpr (Ctx<NW, FEW>::NS == 2) {
     const uint64_t b = wballot((c.lo[1] | c.hi[1]) != 0u);
     const int L1 = b != 0 ? (int)__builtin_ctzll(b) : WAVE;
     set = (L1 >> 3) < (L >> 3) ? 1 : 0;
@@ -360,26 +364,25 @@ __device__ __forceinline__ int best_lane(const Ctx<NW> &c, int &set) {
   }
   return L;
 }
-template <int NW>
-__device__ __forceinline__ bool fits(const Ctx<NW> &, int L, int g) { return L / Ctx<NW>::PER + g <= NGPU; }
+template <int NW, bool FEW>
+__device__ __forceinline__ bool fits(const Ctx<NW, FEW> &, int L, int g) { return L / Ctx<NW, FEW>::PER + g <= NGPU; }
 
 // The records of the tile's jobs that have started since this was last done (before anyone looks at the records: a refill,
 // a second arrival of a session in the tile, the next tile).
-template <int NW>
-__device__ __forceinline__ void save_records(Ctx<NW> &c, State &r) {
-  const uint64_t jobs = r.unsaved & ~r.todo;
+template <int NW, bool FEW>
+__device__ __forceinline__ void save_records(Ctx<NW, FEW> &c, State &r) {
+  const uint64_t started = r.jobs & ~r.todo;
   wave_sync();
-  const bool mine = in_mask(jobs);
+  const bool mine = in_mask(started & ~r.saved);
   const int s = (int)(c.vjob & 0xFFFFu);
   *(mine ? &c.m.time[s] : c.m.stage_t + WAVE) = job_finish(c.vstart, c.vfd);
   *(mine ? &c.m.meta[s] : c.m.stage_k + WAVE) = c.vhost | (((c.vjob >> 16) & 7u) << G_SHIFT);
-  r.started |= jobs;
-  r.unsaved = r.todo;
+  if constexpr (!FEW) r.saved = started;
 }
 
 // The decisions of the tile's jobs in `jobs` go into the digest (they are the latest ones), and into the log.
-template <int NW>
-__device__ __forceinline__ void fold_jobs(Ctx<NW> &c, State &r, uint64_t *dlog, uint64_t jobs) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void fold_jobs(Ctx<NW, FEW> &c, State &r, uint64_t *dlog, uint64_t jobs) {
   const uint32_t lo = c.vhost | ((uint32_t)NBOS_D_BATCH_START << 12) | (c.vjob << 16);
   r.digest = fold_decisions(r.digest, c.power, jobs, lo, (uint32_t)c.vstart);
   if (__builtin_expect(dlog != nullptr, 0)) {
@@ -395,8 +398,8 @@ __device__ __forceinline__ void fold_jobs(Ctx<NW> &c, State &r, uint64_t *dlog, 
 }
 
 // the job of session s finds no host at time T: it asks for one more host
-template <int NW>
-__device__ __forceinline__ void ask_for_host(Ctx<NW> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
+template <int NW, bool FEW>
+__device__ __forceinline__ void ask_for_host(Ctx<NW, FEW> &c, State &r, uint64_t *dlog, uint32_t s, int32_t T) {
   if (!(c.p.flags & NBOS_F_SCALE_OUT) || r.n_on >= c.p.Hmax) return;
   const int32_t up = add_in_range(T, c.p.boot);          // (a host that comes up at the end of the range ends the replay)
   r.status = up == NEVER ? (int32_t)NBOS_E_RANGE : r.status;
@@ -405,7 +408,7 @@ __device__ __forceinline__ void ask_for_host(Ctx<NW> &c, State &r, uint64_t *dlo
   c.m.ready[h] = up;
   r.up_t = r.next_up == h ? up : r.up_t;
   r.latest_up = max(r.latest_up, up);
-  fold_jobs(c, r, dlog, (r.started | (r.unsaved & ~r.todo)) & ~r.folded);
+  fold_jobs(c, r, dlog, r.jobs & ~r.todo & ~r.folded);
   const uint64_t code = decision_code(T, NBOS_D_BATCH_HOST, s, 0u, (uint32_t)h);
   r.digest = r.digest * DIGEST_PRIME + code;
   if (__builtin_expect(dlog != nullptr, 0)) {
@@ -414,7 +417,7 @@ __device__ __forceinline__ void ask_for_host(Ctx<NW> &c, State &r, uint64_t *dlo
   r.n_dec++;
 }
 
-template <int NW>
+template <int NW, bool FEW>
 __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int rep = launch_slot_replay(p);
@@ -429,15 +432,14 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
 
   Lds m;
   unsigned char *q = lds_raw;
-  const bool few = p.batch == 0;
   const size_t n4 = (size_t)((p.n_cap + 3) / 4 * 4);   // (read four at a time)
   m.hist = (uint32_t *)q;           q += (32 + WAVE) * 4;
   m.stage_t = (int32_t *)q;         q += (WAVE + 4) * 4;
   m.stage_k = (uint32_t *)q;        q += (WAVE + 4) * 4;
   m.time = (int32_t *)q;            q += n4 * 4;
   m.meta = (uint32_t *)q;           q += n4 * 4;
-  m.mid_t = (int32_t *)q;           q += (few ? 4 : MID_CAP + 4) * 4;              // (and a word where nothing is kept)
-  m.mid_k = (uint32_t *)q;          q += (few ? 4 : MID_CAP + 4) * 4;
+  m.mid_t = (int32_t *)q;           q += FEW ? 0 : (MID_CAP + 4) * 4;              // (and a word where nothing is kept)
+  m.mid_k = (uint32_t *)q;          q += FEW ? 0 : (MID_CAP + 4) * 4;
   m.ready = (int32_t *)q;
 
   if (lane < 32) m.hist[lane] = 0;
@@ -446,7 +448,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   for (int s = lane; s < n_sess; s += WAVE) m.meta[s] = ((uint32_t)p.sess_gpus[s_lo + s] - 1u) << G_SHIFT;
   __syncthreads();
 
-  Ctx<NW> c{p, m, lane, n_sess, few ? 0 : MID_CAP};
+  Ctx<NW, FEW> c{p, m, lane, n_sess};
 #pragma unroll
   for (int s = 0; s < c.NS; s++) {
     // the hosts that are there from the start are on the level of the slots that are not; the others count as full
@@ -493,20 +495,24 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     const uint32_t rm = m.meta[sid];
     // a cell whose session's previous job has started and outlasts it is dropped
     const bool drop = is_cell & (rt > c.vt);
-    // lanes whose session has an earlier lane in the tile look again at their turn: every lane's mark goes to its session's
-    // record, in bits that are 0 there, and the lowest lane's is the largest
-    atomicMax(is_cell & !drop ? &m.meta[sid] : m.stage_k + WAVE, rm | ((uint32_t)(WAVE - lane) << 16));
-    wave_sync();
-    const uint32_t first = m.meta[sid];
-    wave_sync();
-    m.meta[sid] = rm;
     c.vfd = (int32_t)((uint32_t)p.batch_delay + (uint32_t)vd);
-    c.vjob = sid | (((rm >> G_SHIFT) & 7u) << 16) | (((first >> 16) & 127u) != (uint32_t)(WAVE - lane) ? SLOW : 0u);
+    c.vjob = sid | (((rm >> G_SHIFT) & 7u) << 16);
+    if constexpr (FEW) {
+      c.vsid = sid;
+    } else {
+      // lanes whose session has an earlier lane in the tile look again at their turn: every lane's mark goes to its session's
+      // record, in bits that are 0 there, and the lowest lane's is the largest
+      atomicMax(is_cell & !drop ? &m.meta[sid] : m.stage_k + WAVE, rm | ((uint32_t)(WAVE - lane) << 16));
+      wave_sync();
+      const uint32_t first = m.meta[sid];
+      wave_sync();
+      m.meta[sid] = rm;
+      c.vjob |= ((first >> 16) & 127u) != (uint32_t)(WAVE - lane) ? SLOW : 0u;
+    }
     r.c_total += (uint32_t)__builtin_popcountll(wballot(is_cell));
-    r.c_busy += (uint32_t)__builtin_popcountll(wballot(drop));
     r.todo = wballot(is_cell & !drop);
-    r.unsaved = r.todo;
-    r.started = 0; r.folded = 0;
+    r.jobs = r.todo;
+    r.saved = 0; r.folded = 0;
     while (r.todo != 0) {
       if (__builtin_expect(r.p_f >= 0, 0)) make_room(c, r);
       // ---- jobs that start when they first meet the scheduler, the listed completions due before each applied on the
@@ -519,7 +525,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
       auto look_at_next = [&]() {
         i = (int)__builtin_ctzll(r.todo | (1ull << 63));
         job = (uint32_t)lane_get((int)c.vjob, i);
-        T = max(lane_get(c.vt, i), r.now);
+        T = r.now = max(lane_get(c.vt, i), r.now);
         f = (int32_t)((uint32_t)T + (uint32_t)lane_get(c.vfd, i));      // (below 2^32)
         while (r.q_t <= T) {
           const uint32_t k = r.q_k;
@@ -534,12 +540,12 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
       look_at_next();
       while (__builtin_expect(bad >= 0, 1)) {
         uint32_t wl = (uint32_t)lane_get((int)c.lo[0], L), wh = (uint32_t)lane_get((int)c.hi[0], L);
-        if constexpr (Ctx<NW>::NS == 2) {
+        if constexpr (Ctx<NW, FEW>::NS == 2) {
           const uint32_t vl = (uint32_t)lane_get((int)c.lo[1], L), vh = (uint32_t)lane_get((int)c.hi[1], L);
           wl = set ? vl : wl; wh = set ? vh : wh;
         }
         const uint32_t h = (uint32_t)__builtin_ctzll(((uint64_t)wh << 32) | wl) | ((uint32_t)(L % c.PER) << 6) | ((uint32_t)set << 9);
-        if constexpr (Ctx<NW>::ALL_LEVELS) {
+        if constexpr (Ctx<NW, FEW>::ALL_LEVELS) {
           const uint32_t from = 1u << L;
           flip_host(c, from | (from << g), h);
         } else {
@@ -549,19 +555,27 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
         }
         c.vstart = (int32_t)lane_set((uint32_t)c.vstart, (uint32_t)i, (uint32_t)T);
         c.vhost = lane_set(c.vhost, (uint32_t)i, h);
-        r.now = T;
         r.todo &= r.todo - 1;
-        if (f <= r.mid_t) {
+        if constexpr (FEW) {
+          // of its session's lanes the earlier ones are not the latest job any more (nor the later ones, for now), and
+          // arrivals that it outlasts are dropped
+          const uint64_t same = wballot(c.vsid == (job & 0xFFFFu)), gone = same & wballot(c.vt < f) & r.todo;
+          r.saved = (r.saved | same) & ~(1ull << i);
+          r.todo ^= gone;
+          r.jobs ^= gone;
+        }
+        if (f <= (FEW ? r.win_t : r.mid_t)) {
           const uint32_t k = h | ((uint32_t)(g - 1) << G_SHIFT);
-          const bool near = f <= r.win_t;
           if (((r.win_t - f) | (Q_CAP - 1 - r.qe)) >= 0) {
             insert_completion(c, r, f, k);
           } else {
-            const bool mid = !near & (r.mid_n < MID_CAP);
-            const int at = mid ? r.mid_n : c.mid_sink;
-            c.m.mid_t[at] = f;
-            c.m.mid_k[at] = k;
-            r.mid_n += mid ? 1 : 0;
+            const bool mid = !FEW & (f > r.win_t) & (r.mid_n < MID_CAP);
+            if constexpr (!FEW) {
+              const int at = mid ? r.mid_n : MID_CAP;
+              c.m.mid_t[at] = f;
+              c.m.mid_k[at] = k;
+              r.mid_n += mid ? 1 : 0;
+            }
             r.p_f = mid ? -1 : f;
             r.p_k = k;
             other_t = mid ? other_t : -1;
@@ -573,13 +587,12 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
       // ---- one job that does not start like that ----
       save_records(c, r);
       const uint32_t s = job & 0xFFFFu;
-      if (__builtin_expect((job & SLOW) != 0u, 0)) {
+      if (!FEW && __builtin_expect((job & SLOW) != 0u, 0)) {
         wave_sync();
-        const bool dropped = uni(m.time[s]) > lane_get(c.vt, i);       // its previous job has not finished
-        r.c_busy += dropped ? 1u : 0u;
-        r.todo = dropped ? r.todo & (r.todo - 1) : r.todo;
-        r.unsaved = r.todo;
-        c.vjob = in_mask(1ull << i) ? c.vjob & ~SLOW : c.vjob;
+        const uint64_t here = 1ull << i, gone = uni(m.time[s]) > lane_get(c.vt, i) ? here : 0ull;    // its previous job has not finished
+        r.todo ^= gone;
+        r.jobs ^= gone;
+        c.vjob = in_mask(here) ? c.vjob & ~SLOW : c.vjob;
         continue;
       }
       bool asked = false;
@@ -625,9 +638,9 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     if (r.status != NBOS_OK) break;
     save_records(c, r);
     // the tile's jobs: digest, sums, waits (those that start at once are all in the histogram's bin of the container start)
-    fold_jobs(c, r, dlog, r.started & ~r.folded);
-    r.c_started += (uint32_t)__builtin_popcountll(r.started);
-    const bool mine = in_mask(r.started);
+    fold_jobs(c, r, dlog, r.jobs & ~r.folded);
+    r.c_started += (uint32_t)__builtin_popcountll(r.jobs);
+    const bool mine = in_mask(r.jobs);
     const uint32_t one = mine ? 1u : 0u, g = ((c.vjob >> 16) & 7u) + 1u;
     const uint32_t d = one * (uint32_t)vd, wait = one * (uint32_t)(c.vstart - c.vt);
     r.c_imm += (uint32_t)__builtin_popcountll(wballot(mine & (wait == 0u)));
@@ -661,7 +674,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     out->sessions_placed = 0; out->sessions_rejected = 0;
     out->cells_total = r.c_total; out->cells_immediate = r.c_imm; out->cells_started = r.c_started;
     out->cells_queued = r.c_started - r.c_imm; out->cells_aborted = 0;
-    out->cells_dropped_busy = r.c_busy; out->cells_dropped_unplaced = 0;
+    out->cells_dropped_busy = r.c_total - r.c_started; out->cells_dropped_unplaced = 0;
     out->executor_reused = 0; out->migrations = 0;
     out->scale_out_hosts = (uint32_t)(r.n_on - p.H0); out->scale_in_hosts = 0; out->peak_hosts = (uint32_t)r.n_on;
     out->migrations_warm = 0;

@@ -319,7 +319,6 @@ struct Shape {
   int HP = 0;               // hosts_max rounded up to whole waves
   int n_cap = 1;            // session capacity of a replay's LDS
   bool in_regs = false;     // the register kernel runs
-  bool listed = false;      // Batch kernel: there is room for its list of completions in LDS, and use for it
 };
 
 // the offsets of the traces, copied to the host
@@ -368,8 +367,14 @@ template <uint32_t F> void set_reg_closed_kernel(nbos_replay *h, int nj) {
 
 // the Batch baseline's kernel for clusters of up to 64, 512 or 1,024 hosts (256 replays of 20,000 cells: 64 hosts 5.90 ms
 // with the first instance, 65 hosts 6.41 with the second; 512 hosts fill the lanes of one set of registers)
-template <int NW> void set_batch_kernel(nbos_replay *h) {
-  set_kernel(h, (const void *)batchk::nbos_replay_batch_kernel<NW>, "batchk::nbos_replay_batch_kernel<%d>", NW, 0u);
+template <int NW> void set_batch_kernel_of(nbos_replay *h, bool few) {
+  set_kernel(h, few ? (const void *)batchk::nbos_replay_batch_kernel<NW, true> : (const void *)batchk::nbos_replay_batch_kernel<NW, false>,
+             few ? "batchk::nbos_replay_batch_kernel<%d, true>" : "batchk::nbos_replay_batch_kernel<%d, false>", NW, 0u);
+}
+void set_batch_kernel(nbos_replay *h, int chunks, bool few) {
+  if (chunks <= 1) set_batch_kernel_of<1>(h, few);
+  else if (chunks <= 8) set_batch_kernel_of<8>(h, few);
+  else set_batch_kernel_of<16>(h, few);
 }
 
 // LDS of a replay with its hosts in registers: counters, 8 bytes per session, the pre-warmed pool
@@ -446,13 +451,10 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
     const int chunks = HP / WAVE;
     const size_t rows = (size_t)(chunks <= 2 ? chunks : chunks <= 4 ? 4 : chunks <= 8 ? 8 : chunks <= 12 ? 12 : 16) * WAVE * 32;
     if (rows + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2 > (size_t)maxlds) return NBOS_E_LIMIT;
-    const size_t least = 128 + WAVE * 4 + (WAVE + 4) * 8 + (n_cap + 3) / 4 * 32 + 4 * 8 +
-                         ((cfg->flags & NBOS_F_SCALE_OUT) ? (size_t)HP * 4 : 0);
-    sh->listed = n_cap > (size_t)batchk::MID_CAP && least + batchk::MID_CAP * 8 <= (size_t)maxlds;
-    h->lds_bytes = least + (sh->listed ? batchk::MID_CAP * 8 : 0);
-    if (chunks <= 1) set_batch_kernel<1>(h);
-    else if (chunks <= 8) set_batch_kernel<8>(h);
-    else set_batch_kernel<16>(h);
+    const bool few = n_cap <= (size_t)batchk::MID_CAP;
+    h->lds_bytes = 128 + WAVE * 4 + (WAVE + 4) * 8 + (n_cap + 3) / 4 * 32 + (few ? 0 : (batchk::MID_CAP + 4) * 8) +
+                   ((cfg->flags & NBOS_F_SCALE_OUT) ? (size_t)HP * 4 : 0);
+    set_batch_kernel(h, chunks, few);
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
     // hosts in registers; 8 bytes per session
     h->lds_bytes = reg_lds_bytes(n_cap, warm_pool);
@@ -613,7 +615,6 @@ void fill_params(nbos_replay *h, const Shape &sh) {
   // without, 119 ms with). NBOS_F_ROUNDS_OFF / _ON force the choice (comparison runs, tests).
   const bool closed_loop = (cfg->flags & NBOS_F_CLOSED_LOOP) != 0;
   k.batch = (cfg->flags & NBOS_F_ROUNDS_OFF) ? 0 : (cfg->flags & NBOS_F_ROUNDS_ON) ? 1 : (closed_loop && cfg->hosts_max <= WAVE) ? 0 : 1;
-  if (cfg->flags & NBOS_F_BATCH_MODE) k.batch = sh.listed ? 1 : 0;
   k.cl_chain = (const int2 *)h->d_chain;
   k.cl_cursor = h->d_chain ? h->d_chain + 2 * (size_t)sh.total_ev : nullptr;
 }

@@ -81,6 +81,20 @@ def test_batch_crowds_of_completions(rp, oracle, hosts, sizes):  # noqa: F811
     assert hosts < 100 or st["cells_started"].min() == len(ev)
 
 
+@pytest.mark.parametrize("hosts", [1, 64, 65, 513])
+@pytest.mark.parametrize("sessions", [1, 3, 60, 512, 513])
+def test_batch_arrivals_of_one_session_in_a_tile(rp, oracle, hosts, sessions):  # noqa: F811
+    # a session's next cell arrives up to 15 s (the container start) after the one before has ended, to the second: it is
+    # dropped, or starts in the millisecond in which that one ends; both lanes of a tile of 64 events, or of two tiles
+    on_grid = lambda v: np.maximum(v // 1000, 1) * 1000  # noqa: E731
+    tr = tg.make_trace(31, sessions, max(sessions, 200) * 5 + 7, ramp_ms=60_000, gpus=tg.gpus_uniform,
+                       gap=lambda r, s: on_grid(tg.exp_ms(r, 15.0, s)), dur=lambda r, s: on_grid(tg.exp_ms(r, 8.0, s)), with_end=True)
+    b = tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts), [tr], [0, 0], [1000, 1000], "tile")
+    st, logs = gpu_run(rp, as_batch(b, delay=15_000, scale_out=False), log=True)
+    assert_same(rp, oracle, b, st, logs, check=True)
+    assert st["cells_dropped_busy"].min() > 0
+
+
 def cell_timers_at_once(b, log):
     """The most cells that timers of one instant have started or given up, by the decision log (a closed loop's cells all
     come by timer, an open loop's if they do not arrive at that instant). All of these timers were pending before it."""
