@@ -445,15 +445,15 @@ int32_t choose_kernel(nbos_replay *h, Shape *sh) {
   const size_t n_cap = (size_t)sh->n_cap;
   const bool force_generic = (cfg->flags & NBOS_F_GENERIC_KERNEL) != 0;
   if (batch_mode) {
-    // a record of 8 bytes per session, and where hosts are added the time each comes up. What is accepted stays what it
-    // was when there was a queue as well (2 bytes per session) and a row of 32 bytes per host, for up to 64, 128, 256, 512,
-    // 768 or 1,024 hosts.
+    // The sessions that a call may have are a limit of the interface: 10 bytes each beside 32 per host, for up to 64, 128,
+    // 256, 512, 768 or 1,024 hosts, in 160 KB. The kernels need 8 bytes per session, and 4 per host where hosts are added.
     const int chunks = HP / WAVE;
-    const size_t rows = (size_t)(chunks <= 2 ? chunks : chunks <= 4 ? 4 : chunks <= 8 ? 8 : chunks <= 12 ? 12 : 16) * WAVE * 32;
-    if (rows + 128 + WAVE * 4 + n_cap * 8 + (n_cap + 2) * 2 > (size_t)maxlds) return NBOS_E_LIMIT;
+    const size_t hosts = (size_t)(chunks <= 2 ? chunks : chunks <= 4 ? 4 : chunks <= 8 ? 8 : chunks <= 12 ? 12 : 16) * WAVE;
+    const size_t limit = 32 * hosts + 388 + 10 * n_cap;
     const bool few = n_cap <= (size_t)batchk::MID_CAP;
     h->lds_bytes = 128 + WAVE * 4 + (WAVE + 4) * 8 + (n_cap + 3) / 4 * 32 + (few ? 0 : (batchk::MID_CAP + 4) * 8) +
                    ((cfg->flags & NBOS_F_SCALE_OUT) ? (size_t)HP * 4 : 0);
+    if (std::max(limit, h->lds_bytes) > (size_t)maxlds) return NBOS_E_LIMIT;
     set_batch_kernel(h, chunks, few);
   } else if (closed_loop && cfg->hosts_max <= WAVE && !(cfg->flags & NBOS_F_HOSTS_IN_LDS)) {
     // hosts in registers; 8 bytes per session

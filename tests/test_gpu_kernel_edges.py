@@ -95,6 +95,27 @@ def test_batch_arrivals_of_one_session_in_a_tile(rp, oracle, hosts, sessions):  
     assert st["cells_dropped_busy"].min() > 0
 
 
+@pytest.mark.parametrize("grow", [False, True], ids=["fixed", "grow"])
+@pytest.mark.parametrize("hosts,most", [(64, 16_140), (65, 15_935), (1024, 13_068)])
+def test_batch_sessions_up_to_the_limit(rp, oracle, hosts, most, grow):  # noqa: F811
+    # as many sessions as a call may have, and one more
+    for sessions in (most, most + 1):
+        rng = np.random.default_rng(hosts)
+        t = np.sort(rng.integers(0, 600_000, 3_000)).astype(np.int32)
+        d = rng.integers(1, 400_000, len(t)).astype(np.int32)
+        sk = (rng.integers(sessions - 2_000, sessions, len(t)) | tg.EV_CELL << 24).astype(np.int32)
+        b = tg.pack(tg.base_config(hosts_initial=hosts // 2 if grow else hosts, hosts_max=hosts),
+                    [(t, d, sk, rng.integers(1, 9, sessions).astype(np.uint8))], [0], [1000], "most")
+        b.config.update(flags=tg.F_BATCH_MODE | (tg.F_SCALE_OUT if grow else 0), boot_delay_ms=20_000)
+        if sessions > most:
+            with pytest.raises(rp.NbosError) as e:
+                gpu_run(rp, b)
+            assert e.value.code == rp.E_LIMIT
+        else:
+            st, logs = gpu_run(rp, b, log=True)
+            assert_same(rp, oracle, b, st, logs)
+
+
 def cell_timers_at_once(b, log):
     """The most cells that timers of one instant have started or given up, by the decision log (a closed loop's cells all
     come by timer, an open loop's if they do not arrive at that instant). All of these timers were pending before it."""
