@@ -44,19 +44,46 @@ def on_a_grid(seed, hosts, sessions, step_ms, flags, caps):
     return tg.pack(tg.base_config(hosts_initial=hosts, hosts_max=hosts, flags=flags), [tr], [0] * len(caps), list(caps), "refill")
 
 
+def jobs_run(b, log):
+    """Start and end of every job of a Batch replay, by the decision log and the trace (a cell that arrives before the
+    session's job ends is dropped)."""
+    delay, cells = b.config["batch_start_delay_ms"], [[] for _ in range(len(b.sess_gpus))]
+    for t, d, sk in zip(b.ev_time.tolist(), b.ev_dur.tolist(), b.ev_sk.tolist()):
+        if sk >> 24 == tg.EV_CELL:
+            cells[sk & 0xFFFFFF].append((t, d))
+    start, end, over = [], [], [-1] * len(cells)
+    for code in log.tolist():
+        if code >> 12 & 15 == 10:
+            s, t = code >> 16 & 0xFFFF, code >> 32
+            cell = next(c for c in cells[s] if c[0] >= over[s])
+            cells[s] = cells[s][cells[s].index(cell) + 1:]
+            over[s] = t + delay + cell[1]
+            start.append(t)
+            end.append(over[s])
+    return np.array(start), np.array(end)
+
+
 @pytest.mark.parametrize("grow", [False, True], ids=["fixed", "grow"])
-@pytest.mark.parametrize("hosts,sessions,step_ms,delay", [(40, 60, 1, 0), (40, 512, 1, 15_000), (64, 513, 1, 0), (100, 2000, 1, 15_000),
-                                                          (100, 400, 600_000, 0), (100, 3000, 600_000, 0), (600, 3000, 60_000, 15_000),
-                                                          (600, 6000, 1_200_000, 0), (520, 5000, 1000, 0), (3, 700, 100_000, 15_000)])
-def test_batch_completions_in_order(rp, oracle, hosts, sessions, step_ms, delay, grow):  # noqa: F811
+@pytest.mark.parametrize("hosts,sessions,step_ms,delay,more_than,at_once",
+                         [(40, 60, 1, 0, 0, 1), (40, 512, 1, 15_000, 63, 1), (64, 513, 1, 0, 63, 1), (100, 2000, 1, 15_000, 63, 1),
+                          (100, 400, 600_000, 0, 63, 64), (100, 3000, 600_000, 0, 63, 64), (600, 3000, 60_000, 15_000, 512, 64),
+                          (600, 6000, 1_200_000, 0, 512, 513), (520, 5000, 1000, 0, 512, 2), (40, 700, 100_000, 15_000, 63, 10),
+                          (3, 700, 100_000, 15_000, 0, 2)])
+def test_batch_completions_in_order(rp, oracle, hosts, sessions, step_ms, delay, more_than, at_once, grow):  # noqa: F811
     # the list of completions in registers (63) and the one in LDS (512 jobs, only with more sessions than that): refilled,
-    # pushed into, overrun, and hundreds of jobs (1,200 and more on the coarsest grid) that end at one instant
+    # pushed into, overrun, and hundreds of jobs that end at one instant; the first and the last case never fill the registers
     b = as_batch(on_a_grid(9, hosts, sessions, step_ms, 0, [1000]), delay=delay, scale_out=grow)
     if grow:
         b.config.update(hosts_initial=max(1, hosts // 2), hosts_max=hosts, boot_delay_ms=20_000)
     st, logs = gpu_run(rp, b, log=True)
     assert_same(rp, oracle, b, st, logs)
-    assert st["cells_started"].min() > 0
+    start, end = jobs_run(b, logs[0])
+    assert len(start) == st["cells_started"][0] > 0
+    change = np.concatenate([np.ones(len(start), int), -np.ones(len(end), int)])
+    order = np.lexsort((change, np.concatenate([start, end])))         # at one instant jobs end before others start
+    most = np.cumsum(change[order]).max()
+    assert most > more_than and (more_than > 0 or most <= 63)
+    assert grow or np.unique(end, return_counts=True)[1].max() >= at_once      # (added hosts spread the starts)
 
 
 @pytest.mark.parametrize("hosts", [10, 64, 100, 600])
