@@ -104,7 +104,8 @@ __device__ __forceinline__ void refuse_replay(const KParams &p, int rep, int lan
 __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ int32_t lane_get(int32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
-// v with lane l mod 64 holding x (v_writelane_b32; clang has no builtin for it)
+// v with lane l mod 64 holding x (v_writelane_b32; clang has no builtin for it, so the intrinsic is declared under its own
+// name: with a compiler that does not know it by that name the device link ends with an undefined symbol)
 extern "C" __device__ __attribute__((const)) int nbos_writelane(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
 __device__ __forceinline__ uint32_t lane_set(uint32_t v, uint32_t l, uint32_t x) {
   return (uint32_t)nbos_writelane((int)x, (int)l, (int)v);

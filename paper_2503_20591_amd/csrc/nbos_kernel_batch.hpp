@@ -36,8 +36,9 @@
 // scalar one that reads what the vector side has just produced 20 more, a branch 12 to 25: hence bit scans where
 // a minimum over the keys of all hosts was taken (and the rows of the hosts with a completion read again to refresh
 // them); a job leaves its start and host in its lane, and records, sums, waits and digest are made from those for 64 jobs
-// at a time. 512 hosts, 250,000 jobs, 256 replays: 152.4 ms with a key per host, a minimum over the keys and the queue, 88.2
-// with this; of it 60 % the loop of jobs that start at once (570 clocks per job and completion), 18 % refills.
+// at a time. 512 hosts, 250,000 jobs, 256 replays: 152.4 ms with a key per host, a minimum over the keys and the queue, 84.4
+// with this. By the path profile (500,000 jobs) 53 % are the loop of starts, 600 clocks per job and completion with the
+// marks, 30 % the one job in ten that leaves it (it waits, or has to be preceded by a refill), 15 % refills.
 // Control flow is uniform throughout: a store that one lane would do is done by all lanes.
 #pragma once
 #include "nbos_common.hpp"
@@ -476,6 +477,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
   int32_t latest = 0, max_wait = 0;
 
   // the events: one per lane per tile, next tile in flight
+  PROF_BEGIN();
   int32_t nt = 0, nd = 0, ns = 0;
   if (ev_lo < ev_hi) {
     const int64_t at = min(ev_lo + lane, ev_hi - 1);
@@ -513,7 +515,9 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     r.todo = wballot(is_cell & !drop);
     r.jobs = r.todo;
     r.saved = 0; r.folded = 0;
+    PROF(PC_TILE, 1);
     while (r.todo != 0) {
+      [[maybe_unused]] const uint64_t prof_jobs0 = r.jobs & ~r.todo;
       if (__builtin_expect(r.p_f >= 0, 0)) make_room(c, r);
       // ---- jobs that start when they first meet the scheduler, the listed completions due before each applied on the
       // way: a loop with nothing else in it and one way out. `bad` is negative when it ends: no job of the tile is left (lane
@@ -583,6 +587,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
         }
         look_at_next();
       }
+      PROF(PC_ROUND, __builtin_popcountll((r.jobs & ~r.todo) ^ prof_jobs0));
       if ((r.todo == 0) | (r.p_f >= 0)) continue;
       // ---- one job that does not start like that ----
       save_records(c, r);
@@ -593,13 +598,19 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
         r.todo ^= gone;
         r.jobs ^= gone;
         c.vjob = in_mask(here) ? c.vjob & ~SLOW : c.vjob;
+        PROF(PC_DROP, 1);
         continue;
       }
       bool asked = false;
       for (;;) {
         // what happens to the hosts up to T
         while (due_time(r) <= T) {
-          if (r.win_t < min(r.q_t, r.up_t)) { refill(c, r, min(T, r.up_t)); continue; }
+          if (r.win_t < min(r.q_t, r.up_t)) {
+            PROF(PC_FAIL, 0);
+            refill(c, r, min(T, r.up_t));
+            PROF(PC_TIMER_OTHER, 1);
+            continue;
+          }
           const bool listed = r.q_t <= r.up_t;
           const uint32_t k = listed ? r.q_k : (uint32_t)r.next_up | ((uint32_t)(p.G - 1) << G_SHIFT);
           r.next_up += listed ? 0 : 1;
@@ -634,6 +645,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
       r.status = (uint32_t)T + (uint32_t)lane_get(c.vfd, i) >= 0x7FFFFFFFu ? (int32_t)NBOS_E_RANGE : r.status;
       if (r.status != NBOS_OK) break;
       r.now = T;
+      PROF(PC_FAIL, 1);
     }
     if (r.status != NBOS_OK) break;
     save_records(c, r);
@@ -652,6 +664,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     latest = max(latest, mine ? job_finish(c.vstart, c.vfd) : 0);
     const int b = min(32 - __builtin_clz(wait + (uint32_t)p.batch_delay), 31);      // (of a wait of 0: not looked at)
     atomicAdd(&m.hist[wait != 0u ? b : 32 + lane], 1u);
+    PROF(PC_TILE, 0);
   }
   if (ev_lo < ev_hi) {
     const int32_t tl = p.ev_time[ev_hi - 1];
@@ -685,6 +698,7 @@ __global__ void __launch_bounds__(WAVE) nbos_replay_batch_kernel(KParams p) {
     out->reservation_gpu_ms = 0; out->sub_gpu_ms = 0; out->replica_ms = 0;
     out->digest = r.digest;
   }
+  PROF_OUT(rep);
 }
 
 }  // namespace batchk

@@ -104,9 +104,9 @@ struct Ctx {
 };
 
 // A decision's code goes into the digest (and into the log). The digest is kept in vector registers, the same in all lanes:
-// the scalar unit, which is what many small replays are bound by (0.86 instructions a clock with 64 of them on a
-// compute unit), would take nine instructions for the 64-bit product, the vector side takes four. 24 hosts, 16,384 replays:
-// 45.0 ms with the scalar product, 42.5 with this; 300 short replays 0.766 -> 0.744. (Codes kept in lanes and folded 64 at a
+// the scalar unit, which is what many small replays are bound by (with the scalar product 0.86 instructions a clock with 64
+// of them on a compute unit), would take nine instructions for the 64-bit product, the vector side takes four. 24 hosts,
+// 16,384 replays: 45.0 ms with the scalar product, 42.5 with this; 300 short replays 0.766 -> 0.744. (Codes kept in lanes and folded 64 at a
 // time: 43.5, but 30 hosts 27.2 -> 31.3 and 64 hosts 64.6 -> 71.7, as every path then carries two more registers.)
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void decide_code(Ctx<NJ, F> &c, Regs &r, int32_t now, uint32_t code_lo) {
@@ -590,9 +590,8 @@ __device__ __forceinline__ void start_at_once(Ctx<NJ, F> &c, Regs &r, int32_t &v
 // The tile's cells that started at once (lanes of r.at_once), all at a time: counts on the scalar unit, durations,
 // GPU time added up by the LDS unit, the latest finish per lane. fl: the word of the prefetched record (a session's g never changes). In the
 // loop of starts, bound by the number of its instructions (a lone wave takes 7 clocks for each), these sums were
-// fourteen of 165; with the election's minima on the scalar unit, the binding's lanes as scalar masks and one LDS read
-// for a stale record, 24 hosts went from 50.2 to 47.2 ms (16,384 replays of 20,000 cells), 300 short replays
-// from 0.90 to 0.85 ms, 64 hosts from 71.7 to 69.9 ms.
+// fourteen of 165. Taken out of it, together with other cuts of the same kind: 24 hosts 50.2 -> 47.2 ms (16,384 replays of
+// 20,000 cells), 300 short replays 0.90 -> 0.85, 64 hosts 71.7 -> 69.9.
 template <int NJ, uint32_t F>
 __device__ __forceinline__ void fold_starts(Ctx<NJ, F> &c, Regs &r, int32_t vt, int32_t vd, uint32_t fl) {
   const uint32_t n = (uint32_t)__builtin_popcountll(r.at_once);

@@ -5,8 +5,11 @@
 Loads libnbos_pathprofile.so (the product sources compiled with -DNBOS_PATH_PROFILE; built on demand), runs
 each workload once and prints, for the mean replay and for the slowest one, the share of the clocks of the
 wave that runs the replay that each path of the main loop took, how often it ran, and the clocks per run.
-Marshalling and printing only; the open-loop replay kernels and the closed-loop any-size kernel carry the marks
-(there "other timer" is the scheduling of the next events of the cells a round has started; n = those cells).
+Marshalling and printing only; the open-loop replay kernels, the closed-loop any-size kernel and the Batch kernel carry
+the marks. In the closed loop "other timer" is the scheduling of the next events of the cells a round has started (n = those
+cells). In the Batch kernel "immediate starts" is its loop of starts with the completions on the way, "other timer" a refill
+of the list of completions, "arrival: queued" the rest of a job that does not start in that loop (n = those jobs, also the
+ones that only need a refill), "dropped arrival" the second look at an arrival whose session has an earlier one in the tile.
 The marks cost time themselves, so the launch runs a fifth to two fifths longer than the product build's.
 """
 from __future__ import annotations

@@ -307,8 +307,8 @@ def test_batch_mode_named_workloads(rp, oracle, name, n, hosts):
 
 @pytest.mark.parametrize("h0,hmax,name", [(60, 70, "c2"), (64, 66, "c2"), (63, 129, "c5"), (120, 200, "c3")])
 def test_batch_mode_grows_across_chunks_of_hosts(rp, oracle, h0, hmax, name):
-    # the Batch kernel keeps minima per chunk of 64 hosts on clusters of more than 64: hosts are added on
-    # demand into a chunk that was empty, into one that is partly on, and the last chunk is ragged
+    # the Batch kernel keeps hosts as bits, 64 to a word: hosts are added on demand into a word that was empty, into
+    # one that is partly on, and the last word is ragged
     b = tg.workload(name, n_replays=3)
     as_batch(b, delay=5_000, scale_out=True)
     b.config.update(hosts_initial=h0, hosts_max=hmax, boot_delay_ms=30_000)
