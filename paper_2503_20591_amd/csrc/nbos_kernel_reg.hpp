@@ -332,12 +332,14 @@ __device__ __forceinline__ void bind_words(Ctx<NJ, F> &c, int h, int g, int32_t 
   }
 }
 
-// The same for migrations and new hosts: the one word that counts is made again (one comparison). Two scalar registers per
-// group of hosts, kept over the choice of a target, the pool and a new host for the sake of a few bindings, are spilled on
-// more than 40 hosts: lane reads of the closed loop's instances for 48 and 64 hosts 225 and 424 with the words, 158 and 206
-// with this; 4,096 replays of 48 hosts 6.16 -> 5.99 ms, of 64 hosts 6.15 -> 6.03, open loops the same.
+// The same for migrations and new hosts. On more than 40 hosts the one word that counts is made again (one comparison): two
+// scalar registers per group of hosts, kept over the choice of a target, the pool and a new host for the sake of a few
+// bindings, are spilled there. Lane reads of the closed loop's instances for 48 and 64 hosts 225 and 424 with the words,
+// 158 and 206 with this; 4,096 replays of 48 hosts 6.16 -> 5.99 ms, of 64 hosts 6.15 -> 6.03, open loops the same. On 12
+// hosts with scale-in, 2,048 replays, 3.05 ms with the words and 3.14 with this, on 40 hosts with closed loops 21.47 and 21.60.
 template <int NJ, uint32_t F>
-__device__ __forceinline__ void bind_gpus(Ctx<NJ, F> &c, int h, int g, int32_t finish, int32_t now) {
+__device__ __forceinline__ void bind_late(Ctx<NJ, F> &c, int h, int g, int32_t finish, int32_t now, const uint64_t (&busy)[NJ]) {
+  if constexpr (NJ <= 5) return bind_words(c, h, g, finish, busy);
   const int j = h >> 3, hl = h & 7;
   const uint64_t mine = 0xFFull << (8 * hl);
 #pragma unroll
@@ -683,11 +685,11 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       if (warm) {
         const int32_t start = after(c, now, c.p.warm_migr);
-        bind_gpus(c, dst, g, wrap_add(start, dur), now);
+        bind_late(c, dst, g, wrap_add(start, dur), now, busy);
         start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, NBOS_D_MIGRATE_WARM);
       } else {
         const int32_t start = after(c, now, c.p.migr);
-        bind_gpus(c, dst, g, wrap_add(start, dur), now);
+        bind_late(c, dst, g, wrap_add(start, dur), now, busy);
         start_cell(c, r, s, hw, fl, victim, dst, now, start, t_submit, dur, NBOS_D_MIGRATE);
       }
     } else {
@@ -697,7 +699,7 @@ __device__ __forceinline__ void attempt(Ctx<NJ, F> &c, Regs &r, uint32_t s, uint
       const int h = boot_host(c, r, now, moved);
       wave_sync();
       c32_max(c.m, c.lane, CS_PEAK, uni(c.m.c32[CS_NON]));
-      bind_gpus(c, h, g, wrap_add(start, dur), now);       // (a host that was off has all its GPUs idle)
+      bind_late(c, h, g, wrap_add(start, dur), now, busy);       // (a host that was off has all its GPUs idle)
       c32_add(c.m, c.lane, CS_MIGR, 1u);
       start_cell(c, r, s, hw, fl, victim, h, now, start, t_submit, dur, NBOS_D_SCALE_CELL);
     }
