@@ -10,7 +10,8 @@
 // level l, and level 8 is there as well: every host is in exactly one lane, so that a completion's two lanes are a ballot
 // and that ballot shifted by g. Many replays of a small cluster share a compute unit and are bound by its scalar unit,
 // not by latency: 46 scalar instructions per job and completion in place of 67 take 4,096 replays of 16, 30 and 64 hosts
-// with 3,000 cells from 2.86, 2.56 and 3.44 ms to 2.34, 2.08 and 2.81 (with a key per host 2.35, 2.31 and 3.35).
+// with 3,000 cells from 2.86, 2.56 and 3.44 ms to 2.34, 2.08 and 2.81 (with a key per host 2.35, 2.31 and 3.35; with all
+// that follows 1.61, 1.61 and 2.75).
 // Completions: the earliest ones, in the order of their times, in registers (qt, qk: entry i in lane i, qe of them,
 // at most 63): all running jobs that finish up to win_t. With more than MID_CAP sessions those that finish up to mid_t are
 // in a list in LDS as well (mid_t[], mid_k[], in no order), the others are found in the session records only: a refill of
@@ -349,7 +350,7 @@ __device__ __forceinline__ void pop_completion(Ctx<NW, FEW> &c, State &r) {
   r.q_t = lane_get(c.qt, 0); r.q_k = (uint32_t)lane_get((int)c.qk, 0);
 }
 
-// The ready host with the fewest held GPUs, lowest index first: its lane (8 level + word; beyond level 7: all are full).
+// The ready host with the fewest held GPUs, lowest index first: its lane (level 8 or beyond: all are full).
 // The choice of the set comes back in `set`.
 template <int NW, bool FEW>
 __device__ __forceinline__ int best_lane(const Ctx<NW, FEW> &c, int &set) {

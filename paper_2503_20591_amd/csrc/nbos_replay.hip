@@ -365,8 +365,8 @@ template <uint32_t F> void set_reg_closed_kernel(nbos_replay *h, int nj) {
   set_kernel(h, reg_closed_kernel_for<F>(nj), "regk::nbos_replay_reg_closed_kernel<%d, %uu>", nj > 8 ? 8 : nj, F);
 }
 
-// the Batch baseline's kernel for clusters of up to 64, 512 or 1,024 hosts (256 replays of 20,000 cells: 64 hosts 5.90 ms
-// with the first instance, 65 hosts 6.41 with the second; 512 hosts fill the lanes of one set of registers)
+// the Batch baseline's kernel for clusters of up to 64, 512 or 1,024 hosts (256 replays of 20,000 cells: 64 hosts 5.73 ms
+// with the first, 65 hosts 6.26 with the second; 512 hosts fill the lanes of one set of registers)
 template <int NW> void set_batch_kernel_of(nbos_replay *h, bool few) {
   set_kernel(h, few ? (const void *)batchk::nbos_replay_batch_kernel<NW, true> : (const void *)batchk::nbos_replay_batch_kernel<NW, false>,
              few ? "batchk::nbos_replay_batch_kernel<%d, true>" : "batchk::nbos_replay_batch_kernel<%d, false>", NW, 0u);
